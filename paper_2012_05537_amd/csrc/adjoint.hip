@@ -33,6 +33,7 @@
 #include "nt.h"
 #include "sllbm_internal.h"
 #include "velset.h"
+#include "xcd.h"
 
 namespace sllbm {
 
@@ -96,29 +97,82 @@ __device__ __forceinline__ double bder(const Bracket &b, double c)    // d b / d
 // Collision VJP: lam = J_C(X)^T mu, two lanes per node.  dmu_part[block]
 // receives the block's sum of dL/dmu_inf.
 // ---------------------------------------------------------------------------
+// alpha of a lane in registers
+struct AlphaReg {
+    double v[vs::Q];
+    __device__ __forceinline__ double operator()(int i) const { return v[i]; }
+    __device__ __forceinline__ void refresh(double &) { __builtin_amdgcn_sched_barrier(0); }
+};
+
+// alpha of a lane in LDS (velocity i at base[i * NB + off]).  refresh(x) makes
+// the compiler read it again afterwards, and not before x is known, instead
+// of holding 45 values in registers through the sweep.
+template <typename S, int NB>
+struct AlphaLds {
+    const S *base;
+    int off;
+    __device__ __forceinline__ double operator()(int i) const { return static_cast<double>(base[i * NB + off]); }
+    __device__ __forceinline__ void refresh(double &x)
+    {
+        asm volatile("" : "+v"(off), "+v"(x));
+        __builtin_amdgcn_sched_barrier(0);
+    }
+};
+
 // One lane of the collision VJP (its node's population is_g): X of the node
 // from X + off (stride N), the lane's adjoint inputs alpha_i from AL(i), the
-// partner lane l ^ XM; writes lambda of its population at lp (stride N) and
-// returns the node's dL/dmu_inf (counted on the f lane).  Inactive lanes (a
+// partner lane l ^ XM; writes lambda of its population at lam + off (stride N)
+// and returns the node's dL/dmu_inf (counted on the f lane).  Inactive lanes (a
 // node past the end) compute on node 0 for their partner and write nothing.
+// X is read in groups of pairs, and the sums over the velocities are pinned
+// where they are formed, so that alpha (90 registers, or LDS) and the sums are
+// all that lives through the sweep.
 template <typename S, bool NTH, int XM, class Alpha>
 __device__ __forceinline__ double collide_vjp_lane(int64_t N, const CollisionParams &cp, const S *__restrict__ X,
-                                                   int64_t off, bool is_g, bool active, Alpha &&AL, S *lp)
+                                                   int64_t off, bool is_g, bool active, Alpha AL, S *lam)
 {
     // X enters only through its raw moments and sum alpha h, so it is dead
     // before the sweep
     RawMoments<D3Q45> rm;
-    double dot_ah = 0.0;
+    double dot_ah;
     {
-        double h[vs::Q];
+        // two groups of GP pairs in registers: the next group's loads are in
+        // flight while a group is summed
+        constexpr int GP = 8, NG = (22 + GP - 1) / GP;
+        S h[2][2 * GP];
+        auto load_group = [&](int g) {
 #pragma unroll
-        for (int i = 0; i < vs::Q; ++i) {
-            h[i] = static_cast<double>(load_hint<NTH>(&X[off + static_cast<int64_t>(i) * N]));
+            for (int k = 0; k < GP; ++k) {
+                const int q = g * GP + k;
+                if (q >= 22) continue;
+                h[g & 1][2 * k] = load_hint<NTH>(&X[off + static_cast<int64_t>(vs::PAIRS.a[q]) * N]);
+                h[g & 1][2 * k + 1] = load_hint<NTH>(&X[off + static_cast<int64_t>(vs::PAIRS.b[q]) * N]);
+            }
+        };
+        const S h0 = load_hint<NTH>(&X[off]);
+        load_group(0);
+        clear_moments<D3Q45>(rm);
+        rm.m0 = static_cast<double>(h0);
+        dot_ah = AL(0) * static_cast<double>(h0);
+#pragma unroll
+        for (int g = 0; g < NG; ++g) {
+            asm volatile("" ::: "memory");
+            if (g + 1 < NG) load_group(g + 1);
+            AL.refresh(dot_ah);
+#pragma unroll
+            for (int k = 0; k < GP; ++k) {
+                const int q = g * GP + k;
+                if (q >= 22) continue;
+                const double hi = static_cast<double>(h[g & 1][2 * k]), hj = static_cast<double>(h[g & 1][2 * k + 1]);
+                add_pair_moments<D3Q45>(rm, q, hi, hj);
+                dot_ah = fma(AL(vs::PAIRS.a[q]), hi, dot_ah);
+                dot_ah = fma(AL(vs::PAIRS.b[q]), hj, dot_ah);
+            }
         }
-        rm = raw_moments<D3Q45>(h);
-#pragma unroll
-        for (int i = 0; i < vs::Q; ++i) dot_ah = fma(AL(i), h[i], dot_ah);
     }
+    pin(dot_ah);
+    pin_moments<D3Q45>(rm);
+    AL.refresh(rm.m0);
 
     // ---- forward quantities (as in collide_half) ----
     const double ktr = rm.m2[0] + rm.m2[3] + rm.m2[5];
@@ -135,16 +189,7 @@ __device__ __forceinline__ double collide_vjp_lane(int64_t N, const CollisionPar
     const double T = (K * ir - u2) / (2.0 * Cv);
     double qb[10];
     centred_third<D3Q45>(rm, u, qb);
-    const double P = rho * T;
-    double dfac;
-    const double fac = viscosity_factor(cp, T, dfac);
-    const double mu_v = cp.mu_inf * fac;
-    const double tau = mu_v / (P * cp.dt) + 0.5;
-    const double tau_pr = (tau - 0.5) * cp.inv_pr + 0.5;
-    const double om = 1.0 / tau;
-    const double kap = 1.0 / tau - 1.0 / tau_pr;
     const double th = T - 1.0;
-    const double eqs = is_g ? cp.beta * T : 1.0;
 
     // centred second moment of the own population (for the Qbar -> u term);
     // the raw moments are dead after this
@@ -155,55 +200,89 @@ __device__ __forceinline__ double collide_vjp_lane(int64_t N, const CollisionPar
         for (int b = a; b < 3; ++b)
             C2[sym2(a, b)] = rm.m2[sym2(a, b)] - u[a] * rm.m1[b] - u[b] * rm.m1[a] + rm.m0 * u[a] * u[b];
 
-    Bracket br[4];
-#pragma unroll
-    for (int s = 0; s < 4; ++s) br[s] = bracket(u2, th, vs::SHELL_X2[s]);
-
     // ---- reverse sweep over the velocities (own population) ----
-    double s_ka = 0, s_heq = 0, s_eqT = 0, s_u2 = 0, s_th = 0;
+    // With b(c) = a0 + a1 c + a2 c^2 + c^3/6 + c^4/24 and, over the pairs of a
+    // shell, S0 = sum s, S1 = sum d c, S2 = sum s c^2, S3 = sum d c^3,
+    // S4 = sum s c^4 (s, d: sum and difference of the pair's alpha), the
+    // shell adds w times
+    //   a0 S0 + a1 S1 + a2 S2 + S3/6 + S4/24    to sum alpha b,
+    //   its derivatives in |u|^2 and theta      to s_u2, s_th,
+    //   xi (d o' + s e'), o' = a1 + c^2/2, e' = c (2 a2 + c^2/6), to ubar;
+    // rho and the population's factor of f^eq come in at the end, and
+    // sum alpha h* = sum_m abar_m Qbar_m needs no h* per velocity.
+    double s_b, s_u2, s_th;
     double ubar[3] = {0, 0, 0};
     double abar[10];
 #pragma unroll
     for (int m = 0; m < 10; ++m) abar[m] = 0.0;
     {   // rest velocity: c = 0, h* = 0
-        const double w = vs::T.w[0];
-        const double feq = w * rho * br[0].a0;
-        const double heq = eqs * feq;
-        s_heq = fma(AL(0), heq, s_heq);
-        s_eqT = fma(AL(0), feq, s_eqT);
-        s_u2 = fma(AL(0) * w * rho * eqs, br[0].d0u, s_u2);
-        s_th = fma(AL(0) * w * rho * eqs, br[0].d0t, s_th);
+        const Bracket b = bracket(u2, th, vs::SHELL_X2[0]);
+        const double wa = vs::T.w[0] * AL(0);
+        s_b = wa * b.a0;
+        s_u2 = wa * b.d0u;
+        s_th = wa * b.d0t;
     }
 #pragma unroll
-    for (int q = 0; q < 22; ++q) {
-        const int i = vs::PAIRS.a[q], j = vs::PAIRS.b[q];
-        const Bracket &b = br[vs::T.shell[i]];
-        const double w = vs::T.w[i];
-        const double c = fma_nz(vs::T.xi[i][2], u[2],
-                                fma_nz(vs::T.xi[i][1], u[1], vs::T.xi[i][0] == 0.0 ? 0.0 : vs::T.xi[i][0] * u[0]));
-        const double feq_i = w * rho * bval(b, c), feq_j = w * rho * bval(b, -c);
-        const double heq_i = eqs * feq_i, heq_j = eqs * feq_j;
-        double hs = 0.0;
+    for (int s = 1; s < 4; ++s) {
+        const Bracket b = bracket(u2, th, vs::SHELL_X2[s]);
+        const double x2 = vs::SHELL_X2[s];
+        double S0 = 0, S1 = 0, S2 = 0, S3 = 0, S4 = 0, g[3] = {0, 0, 0}, w = 0;
+        const double two_a2 = 2.0 * b.a2;
 #pragma unroll
-        for (int m = 0; m < 10; ++m) hs = fma_nz(vs::H3.c[i][m], qb[m], hs);
-        const double ai = AL(i), aj = AL(j);
-        s_ka += (ai - aj) * hs;
-        s_heq += ai * heq_i + aj * heq_j;
-        s_eqT += ai * feq_i + aj * feq_j;
-        const double wre = w * rho * eqs;
-        const double gu = wre * (ai * bder(b, c) - aj * bder(b, -c));      // d/du through c
-        ubar[0] = fma_nz(vs::T.xi[i][0], gu, ubar[0]);
-        ubar[1] = fma_nz(vs::T.xi[i][1], gu, ubar[1]);
-        ubar[2] = fma_nz(vs::T.xi[i][2], gu, ubar[2]);
-        const double sp = ai + aj, sm = ai - aj;
-        const double x2 = vs::SHELL_X2[vs::T.shell[i]];
-        s_u2 += wre * (sp * (b.d0u + c * c * D2U) + sm * c * D1U);
-        s_th += wre * (sp * (b.d0t + c * c * d2t_of(x2)) + sm * c * d1t_of(x2));
+        for (int q = 0; q < 22; ++q) {
+            const int i = vs::PAIRS.a[q], j = vs::PAIRS.b[q];
+            if (vs::T.shell[i] != s) continue;
+            w = vs::T.w[i];
+            const double c = fma_nz(vs::T.xi[i][2], u[2],
+                                    fma_nz(vs::T.xi[i][1], u[1], vs::T.xi[i][0] == 0.0 ? 0.0 : vs::T.xi[i][0] * u[0]));
+            const double ai = AL(i), aj = AL(j);
+            const double sp = ai + aj, sm = ai - aj;
+            const double c2 = c * c, d1 = sm * c, e2 = sp * c2;
+            S0 += sp;
+            S1 += d1;
+            S2 += e2;
+            S3 = fma(d1, c2, S3);
+            S4 = fma(e2, c2, S4);
+            const double gu = fma(sm, fma(c2, 0.5, b.a1), sp * (c * fma(c2, 1.0 / 6.0, two_a2)));
 #pragma unroll
-        for (int m = 0; m < 10; ++m) abar[m] = fma_nz(vs::H3.c[i][m], sm, abar[m]);
+            for (int a = 0; a < 3; ++a) g[a] = fma_nz(vs::T.xi[i][a], gu, g[a]);
+#pragma unroll
+            for (int m = 0; m < 10; ++m) abar[m] = fma_nz(vs::H3.c[i][m], sm, abar[m]);
+            if (q % 2 == 2 - 1) AL.refresh(S4);
+        }
+        s_b = fma(w, fma(b.a0, S0, fma(b.a1, S1, fma(b.a2, S2, fma(S3, 1.0 / 6.0, S4 * (1.0 / 24.0))))), s_b);
+        s_u2 = fma(w, fma(b.d0u, S0, fma(D1U, S1, D2U * S2)), s_u2);
+        s_th = fma(w, fma(b.d0t, S0, fma(d1t_of(x2), S1, d2t_of(x2) * S2)), s_th);
+#pragma unroll
+        for (int a = 0; a < 3; ++a) ubar[a] = fma(w, g[a], ubar[a]);
     }
+    pin(s_b);
+    pin(s_u2);
+    pin(s_th);
 #pragma unroll
-    for (int m = 0; m < 10; ++m) abar[m] *= kap;
+    for (int a = 0; a < 3; ++a) pin(ubar[a]);
+#pragma unroll
+    for (int m = 0; m < 10; ++m) pin(abar[m]);
+    const double P = rho * T;
+    double dfac;
+    const double fac = viscosity_factor(cp, T, dfac);
+    const double mu_v = cp.mu_inf * fac;
+    const double tau = mu_v / (P * cp.dt) + 0.5;
+    const double tau_pr = (tau - 0.5) * cp.inv_pr + 0.5;
+    const double om = 1.0 / tau;
+    const double kap = 1.0 / tau - 1.0 / tau_pr;
+    const double eqs = is_g ? cp.beta * T : 1.0;
+    double s_ka = 0.0;
+#pragma unroll
+    for (int m = 0; m < 10; ++m) {
+        s_ka = fma(abar[m], qb[m], s_ka);
+        abar[m] *= kap;
+    }
+    const double s_eqT = rho * s_b, s_heq = eqs * s_eqT, re = rho * eqs;
+    s_u2 *= re;
+    s_th *= re;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) ubar[a] *= re;
 
     // Qbar -> u: -sum_m abar_m (delta_ad C2_bc + delta_bd C2_ac + delta_cd C2_ab)
     double uq[3] = {0, 0, 0};
@@ -248,45 +327,51 @@ __device__ __forceinline__ double collide_vjp_lane(int64_t N, const CollisionPar
 
     // ---- per-velocity outputs ----
     // Abar : (xi - u)^3 = T3 - T2 + T1 - T0 and Abar : (-xi - u)^3 = -(T3 + T2 + T1 + T0)
-    // with T3 = Abar : xi xi xi, T2 = Bs : xi xi, T1 = Cv . xi, T0 = Abar : u u u,
-    // where Bs and Cv collect Abar with one and two of its indices contracted with u
+    // with T3 = Abar : xi xi xi, T2 = B : xi xi, T1 = C . xi, T0 = Abar : u u u,
+    // where B and C collect Abar with one and two of its indices contracted
+    // with u.  The pair's outputs are (1 - omega) alpha + E +- O with the even
+    // part E = E0 + Ev : xi xi and the odd part O = Ov . xi + T3.
     if (active) {
-        double Bs[6] = {0, 0, 0, 0, 0, 0}, Cu[3] = {0, 0, 0}, T0 = 0.0;
+        double Ev[6] = {0, 0, 0, 0, 0, 0}, Ov[3], T0 = 0.0;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            Ov[a] = is_g ? 0.0 : J_bar[a];
+            Ev[sym2(a, a)] = is_g ? 0.0 : K_bar;
+        }
 #pragma unroll
         for (int m = 0; m < 10; ++m) {
             const int a = vs::IDX3[m][0], b = vs::IDX3[m][1], c = vs::IDX3[m][2];
-            Bs[sym2(b, c)] = fma(abar[m], u[a], Bs[sym2(b, c)]);
-            Bs[sym2(a, c)] = fma(abar[m], u[b], Bs[sym2(a, c)]);
-            Bs[sym2(a, b)] = fma(abar[m], u[c], Bs[sym2(a, b)]);
-            Cu[a] = fma(abar[m], u[b] * u[c], Cu[a]);
-            Cu[b] = fma(abar[m], u[a] * u[c], Cu[b]);
-            Cu[c] = fma(abar[m], u[a] * u[b], Cu[c]);
-            T0 = fma(abar[m], u[a] * u[b] * u[c], T0);
+            Ev[sym2(b, c)] = fma(-abar[m], u[a], Ev[sym2(b, c)]);
+            Ev[sym2(a, c)] = fma(-abar[m], u[b], Ev[sym2(a, c)]);
+            Ev[sym2(a, b)] = fma(-abar[m], u[c], Ev[sym2(a, b)]);
+            const double bc = u[b] * u[c];
+            Ov[a] = fma(abar[m], bc, Ov[a]);
+            Ov[b] = fma(abar[m], u[a] * u[c], Ov[b]);
+            Ov[c] = fma(abar[m], u[a] * u[b], Ov[c]);
+            T0 = fma(abar[m], u[a] * bc, T0);
         }
-        asm volatile("" : "+v"(lp));      // fresh store addresses (the load addresses are not kept live)
+        int64_t so = off;
+        asm volatile("" : "+v"(so));      // fresh store addresses (the load addresses are not kept live)
+        AL.refresh(T0);
+        S *lp = lam + so;
         const double one_m = 1.0 - om;
-        const double base_f = rho_bar, x2g = is_g ? 0.0 : 1.0, kg = is_g ? K_bar : 0.0;
-        {   // rest velocity: xi = 0
-            double r = one_m * AL(0) - T0 + kg;
-            if (!is_g) r += base_f;
-            store_hint<NTH>(&lp[0], static_cast<S>(r));
-        }
+        double E0 = (is_g ? K_bar : rho_bar) - T0;
+        store_hint<NTH>(&lp[0], static_cast<S>(fma(one_m, AL(0), E0)));      // rest velocity: xi = 0
 #pragma unroll
         for (int q = 0; q < 22; ++q) {
             const int i = vs::PAIRS.a[q], j = vs::PAIRS.b[q];
-            const double x = vs::T.xi[i][0], y = vs::T.xi[i][1], z = vs::T.xi[i][2];
-            double T3 = 0.0;
+            const double *x = vs::T.xi[i];
+            double E = E0, O = 0.0;
 #pragma unroll
-            for (int m = 0; m < 10; ++m) T3 = fma_nz(vs::H3.mono[i][m], abar[m], T3);
-            const double T2 = Bs[0] * (x * x) + Bs[1] * (x * y) + Bs[2] * (x * z) + Bs[3] * (y * y) +
-                              Bs[4] * (y * z) + Bs[5] * (z * z);
-            const double T1 = Cu[0] * x + Cu[1] * y + Cu[2] * z;
-            const double jx = is_g ? 0.0 : J_bar[0] * x + J_bar[1] * y + J_bar[2] * z;
-            const double common = kg + x2g * (base_f + K_bar * vs::T.x2[i]);
-            const double ri = one_m * AL(i) + common + jx + (T3 - T2 + T1 - T0);
-            const double rj = one_m * AL(j) + common - jx - (T3 + T2 + T1 + T0);
-            store_hint<NTH>(&lp[static_cast<int64_t>(i) * N], static_cast<S>(ri));
+            for (int k = 0; k < 6; ++k) E = fma_nz(x[IDX2[k][0]] * x[IDX2[k][1]], Ev[k], E);
+#pragma unroll
+            for (int a = 0; a < 3; ++a) O = fma_nz(x[a], Ov[a], O);
+#pragma unroll
+            for (int m = 0; m < 10; ++m) O = fma_nz(vs::H3.mono[i][m], abar[m], O);
+            store_hint<NTH>(&lp[static_cast<int64_t>(i) * N], static_cast<S>(fma(one_m, AL(i), E + O)));
+            const double rj = fma(one_m, AL(j), E - O);
             store_hint<NTH>(&lp[static_cast<int64_t>(j) * N], static_cast<S>(rj));
+            if (q % 2 == 2 - 1) AL.refresh(E0);
         }
     }
 
@@ -294,36 +379,43 @@ __device__ __forceinline__ double collide_vjp_lane(int64_t N, const CollisionPar
     return active && !is_g ? mu_bar * fac : 0.0;
 }
 
-// Grid-stride over lane pairs; the whole block runs the same number of
-// iterations, so every shuffle partner is live.  mu and lam may be the same
-// buffer: each lane reads its 45 values before writing them.
-// NTH: non-temporal loads and stores (states larger than the Infinity Cache)
-template <typename S, bool NTH>
-__global__ void __launch_bounds__(256) k_collide_vjp(int64_t N, CollisionParams cp, const S *__restrict__ X,
-                                                     const S *mu, S *lam, double *__restrict__ dmu_part)
+// sum of the block's 256 values in thread 0's red[0], in a fixed order
+__device__ __forceinline__ double block_sum256(double v, double *red)
 {
-    __shared__ double red[256];
-    double dmu_acc = 0.0;
-    const int64_t stride = static_cast<int64_t>(gridDim.x) * blockDim.x;
-    for (int64_t t0 = blockIdx.x * static_cast<int64_t>(blockDim.x); t0 < 2 * N; t0 += stride) {
-        const int64_t t = t0 + threadIdx.x;
-        const int64_t n = t >> 1;
-        const int pop = static_cast<int>(t & 1);
-        const bool active = n < N;
-        const int64_t off = static_cast<int64_t>(pop) * vs::Q * N + (active ? n : 0);
-        double al[vs::Q];
-#pragma unroll
-        for (int i = 0; i < vs::Q; ++i) al[i] = static_cast<double>(load_hint<NTH>(&mu[off + static_cast<int64_t>(i) * N]));
-        dmu_acc += collide_vjp_lane<S, NTH, 1>(N, cp, X, off, pop != 0, active, [&](int i) { return al[i]; },
-                                               lam + off);
-    }
-    red[threadIdx.x] = dmu_acc;
+    red[threadIdx.x] = v;
     __syncthreads();
-    for (int s = blockDim.x / 2; s > 0; s >>= 1) {
+    for (int s = 128; s > 0; s >>= 1) {
         if (threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
         __syncthreads();
     }
-    if (threadIdx.x == 0) dmu_part[blockIdx.x] = red[0];
+    return red[0];
+}
+
+// One lane pair per node, alpha in registers; no grid-stride loop, out of
+// which the compiler would hoist the sweep's FP64 constants (230 SGPR
+// spills).  mu and lam may be the same buffer: each lane reads its 45 values
+// before writing them.  255 VGPRs, 2 waves per SIMD; in FP64 6.78 ms at 256^3
+// nodes (36.2 GB, 5.3 TB/s: HBM-bound), 114 us at 64^3 (175 us with 332
+// registers and one wave per SIMD).
+// NTH: non-temporal loads and stores (states larger than the Infinity Cache)
+template <typename S, bool NTH>
+__global__ void __launch_bounds__(256, 2) k_collide_vjp(int64_t N, CollisionParams cp, const S *__restrict__ X,
+                                                     const S *mu, S *lam, double *__restrict__ dmu_part)
+{
+    __shared__ double red[256];
+    const int64_t t = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x;
+    const int64_t n = t >> 1;
+    const int pop = static_cast<int>(t & 1);
+    const bool active = n < N;
+    const int64_t off = static_cast<int64_t>(pop) * vs::Q * N + (active ? n : 0);
+    AlphaReg al;
+#pragma unroll
+    for (int i = 0; i < vs::Q; ++i) al.v[i] = static_cast<double>(load_hint<NTH>(&mu[off + static_cast<int64_t>(i) * N]));
+    const double dmu = collide_vjp_lane<S, NTH, 1>(N, cp, X, off, pop != 0, active, al, lam);
+    if (dmu_part) {
+        const double s = block_sum256(dmu, red);
+        if (threadIdx.x == 0) dmu_part[blockIdx.x] = s;
+    }
 }
 
 // DMA copy of 16 bytes per lane from g into LDS at l + 16 * lane (l is
@@ -335,51 +427,51 @@ __device__ __forceinline__ void dma16_adj(const void *g, void *l)
     __builtin_amdgcn_global_load_lds(g, l, 16, 0, AUX);
 }
 
-// The collision VJP in FP32 storage with the adjoint inputs alpha staged in
-// LDS: per iteration a block takes 128 consecutive nodes, copies their 90
-// rows of mu (row r = pop * 45 + i, 512 contiguous bytes) into LDS by 16-byte
-// DMA copies, and each lane reads its alpha_i from there (lane l of wave w:
-// node w * 32 + (l & 31), population l >> 5, partner l ^ 32).  256 VGPRs
-// and 38 spilled at two waves per SIMD, against 330 registers and one wave
-// for k_collide_vjp.  N % 4 == 0 and mu 16-byte aligned; mu and lam may be
-// the same buffer (every copy of an iteration lands before its writes, and
-// the next iteration's copies wait for all its reads).
-template <bool NTH>
-__global__ void __launch_bounds__(256, 2) k_collide_vjp_lds(int64_t N, CollisionParams cp,
-                                                            const float *__restrict__ X, const float *mu, float *lam,
+// The collision VJP with the adjoint inputs alpha staged in LDS: a block takes
+// NB = 512 / sizeof(S) consecutive nodes (blocks in XCD order), copies their
+// 90 rows of mu (row r = pop * 45 + i, 512 contiguous bytes) into LDS by
+// 16-byte DMA copies, and each lane reads its alpha_i from there (lane l of
+// wave w: node w * 32 + (l & 31), population l >> 5, partner l ^ 32).
+// N % (16 / sizeof(S)) == 0 and mu 16-byte aligned; mu and lam may be the same
+// buffer (every copy has landed before the block's first write).
+// Bound by HBM: it reads X and alpha and writes lambda once, 3.53 ms at 256^3
+// nodes in FP32 (18.1 GB, 5.1 TB/s; 166 VGPRs, 3 waves per SIMD), 451 us at
+// 128^3 and 63 us at 64^3.  While the sweep's sums sank past the branch on the
+// viscosity law it needed 256 VGPRs with spills (2 waves) and took 5.73 ms.
+template <typename S, bool NTH>
+__global__ void __launch_bounds__(1024 / sizeof(S), sizeof(S) == 4 ? 3 : 2) k_collide_vjp_lds(int64_t N, CollisionParams cp,
+                                                            const S *__restrict__ X, const S *mu, S *lam,
                                                             double *__restrict__ dmu_part)
 {
-    constexpr int NB = 128, ROWS = 2 * vs::Q;
-    __shared__ float tile[ROWS][NB];
-    __shared__ double red[256];
-    double dmu_acc = 0.0;
+    constexpr int NB = 512 / sizeof(S), ROWS = 2 * vs::Q, NW = NB / 32, VL = 16 / sizeof(S);
+    __shared__ S tile[ROWS][NB];
     const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int pop = lane >> 5;
     const int c = w * 32 + (lane & 31);
-    for (int64_t nb = static_cast<int64_t>(blockIdx.x) * NB; nb < N; nb += static_cast<int64_t>(gridDim.x) * NB) {
-        __syncthreads();                         // the previous nodes' reads of the tile are done
-        const int64_t col = nb + 4 * (lane & 31);
-        if (col < N) {
-            const float *src = mu + static_cast<int64_t>(lane >> 5) * N + col;
-            for (int m = w; m < ROWS / 2; m += 4)
-                dma16_adj<NTH ? 2 : 0>(src + static_cast<int64_t>(2 * m) * N, &tile[2 * m][0]);
-        }
-        __builtin_amdgcn_s_waitcnt(0);           // this wave's copies have landed
-        __syncthreads();                         // and every other wave's
-        const int64_t n = nb + c;
-        const bool active = n < N;
-        const int64_t off = static_cast<int64_t>(pop) * vs::Q * N + (active ? n : 0);
-        const float *sl = &tile[pop * vs::Q][c];
-        dmu_acc += collide_vjp_lane<float, NTH, 32>(N, cp, X, off, pop != 0, active,
-                                                    [&](int i) { return static_cast<double>(sl[i * NB]); }, lam + off);
+    const int64_t nb = static_cast<int64_t>(xcd_linear(blockIdx.x, gridDim.x)) * NB;
+    const int64_t col = nb + VL * (lane & 31);
+    if (col < N) {
+        const S *src = mu + static_cast<int64_t>(lane >> 5) * N + col;
+        for (int m = w; m < ROWS / 2; m += NW) dma16_adj<NTH ? 2 : 0>(src + static_cast<int64_t>(2 * m) * N, &tile[2 * m][0]);
     }
-    red[threadIdx.x] = dmu_acc;
-    __syncthreads();
-    for (int s = blockDim.x / 2; s > 0; s >>= 1) {
-        if (threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
+    __builtin_amdgcn_s_waitcnt(0);               // this wave's copies have landed
+    __syncthreads();                             // and every other wave's
+    const int64_t n = nb + c;
+    const bool active = n < N;
+    const int64_t off = static_cast<int64_t>(pop) * vs::Q * N + (active ? n : 0);
+    const double dmu = collide_vjp_lane<S, NTH, 32>(N, cp, X, off, pop != 0, active,
+                                                    AlphaLds<S, NB>{&tile[0][0], pop * vs::Q * NB + c}, lam);
+    if (dmu_part) {
+        __syncthreads();                         // the tile's reads are done: its memory takes the sums
+        double *red = reinterpret_cast<double *>(&tile[0][0]);
+        red[threadIdx.x] = dmu;
         __syncthreads();
+        for (int s = 2 * NB / 2; s > 0; s >>= 1) {
+            if (static_cast<int>(threadIdx.x) < s) red[threadIdx.x] += red[threadIdx.x + s];
+            __syncthreads();
+        }
+        if (threadIdx.x == 0) dmu_part[blockIdx.x] = red[0];
     }
-    if (threadIdx.x == 0) dmu_part[blockIdx.x] = red[0];
 }
 
 // Fixed-order sum of n block partials by one block of 256 threads; the
@@ -839,35 +931,37 @@ hipError_t Launch<S>::diagnostics(const Geometry &g, const CollisionParams &cp, 
 
 template <typename S>
 hipError_t Launch<S>::collide_vjp(const Geometry &g, const CollisionParams &cp, const S *state_n, S *lam,
-                                  double *dmu_partials, int nblocks, double *dmu, hipStream_t st)
+                                  double *dmu_partials, double *dmu, hipStream_t st)
 {
     // lam <- J_C(X_n)^T lam in place
     const bool nt = use_nontemporal(90 * g.nodes * static_cast<int64_t>(sizeof(S)));
     int blocks = 0;
     bool staged = false;
-    if constexpr (sizeof(S) == 4) {
-        // FP32: alpha staged in LDS (measured per adjoint step: 3-5 % faster
-        // at 128^3 and 256^3 nodes, 8 % at 64^3; in FP64 the staged form
-        // spills 81 registers and is 17-20 % slower)
-        if (g.nodes % 4 == 0 && reinterpret_cast<uintptr_t>(lam) % 16 == 0) {
+    // alpha staged in LDS (see k_collide_vjp_lds): in FP32 always; in FP64 it
+    // leaves 1.5 waves per SIMD, which is faster while the grid has at most two
+    // blocks per CU (10.3 against 12.4 us at 512 nodes, 11.4 against 14.2 at
+    // 13,824) and 1-6 % slower from 110,592 nodes on
+    if (sizeof(S) == 4 || g.nodes <= 32768) {
+        constexpr int NB = 512 / sizeof(S);
+        if (g.nodes % (16 / sizeof(S)) == 0 && reinterpret_cast<uintptr_t>(lam) % 16 == 0) {
             staged = true;
-            blocks = static_cast<int>(std::min<int64_t>((g.nodes + 127) / 128, nblocks));
+            blocks = static_cast<int>((g.nodes + NB - 1) / NB);
             if (nt)
-                hipLaunchKernelGGL((k_collide_vjp_lds<true>), dim3(static_cast<unsigned>(blocks)), dim3(256), 0, st,
-                                   g.nodes, cp, state_n, lam, lam, dmu_partials);
+                hipLaunchKernelGGL((k_collide_vjp_lds<S, true>), dim3(static_cast<unsigned>(blocks)), dim3(2 * NB), 0, st,
+                                   g.nodes, cp, state_n, lam, lam, dmu ? dmu_partials : nullptr);
             else
-                hipLaunchKernelGGL((k_collide_vjp_lds<false>), dim3(static_cast<unsigned>(blocks)), dim3(256), 0, st,
-                                   g.nodes, cp, state_n, lam, lam, dmu_partials);
+                hipLaunchKernelGGL((k_collide_vjp_lds<S, false>), dim3(static_cast<unsigned>(blocks)), dim3(2 * NB), 0, st,
+                                   g.nodes, cp, state_n, lam, lam, dmu ? dmu_partials : nullptr);
         }
     }
     if (!staged) {
-        blocks = static_cast<int>(std::min<int64_t>((2 * g.nodes + 255) / 256, nblocks));
+        blocks = static_cast<int>((2 * g.nodes + 255) / 256);
         if (nt)
             hipLaunchKernelGGL((k_collide_vjp<S, true>), dim3(static_cast<unsigned>(blocks)), dim3(256), 0, st,
-                               g.nodes, cp, state_n, lam, lam, dmu_partials);
+                               g.nodes, cp, state_n, lam, lam, dmu ? dmu_partials : nullptr);
         else
             hipLaunchKernelGGL((k_collide_vjp<S, false>), dim3(static_cast<unsigned>(blocks)), dim3(256), 0, st,
-                               g.nodes, cp, state_n, lam, lam, dmu_partials);
+                               g.nodes, cp, state_n, lam, lam, dmu ? dmu_partials : nullptr);
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;

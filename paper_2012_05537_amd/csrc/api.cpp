@@ -17,7 +17,6 @@ using namespace sllbm;
 namespace {
 
 constexpr int RED_BLOCKS = 1024;   // blocks of the deterministic reductions
-constexpr int ADJ_BLOCKS = 4096;   // largest grid of the collision VJP (grid-stride beyond)
 
 std::string g_create_error;
 
@@ -47,7 +46,7 @@ struct sllbm_ctx {
     double *d_scr_u = nullptr;     // [3N]
     double *d_scr_div = nullptr;   // [cells * (p+1)^3]
     double *d_scr_T = nullptr;     // [N]   diagnostics scratch
-    double *d_adj_part = nullptr;  // [ADJ_BLOCKS] dmu_inf partials of the collision VJP
+    double *d_adj_part = nullptr;  // [ceil(N/64)] dmu_inf partials of the collision VJP's blocks
     // kernel timing: event pairs per launch kind (0 collision, 1 streaming)
     bool timing = false;
     std::vector<hipEvent_t> ev[2];
@@ -473,7 +472,7 @@ int sllbm_create(const sllbm_config *cfg, sllbm_ctx **out)
         (e = dalloc(&c->d_scr_u, 3 * nodes * sizeof(double))) != hipSuccess ||
         (e = dalloc(&c->d_scr_div, cpts * sizeof(double))) != hipSuccess ||
         (e = dalloc(&c->d_scr_T, nodes * sizeof(double))) != hipSuccess ||
-        (e = dalloc(&c->d_adj_part, ADJ_BLOCKS * sizeof(double))) != hipSuccess)
+        (e = dalloc(&c->d_adj_part, (nodes + 63) / 64 * sizeof(double))) != hipSuccess)
         return bail(fail(c, SLLBM_ENOMEM, std::string("allocation failed: ") + hipGetErrorString(e)));
     if ((e = hipMemcpy(c->d_nodew, nodew.data(), nodew.size() * sizeof(double), hipMemcpyHostToDevice)) !=
             hipSuccess ||
@@ -1060,9 +1059,9 @@ int sllbm_adjoint_step(sllbm_ctx *ctx, const void *state_n, const void *lam_next
     if (e != hipSuccess) return hip_fail(ctx, e, "adjoint_step (transposed streaming)");
     e = is_fp64(ctx)
         ? Launch<double>::collide_vjp(ctx->geo, ctx->cp, static_cast<const double *>(state_n),
-                                      static_cast<double *>(lam_out), ctx->d_adj_part, ADJ_BLOCKS, dmu, ctx->stream)
+                                      static_cast<double *>(lam_out), ctx->d_adj_part, dmu, ctx->stream)
         : Launch<float>::collide_vjp(ctx->geo, ctx->cp, static_cast<const float *>(state_n),
-                                     static_cast<float *>(lam_out), ctx->d_adj_part, ADJ_BLOCKS, dmu, ctx->stream);
+                                     static_cast<float *>(lam_out), ctx->d_adj_part, dmu, ctx->stream);
     return check_launch(ctx, e, "adjoint_step (collision VJP)");
 }
 

@@ -61,32 +61,62 @@ struct RawMoments {
 
 constexpr int IDX2[6][2] = {{0, 0}, {0, 1}, {0, 2}, {1, 1}, {1, 2}, {2, 2}};
 
-template <class L, class Get>
-__device__ __forceinline__ RawMoments<L> raw_moments_of(Get &&h)
+template <class L>
+__device__ __forceinline__ void clear_moments(RawMoments<L> &r)
 {
-    RawMoments<L> r;
-    r.m0 = static_cast<double>(h(0));
+    r.m0 = 0.0;
 #pragma unroll
     for (int k = 0; k < 3; ++k) r.m1[k] = 0.0;
 #pragma unroll
     for (int k = 0; k < 6; ++k) r.m2[k] = 0.0;
 #pragma unroll
     for (int k = 0; k < L::NM3; ++k) r.m3[k] = 0.0;
+}
+
+// adds pair q, whose values are hi (velocity xi) and hj (velocity -xi)
+template <class L>
+__device__ __forceinline__ void add_pair_moments(RawMoments<L> &r, int q, double hi, double hj)
+{
+    const int i = L::PAIRS.a[q];
+    const double s = hi + hj, d = hi - hj;
+    const double *x = L::T.xi[i];
+    r.m0 += s;
 #pragma unroll
-    for (int q = 0; q < L::NPAIR; ++q) {
-        const int i = L::PAIRS.a[q], j = L::PAIRS.b[q];
-        const double hi = static_cast<double>(h(i)), hj = static_cast<double>(h(j));
-        const double s = hi + hj, d = hi - hj;
-        const double *x = L::T.xi[i];
-        r.m0 += s;
+    for (int a = 0; a < L::D; ++a) r.m1[a] = fma_nz(x[a], d, r.m1[a]);
 #pragma unroll
-        for (int a = 0; a < L::D; ++a) r.m1[a] = fma_nz(x[a], d, r.m1[a]);
+    for (int k = 0; k < 6; ++k)
+        if (IDX2[k][1] < L::D) r.m2[k] = fma_nz(x[IDX2[k][0]] * x[IDX2[k][1]], s, r.m2[k]);
 #pragma unroll
-        for (int k = 0; k < 6; ++k)
-            if (IDX2[k][1] < L::D) r.m2[k] = fma_nz(x[IDX2[k][0]] * x[IDX2[k][1]], s, r.m2[k]);
+    for (int m = 0; m < L::NM3; ++m) r.m3[m] = fma_nz(L::H3.mono[i][m], d, r.m3[m]);
+}
+
+// x is computed here.  Without it the compiler moves sums that are used only
+// after the branch on the viscosity law past that branch, with all their
+// inputs live until then.
+__device__ __forceinline__ void pin(double &x) { asm volatile("" : "+v"(x)); }
+
+template <class L>
+__device__ __forceinline__ void pin_moments(RawMoments<L> &r)
+{
+    pin(r.m0);
 #pragma unroll
-        for (int m = 0; m < L::NM3; ++m) r.m3[m] = fma_nz(L::H3.mono[i][m], d, r.m3[m]);
-    }
+    for (int k = 0; k < L::D; ++k) pin(r.m1[k]);
+#pragma unroll
+    for (int k = 0; k < 6; ++k)
+        if (IDX2[k][1] < L::D) pin(r.m2[k]);
+#pragma unroll
+    for (int k = 0; k < L::NM3; ++k) pin(r.m3[k]);
+}
+
+template <class L, class Get>
+__device__ __forceinline__ RawMoments<L> raw_moments_of(Get &&h)
+{
+    RawMoments<L> r;
+    clear_moments<L>(r);
+    r.m0 = static_cast<double>(h(0));
+#pragma unroll
+    for (int q = 0; q < L::NPAIR; ++q)
+        add_pair_moments<L>(r, q, static_cast<double>(h(L::PAIRS.a[q])), static_cast<double>(h(L::PAIRS.b[q])));
     return r;
 }
 
@@ -133,6 +163,81 @@ __host__ __device__ __forceinline__ EqShell eq_shell(double u2, double th, doubl
     return e;
 }
 
+// What the relaxation of one population at one node needs besides its values.
+template <class L>
+struct RelaxCoef {
+    double om, kap;          // 1/tau, 1/tau - 1/tau_Pr
+    double eqs;              // h^eq = eqs f^eq: 1 (f), (2 C_v - D) T (g)
+    double rho, u2, th;      // density, |u|^2, T - 1
+    double u[3];
+    double qb[L::NM3];       // Qbar of the population
+};
+
+// From the raw moments rm of the population, and rho, momentum J and K = 2 rho E
+// of the node.
+template <class L>
+__device__ __forceinline__ RelaxCoef<L> relax_coef(const RawMoments<L> &rm, double rho, const double (&J)[3], double K,
+                                                   bool is_g, const CollisionParams &cp)
+{
+    constexpr bool D3 = L::D == 3;
+    RelaxCoef<L> c;
+    const double ir = 1.0 / rho;
+    c.rho = rho;
+    c.u[0] = J[0] * ir;
+    c.u[1] = J[1] * ir;
+    c.u[2] = D3 ? J[2] * ir : 0.0;
+    c.u2 = D3 ? c.u[0] * c.u[0] + c.u[1] * c.u[1] + c.u[2] * c.u[2] : c.u[0] * c.u[0] + c.u[1] * c.u[1];
+    const double T = (K * ir - c.u2) / (2.0 * cp.Cv);
+    centred_third<L>(rm, c.u, c.qb);
+    const double P = rho * T;
+    const double tau = viscosity_of(cp, T) / (P * cp.dt) + 0.5;
+    const double tau_pr = (tau - 0.5) * cp.inv_pr + 0.5;
+    c.om = 1.0 / tau;
+    c.kap = 1.0 / tau - 1.0 / tau_pr;
+    c.th = T - 1.0;
+    c.eqs = is_g ? cp.beta * T : 1.0;
+    return c;
+}
+
+// relaxed value of the rest velocity
+template <class L>
+__device__ __forceinline__ double relax_rest(const RelaxCoef<L> &c, double v)
+{
+    const EqShell e = eq_shell<L::D>(c.u2, c.th, L::SHELL_X2[0]);
+    const double heq = c.eqs * L::T.w[0] * (e.a0 * c.rho);
+    return fma(c.om, heq - v, v);
+}
+
+// relaxed values of pair q (vi, vj in, replaced); A: rho times the shell's
+// coefficients, rho6 = rho / 6, rho24 = rho / 24
+template <class L>
+__device__ __forceinline__ void relax_pair(const RelaxCoef<L> &k, const EqShell &A, double rho6, double rho24, int q,
+                                           double &vi, double &vj)
+{
+    const int i = L::PAIRS.a[q];
+    double c = fma_nz(L::T.xi[i][1], k.u[1], L::T.xi[i][0] == 0.0 ? 0.0 : L::T.xi[i][0] * k.u[0]);
+    if constexpr (L::D == 3) c = fma_nz(L::T.xi[i][2], k.u[2], c);
+    const double c2 = c * c;
+    const double even = fma(c2, fma(c2, rho24, A.a2), A.a0);
+    const double odd = c * fma(c2, rho6, A.a1);
+    const double we = k.eqs * L::T.w[i];
+    double hs = 0.0;
+#pragma unroll
+    for (int m = 0; m < L::NM3; ++m) hs = fma_nz(L::H3.c[i][m], k.qb[m], hs);
+    vi = fma(k.kap, hs, fma(k.om, fma(we, even, we * odd) - vi, vi));
+    vj = fma(-k.kap, hs, fma(k.om, fma(we, even, -we * odd) - vj, vj));
+}
+
+template <class L>
+__device__ __forceinline__ EqShell rho_shell(const RelaxCoef<L> &k, int s)
+{
+    EqShell e = eq_shell<L::D>(k.u2, k.th, L::SHELL_X2[s]);
+    e.a0 *= k.rho;
+    e.a1 *= k.rho;
+    e.a2 *= k.rho;
+    return e;
+}
+
 // Collision of one node whose two populations are held by a lane pair,
 // lanes l and l ^ XM: the lane with is_g = false holds f, its partner g.
 // Each lane forms the raw moments of its own population; the pair exchanges
@@ -144,13 +249,14 @@ __host__ __device__ __forceinline__ EqShell eq_shell(double u2, double th, doubl
 // fence() in between: a source in memory is then read again rather than held
 // in registers through the collision.
 // sink(i, value) receives every post-collision value as soon as it is formed.
-template <class L, typename S, int XM = 1, class Get, class Fence, class Sink>
+// PIN: the moments are finished before the branch on the viscosity law.
+template <class L, typename S, int XM = 1, bool PIN = false, class Get, class Fence, class Sink>
 __device__ __forceinline__ void collide_core(Get &&get, Fence &&fence, bool is_g, const CollisionParams &cp,
                                              Sink &&sink)
 {
-    using R = double;   // arithmetic type of the per-velocity terms (storage S is read and written once)
     constexpr bool D3 = L::D == 3;
-    const RawMoments<L> rm = raw_moments_of<L>(get);
+    RawMoments<L> rm = raw_moments_of<L>(get);
+    if constexpr (PIN) pin_moments<L>(rm);
     fence();
     const double ktr = D3 ? rm.m2[0] + rm.m2[3] + rm.m2[5] : rm.m2[0] + rm.m2[3];
     const double p_m0 = __shfl_xor(rm.m0, XM);
@@ -159,76 +265,40 @@ __device__ __forceinline__ void collide_core(Get &&get, Fence &&fence, bool is_g
     const double p_j2 = D3 ? __shfl_xor(rm.m1[2], XM) : 0.0;
     const double p_tr = __shfl_xor(ktr, XM);
     const double rho = is_g ? p_m0 : rm.m0;
-    const double ir = 1.0 / rho;
-    const double u[3] = {(is_g ? p_j0 : rm.m1[0]) * ir, (is_g ? p_j1 : rm.m1[1]) * ir,
-                         D3 ? (is_g ? p_j2 : rm.m1[2]) * ir : 0.0};
+    const double J[3] = {is_g ? p_j0 : rm.m1[0], is_g ? p_j1 : rm.m1[1], is_g ? p_j2 : rm.m1[2]};
     const double K = is_g ? p_tr + rm.m0 : ktr + p_m0;          // 2 rho E
-    const double u2 = D3 ? u[0] * u[0] + u[1] * u[1] + u[2] * u[2] : u[0] * u[0] + u[1] * u[1];
-    const double T = (K * ir - u2) / (2.0 * cp.Cv);
-    double qb[L::NM3];
-    centred_third<L>(rm, u, qb);
-
-    const double P = rho * T;
-    const double tau = viscosity_of(cp, T) / (P * cp.dt) + 0.5;
-    const double tau_pr = (tau - 0.5) * cp.inv_pr + 0.5;
-    const R om = static_cast<R>(1.0 / tau);
-    const R kap = static_cast<R>(1.0 / tau - 1.0 / tau_pr);
-    const double th = T - 1.0;
-    const R eqs = static_cast<R>(is_g ? cp.beta * T : 1.0);
-
-    R A0[L::NSHELL], A1[L::NSHELL], A2[L::NSHELL];
+    const RelaxCoef<L> k = relax_coef<L>(rm, rho, J, K, is_g, cp);
+    EqShell A[L::NSHELL];
 #pragma unroll
-    for (int s = 0; s < L::NSHELL; ++s) {
-        const EqShell e = eq_shell<L::D>(u2, th, L::SHELL_X2[s]);
-        A0[s] = static_cast<R>(e.a0 * rho);
-        A1[s] = static_cast<R>(e.a1 * rho);
-        A2[s] = static_cast<R>(e.a2 * rho);
-    }
-    const R rho6 = static_cast<R>(rho / 6.0), rho24 = static_cast<R>(rho / 24.0);
-    R qr[L::NM3];
-#pragma unroll
-    for (int m = 0; m < L::NM3; ++m) qr[m] = static_cast<R>(qb[m]);
-    const R ux = static_cast<R>(u[0]), uy = static_cast<R>(u[1]), uz = static_cast<R>(u[2]);
-    {
-        const R heq = eqs * static_cast<R>(L::T.w[0]) * A0[0];
-        const R vi = get(0);
-        sink(0, static_cast<S>(fma(om, heq - vi, vi)));
-    }
+    for (int s = 1; s < L::NSHELL; ++s) A[s] = rho_shell<L>(k, s);
+    const double rho6 = rho / 6.0, rho24 = rho / 24.0;
+    sink(0, static_cast<S>(relax_rest<L>(k, static_cast<double>(get(0)))));
 #pragma unroll
     for (int q = 0; q < L::NPAIR; ++q) {
         const int i = L::PAIRS.a[q], j = L::PAIRS.b[q];
-        const int s = L::T.shell[i];
-        R c = fma_nz(L::T.xi[i][1], uy, L::T.xi[i][0] == 0.0 ? R(0) : static_cast<R>(L::T.xi[i][0]) * ux);
-        if constexpr (D3) c = fma_nz(L::T.xi[i][2], uz, c);
-        const R c2 = c * c;
-        const R even = fma(c2, fma(c2, rho24, A2[s]), A0[s]);
-        const R odd = c * fma(c2, rho6, A1[s]);
-        const R we = eqs * static_cast<R>(L::T.w[i]);
-        R hs = 0;
-#pragma unroll
-        for (int m = 0; m < L::NM3; ++m) hs = fma_nz(L::H3.c[i][m], qr[m], hs);
-        const R vi = get(i), vj = get(j);
-        sink(i, static_cast<S>(fma(kap, hs, fma(om, fma(we, even, we * odd) - vi, vi))));
-        sink(j, static_cast<S>(fma(-kap, hs, fma(om, fma(we, even, -we * odd) - vj, vj))));
+        double vi = get(i), vj = get(j);
+        relax_pair<L>(k, A[L::T.shell[i]], rho6, rho24, q, vi, vj);
+        sink(i, static_cast<S>(vi));
+        sink(j, static_cast<S>(vj));
     }
 }
 
 // The same on values held in registers: sink(i, value) receives every
 // post-collision value as soon as it is formed, and v holds them all on
 // return as well.
-template <class L, typename S, class Sink>
+template <class L, typename S, bool PIN = false, class Sink>
 __device__ __forceinline__ void collide_half_s(S (&v)[L::Q], bool is_g, const CollisionParams &cp, Sink &&sink)
 {
-    collide_core<L, S>([&](int i) { return v[i]; }, [] {}, is_g, cp, [&](int i, S x) {
+    collide_core<L, S, 1, PIN>([&](int i) { return v[i]; }, [] {}, is_g, cp, [&](int i, S x) {
         v[i] = x;
         sink(i, x);
     });
 }
 
-template <class L, typename S>
+template <class L, typename S, bool PIN = false>
 __device__ __forceinline__ void collide_half(S (&v)[L::Q], bool is_g, const CollisionParams &cp)
 {
-    collide_half_s<L, S>(v, is_g, cp, [](int, S) {});
+    collide_half_s<L, S, PIN>(v, is_g, cp, [](int, S) {});
 }
 
 }  // namespace sllbm

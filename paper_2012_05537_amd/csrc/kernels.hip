@@ -17,8 +17,12 @@ namespace sllbm {
 // lanes per node (f on the even lane, g on the odd one), the values in
 // registers: D3Q45 in FP64, D2Q19 in FP32, and the cases that k_collide_lds
 // below does not take (N not a multiple of 16 / sizeof(S), an input not
-// 16-byte aligned).  in and out may be the same buffer (each lane reads its
-// values first).  NTH: non-temporal loads and stores (states larger than
+// 16-byte aligned).  On grids larger than the Infinity Cache the moment sums
+// are pinned before the viscosity branch (pin() in collision.h): D3Q45 then
+// needs 168 VGPRs, 3 waves per SIMD, instead of 224 and 2; in FP64 4.61 -> 4.56
+// ms at 256^3 nodes (5.3 TB/s, HBM-bound) and 556 -> 532 us at 128^3.  On
+// smaller grids the third wave gains nothing (64^3 nodes: 68 us unpinned, 70 us).
+// in and out may be the same buffer (each lane reads its values first).  NTH: non-temporal loads and stores (states larger than
 // the Infinity Cache).
 template <typename S, class L, bool NTH>
 __global__ void __launch_bounds__(256) k_collide(int64_t N, CollisionParams cp, const S *in, S *out)
@@ -38,14 +42,13 @@ __global__ void __launch_bounds__(256) k_collide(int64_t N, CollisionParams cp, 
     S *d = out + o;
     if constexpr (sizeof(S) == 4) {
         // FP32 storage: store every value as the relaxation forms it; the
-        // D3Q45 collision is latency-bound here (two waves per SIMD), and
-        // stores spread over it measured 7 % faster at 256^3 nodes (no gain
-        // in FP64)
+        // D3Q45 collision is latency-bound here, and stores spread over it
+        // measured 7 % faster at 256^3 nodes (no gain in FP64)
         asm volatile("" : "+v"(d));
-        collide_half_s<L, S>(v, pop != 0, cp,
-                             [d, N](int i, S x) { store_hint<NTH>(&d[static_cast<int64_t>(i) * N], x); });
+        collide_half_s<L, S, NTH>(v, pop != 0, cp,
+                                  [d, N](int i, S x) { store_hint<NTH>(&d[static_cast<int64_t>(i) * N], x); });
     } else {
-        collide_half<L, S>(v, pop != 0, cp);
+        collide_half<L, S, NTH>(v, pop != 0, cp);
         asm volatile("" : "+v"(d));
 #pragma unroll
         for (int i = 0; i < NQ; ++i) store_hint<NTH>(&d[static_cast<int64_t>(i) * N], v[i]);
@@ -73,8 +76,8 @@ __device__ __forceinline__ void dma16(const T *g, T *l)
 // value is then read from LDS for the moments and again for the relaxation.
 // Lane l of wave w holds node w * 32 + (l & 31) of the block and population
 // l >> 5 (partner lane l ^ 32).  For D3Q45 in FP32: 136 VGPRs and 45 KB of
-// LDS per block (3 waves per SIMD), where the register form needs 224 VGPRs
-// (2 waves) and reads 128-byte segments per plane and half-wave.
+// LDS per block (3 waves per SIMD), where the register form holds the 45
+// values and reads 128-byte segments per plane and half-wave.
 // in may equal out: every copy has landed before the barrier, and a block
 // writes only its own nodes.  NTH: non-temporal copies and stores.
 template <typename S, class L, bool NTH>

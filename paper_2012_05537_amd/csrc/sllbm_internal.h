@@ -208,7 +208,7 @@ struct Launch {
                                   int nblocks, double *out3, hipStream_t st);
     // lam <- J_C(X_n)^T lam in place; dL/dmu_inf added to *dmu if not NULL
     static hipError_t collide_vjp(const Geometry &g, const CollisionParams &cp, const S *state_n, S *lam,
-                                  double *dmu_partials, int nblocks, double *dmu, hipStream_t st);
+                                  double *dmu_partials, double *dmu, hipStream_t st);
     static hipError_t moments_vjp(const Geometry &g, const CollisionParams &cp, const S *state, const double *drho,
                                   const double *du, const double *dT, S *lam, hipStream_t st);
     static hipError_t init_equilibrium_vjp(const Geometry &g, const CollisionParams &cp, const double *rho,

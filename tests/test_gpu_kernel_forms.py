@@ -1,0 +1,70 @@
+"""The forms a kernel has for different sizes, alignments and grids, at the
+sizes where they can go wrong (remainders of tiles and blocks, smallest grids,
+unaligned buffers), against each other or the FP64 oracle."""
+
+import numpy as np
+import pytest
+import torch
+
+from gpu_common import make_pair, require_gpu, to_dev, to_np
+from paper_2012_05537_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(autouse=True)
+def _gpu():
+    require_gpu()
+
+
+@pytest.fixture(scope="module")
+def oracle():
+    from oracle import oracle as O
+    return O
+
+
+def _noisy(oracle, cfg, seed, Ma=0.7):
+    f, g = oracle.init_equilibrium(cfg, *inputs.tgv_fields(*oracle.node_coords(cfg), Ma, 1.4))
+    rng = np.random.default_rng(seed)
+    return f * (1 + 0.03 * rng.normal(size=f.shape)), g * (1 + 0.03 * rng.normal(size=g.shape))
+
+
+# nodes: 1, 27 (odd: register form), 64 (one FP64 block), 130 and 132 (ragged
+# blocks; 130 is no multiple of 4: register form in FP32), 2000
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("n_el,p", [((1, 1, 1), 1), ((1, 1, 1), 3), ((2, 2, 2), 2), ((13, 5, 2), 1), ((11, 4, 3), 1),
+                                    ((5, 2, 2), 5)])
+def test_collision_vjp_forms_agree(oracle, precision, n_el, p):
+    """alpha staged in LDS (aligned buffers) and in registers (a lambda buffer
+    one element past a 16-byte boundary) run the same arithmetic: equal bits,
+    and the derivative along a random direction matches the complex step of
+    the oracle's collision (1e-12 per unit of sum |terms| in FP64; in FP32 the
+    outputs are rounded once, 2^-23 of the same sum)."""
+    ctx, cfg = make_pair(oracle, n_el, p, 0.05, 0.02, precision=precision)
+    f, g = _noisy(oracle, cfg, 3)
+    if precision:
+        f, g = f.astype(np.float32).astype(np.float64), g.astype(np.float32).astype(np.float64)
+    x = to_dev(ctx, f, g)
+    rng = np.random.default_rng(4)
+    lam = torch.from_numpy(rng.normal(size=x.shape)).to(ctx.device, ctx.dtype)
+    n = x.numel()
+    flat = torch.zeros(n + 1, dtype=ctx.dtype, device=ctx.device)
+    off = flat[1:].view(x.shape)
+    al = ctx.empty_state()
+    dmu = torch.zeros(2, dtype=torch.float64, device=ctx.device)
+    print("vjp forms", precision, n_el, p, flush=True)
+    ctx.adjoint_step(x, lam, al, dmu[:1])
+    ctx.adjoint_step(x, lam, off, dmu[1:])
+    assert torch.equal(al, off)
+    assert float(dmu[0]) == pytest.approx(float(dmu[1]), rel=1e-9, abs=1e-12 * float(lam.abs().sum()))
+    # <lam_out, d> = <S^T lam, J_C d>
+    d = rng.normal(size=(2,) + f.shape)
+    h = 1e-30
+    fc, gc = oracle.collide(cfg, f + 1j * h * d[0], g + 1j * h * d[1])
+    st = to_np(ctx.stream(lam, transpose=True))
+    L = to_np(al)
+    terms = np.abs(st[0] * fc.imag / h).sum() + np.abs(st[1] * gc.imag / h).sum() + np.abs(L[0] * d[0]).sum() + \
+        np.abs(L[1] * d[1]).sum()
+    ref = (st[0] * fc.imag / h).sum() + (st[1] * gc.imag / h).sum()
+    got = (L[0] * d[0]).sum() + (L[1] * d[1]).sum()
+    assert abs(got - ref) <= (2.0 ** -23 if precision else 1e-12) * terms
