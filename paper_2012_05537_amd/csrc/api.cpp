@@ -74,6 +74,10 @@ struct sllbm_ctx {
     int32_t *d_minv_start = nullptr;
     void *d_mpart = nullptr;       // partial sums of the transposed streaming, mqchunk velocities
     int mqchunk = 0;
+    int32_t *d_mchunk = nullptr;   // chunks of the streaming by departure cell (mnch per velocity)
+    int32_t *d_mrstart = nullptr;  // first chunk of every run of cells
+    int mnch = 0;
+    MappedRuns mruns{};
     GlcBasis glc{};
     std::string err;
 };
@@ -141,6 +145,8 @@ void free_ctx(sllbm_ctx *c)
     (void)hipFree(c->d_minv);
     (void)hipFree(c->d_minv_start);
     (void)hipFree(c->d_mpart);
+    (void)hipFree(c->d_mchunk);
+    (void)hipFree(c->d_mrstart);
     (void)hipFree(c->d_omin);
     (void)hipFree(c->d_lstar);
     (void)hipFree(c->d_cw);
@@ -221,7 +227,8 @@ int refuse_mapped(sllbm_ctx *c, const char *what)
 MappedTables mapped_tables(const sllbm_ctx *c)
 {
     return MappedTables{c->d_mcell, c->d_mt,        c->glc,  c->d_mwin, c->mwin_nodes,
-                        c->d_minv,  c->d_minv_start, c->d_mpart, c->mqchunk};
+                        c->d_minv,  c->d_minv_start, c->d_mpart, c->mqchunk, c->d_mchunk, c->mnch,
+                        c->d_mrstart, c->mruns};
 }
 
 const double *graded_hw(const sllbm_ctx *c) { return c->graded ? c->d_hw : nullptr; }
@@ -579,6 +586,11 @@ int sllbm_set_displacement(sllbm_ctx *ctx, const double *d)
         (void)hipFree(ctx->d_minv);
         (void)hipFree(ctx->d_minv_start);
         (void)hipFree(ctx->d_mpart);
+        (void)hipFree(ctx->d_mchunk);
+        (void)hipFree(ctx->d_mrstart);
+        ctx->d_mchunk = nullptr;
+        ctx->d_mrstart = nullptr;
+        ctx->mnch = 0;
         ctx->d_mcell = nullptr;
         ctx->d_mt = nullptr;
         ctx->d_mw = nullptr;
@@ -606,15 +618,30 @@ int sllbm_set_displacement(sllbm_ctx *ctx, const double *d)
         return fail(ctx, SLLBM_EINVAL, why);
     std::vector<int32_t> mwin;
     const int tile[3] = {MAPPED_TX, MAPPED_TY, MAPPED_TZ};
-    const int win_nodes = build_mapped_windows(ctx->vs.q, ctx->geo.p, ctx->geo.nel, cell, tile,
+    const bool by_cell = ctx->geo.p >= MAPPED_LIST_ORDER;
+    const int win_nodes = by_cell ? 0 : build_mapped_windows(ctx->vs.q, ctx->geo.p, ctx->geo.nel, cell, tile,
                                                MAPPED_WINDOW_BYTES / (2 * static_cast<int>(ctx->elem)), mwin);
     const int ncells = ctx->geo.nel[0] * ctx->geo.nel[1] * ctx->geo.nel[2];
     std::vector<int32_t> minv, minv_start;
     build_mapped_inverse(ctx->vs.q, N, ncells, cell, minv, minv_start);
+    std::vector<int32_t> mchunk, mrstart;
+    int nch = 0;
+    const MappedRuns runs = mapped_runs(ctx->geo.p, ctx->geo.nel[0], ctx->elem);
+    if (by_cell) {
+        // the local coordinates in list order, as the kernels read them
+        std::vector<double> sorted(tloc.size());
+        for (size_t k = 0; k < tloc.size() / N; ++k) {
+            const int32_t *o = &minv[(k % ctx->vs.q) * N];
+            for (int64_t n = 0; n < N; ++n) sorted[k * N + n] = tloc[k * N + o[n]];
+        }
+        tloc.swap(sorted);
+        cell.clear();
+        nch = build_mapped_chunks(ctx->vs.q, ctx->geo.nel, runs, minv_start, mchunk, mrstart);
+    }
     const int qchunk = mapped_t_chunk(ctx->vs.q, ctx->geo.p, ncells, ctx->elem);
     const int k3 = (ctx->geo.p + 1) * (ctx->geo.p + 1) * (ctx->geo.p + 1);
     const size_t pbytes = static_cast<size_t>(qchunk) * ncells * 2 * k3 * ctx->elem;
-    int32_t *dc = nullptr, *dwin = nullptr, *dinv = nullptr, *dinvs = nullptr;
+    int32_t *dc = nullptr, *dwin = nullptr, *dch = nullptr, *drs = nullptr, *dinv = nullptr, *dinvs = nullptr;
     void *dt = nullptr, *dpart = nullptr;
     double *dw = nullptr, *dj = nullptr;
     auto free_new = [&]() {
@@ -626,6 +653,8 @@ int sllbm_set_displacement(sllbm_ctx *ctx, const double *d)
         (void)hipFree(dinv);
         (void)hipFree(dinvs);
         (void)hipFree(dpart);
+        (void)hipFree(dch);
+        (void)hipFree(drs);
     };
     // local coordinates in the storage type
     std::vector<float> tloc32;
@@ -635,22 +664,28 @@ int sllbm_set_displacement(sllbm_ctx *ctx, const double *d)
         tsrc = tloc32.data();
     }
     const size_t tbytes = tloc.size() * ctx->elem;
-    if ((e = dalloc(&dc, cell.size() * sizeof(int32_t))) != hipSuccess ||
+    if ((!by_cell && (e = dalloc(&dc, cell.size() * sizeof(int32_t))) != hipSuccess) ||
         (e = hipMalloc(&dt, tbytes)) != hipSuccess ||
         (e = dalloc(&dw, nodew.size() * sizeof(double))) != hipSuccess ||
         (e = dalloc(&dj, cjac.size() * sizeof(double))) != hipSuccess ||
-        (e = dalloc(&dwin, mwin.size() * sizeof(int32_t))) != hipSuccess ||
+        (!by_cell && (e = dalloc(&dwin, mwin.size() * sizeof(int32_t))) != hipSuccess) ||
+        (by_cell && ((e = dalloc(&dch, mchunk.size() * sizeof(int32_t))) != hipSuccess ||
+                     (e = dalloc(&drs, mrstart.size() * sizeof(int32_t))) != hipSuccess)) ||
         (e = dalloc(&dinv, minv.size() * sizeof(int32_t))) != hipSuccess ||
         (e = dalloc(&dinvs, minv_start.size() * sizeof(int32_t))) != hipSuccess ||
         (e = hipMalloc(&dpart, pbytes)) != hipSuccess) {
         free_new();
         return fail(ctx, SLLBM_ENOMEM, std::string("distorted-mesh tables: ") + hipGetErrorString(e));
     }
-    if ((e = hipMemcpy(dc, cell.data(), cell.size() * sizeof(int32_t), hipMemcpyHostToDevice)) != hipSuccess ||
+    if ((!by_cell && (e = hipMemcpy(dc, cell.data(), cell.size() * sizeof(int32_t), hipMemcpyHostToDevice)) != hipSuccess) ||
         (e = hipMemcpy(dt, tsrc, tbytes, hipMemcpyHostToDevice)) != hipSuccess ||
         (e = hipMemcpy(dw, nodew.data(), nodew.size() * sizeof(double), hipMemcpyHostToDevice)) != hipSuccess ||
         (e = hipMemcpy(dj, cjac.data(), cjac.size() * sizeof(double), hipMemcpyHostToDevice)) != hipSuccess ||
-        (e = hipMemcpy(dwin, mwin.data(), mwin.size() * sizeof(int32_t), hipMemcpyHostToDevice)) != hipSuccess ||
+        (!by_cell && (e = hipMemcpy(dwin, mwin.data(), mwin.size() * sizeof(int32_t), hipMemcpyHostToDevice)) != hipSuccess) ||
+        (by_cell &&
+         ((e = hipMemcpy(dch, mchunk.data(), mchunk.size() * sizeof(int32_t), hipMemcpyHostToDevice)) != hipSuccess ||
+          (e = hipMemcpy(drs, mrstart.data(), mrstart.size() * sizeof(int32_t), hipMemcpyHostToDevice)) !=
+              hipSuccess)) ||
         (e = hipMemcpy(dinv, minv.data(), minv.size() * sizeof(int32_t), hipMemcpyHostToDevice)) != hipSuccess ||
         (e = hipMemcpy(dinvs, minv_start.data(), minv_start.size() * sizeof(int32_t), hipMemcpyHostToDevice)) !=
             hipSuccess) {
@@ -668,6 +703,10 @@ int sllbm_set_displacement(sllbm_ctx *ctx, const double *d)
     ctx->d_minv_start = dinvs;
     ctx->d_mpart = dpart;
     ctx->mqchunk = qchunk;
+    ctx->d_mchunk = dch;
+    ctx->d_mrstart = drs;
+    ctx->mnch = nch;
+    ctx->mruns = runs;
     const int p = ctx->geo.p;
     glc_points(p, ctx->glc.t);
     for (int k = 0; k <= p; ++k) {

@@ -148,19 +148,42 @@ constexpr int MAPPED_TX = 8, MAPPED_TY = 8, MAPPED_TZ = 4;   // 256 nodes
 constexpr int MAPPED_WINDOW_BYTES = 48 * 1024;                // LDS for the f and g windows of a block
 constexpr int MAPPED_MIN_WAVES = 5;                           // waves per SIMD the kernel is compiled for
 
+// From this order on (at least 27 nodes per cell) the streaming runs by
+// departure cell, on local coordinates in the order of the inverse lists.
+constexpr int MAPPED_LIST_ORDER = 3;
+// It runs over runs of cells along x; a run's source rows fit MAPPED_RUN_BYTES.
+constexpr int MAPPED_RUN_BYTES = 32 * 1024;
+struct MappedRuns {
+    int cells;      // cells of a run (the last one of a row may be shorter), at most 16
+    int nx;         // runs per row of cells
+    int width;      // nodes of a staged row: cells * p + 1, made odd (LDS banks)
+};
+MappedRuns mapped_runs(int p, int nel_x, size_t elem);
+// Chunks of the streaming by departure cell: the inverse lists (start of
+// build_mapped_inverse) cut into pieces of up to 16 nodes of one cell, as pairs
+// (cell in its run | count << 8, first list position), nch (returned) places
+// per velocity; rstart [q][runs + 1]: first chunk of every run of a velocity.
+int build_mapped_chunks(int q, const int nel[3], const MappedRuns &runs, const std::vector<int32_t> &start,
+                        std::vector<int32_t> &chunk, std::vector<int32_t> &rstart);
+
 // Device tables of a distorted mesh (build_mapped_tables); the local
 // coordinates are kept in the storage type (FP32 contexts: 16 bytes per
-// velocity and node instead of 28)
+// velocity and node instead of 28).  From MAPPED_LIST_ORDER on, tloc is in the
+// order of the inverse lists and cell and win are NULL.
 struct MappedTables {
     const int32_t *cell;    // [Q][N] departure cell, x fastest
     const void *tloc;       // [3][Q][N] local coordinates in [0, 1), storage type
     GlcBasis basis;
-    const int32_t *win;     // [Q][tiles][4] source window per (velocity, tile), or NULL
+    const int32_t *win;     // [Q][tiles][4] source window per (velocity, tile)
     int win_nodes;          // largest window (nodes per population) of the blocks that use LDS
     const int32_t *inv_order;   // [Q][N] nodes by departure cell (build_mapped_inverse)
     const int32_t *inv_start;   // [Q][C + 1]
     void *partial;              // [qchunk][C][2][(p+1)^3] partial sums of the transposed streaming
     int qchunk;                 // velocities per pass (mapped_t_chunk)
+    const int32_t *chunk;       // [Q][nch][2] chunks of the streaming by cell (build_mapped_chunks), or NULL
+    int nch;
+    const int32_t *rstart;      // [Q][runs + 1] first chunk of a run
+    MappedRuns runs;
 };
 
 struct CollisionParams {

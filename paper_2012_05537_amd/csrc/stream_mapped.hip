@@ -8,19 +8,11 @@
 // reference coordinates.  The host stores, per velocity and node, the
 // departure cell and the three local coordinates (28 bytes in FP64, 16 in
 // FP32); the weights are formed here ("matrix-free": 3 (P+1) Lagrange values
-// instead of (P+1)^3 stored coefficients).  Three kernels:
-//   * k_stream_mapped_win (the forward streaming): a block per velocity and
-//     node tile stages the tile's source window in LDS and gathers from it;
-//   * k_stream_mapped: the same gather straight from global memory, one
-//     thread per (velocity, node) (the blocks of k_stream_mapped_win whose
-//     window does not fit use the same summation);
+// instead of (P+1)^3 stored coefficients).  Kernels:
+//   * k_stream_mapped_cells (P >= 3): the forward streaming by departure cell;
+//   * k_stream_mapped_win (P < 3): the forward streaming by node tile, its
+//     source window staged in LDS;
 //   * k_stream_mapped_t_cells / _nodes: the transpose in a fixed order.
-// In k_stream_mapped, x-runs of P + 1 values are contiguous and neighbouring
-// threads read neighbouring runs, so the gathers are served by L1/L2.  When
-// rows and planes start on 16-byte boundaries and P is a multiple of the
-// vector width V, the first P values of a run (never wrapped: the cell's
-// first node plus P - 1 stays inside the row) are read as 16-byte vectors
-// and only the last one, which wraps at the periodic end, on its own.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -35,88 +27,187 @@ struct MVec {
     typedef S T __attribute__((ext_vector_type(V)));
 };
 
-template <typename S, int P, int V>
-__global__ void __launch_bounds__(256) k_stream_mapped(Geometry g, GlcBasis gb, const int32_t *__restrict__ cell,
-                                                       const S *__restrict__ tloc, const S *__restrict__ in,
-                                                       S *__restrict__ out)
+// w[a][k] = ell_k(t_a), formed in double from the coordinates tl[a]
+template <typename S, int P>
+__device__ __forceinline__ void lagrange_weights(const GlcBasis &gb, const double (&tl)[3], S (&w)[3][P + 1])
 {
-    const int i = blockIdx.y;
-    const int64_t N = g.nodes;
-    const int64_t n = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x;
-    if (n >= N) return;
-    const int Nx = g.N[0], Ny = g.N[1], Nz = g.N[2];
-    const int c = cell[static_cast<int64_t>(i) * N + n];
-    const int ex = c % g.nel[0], rest = c / g.nel[0];
-    const int ey = rest % g.nel[1], ez = rest / g.nel[1];
-    // Lagrange weights on the GLC points at the local coordinates
-    S w[3][P + 1];
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-        const double t = static_cast<double>(tloc[(static_cast<int64_t>(a) * Q + i) * N + n]);
+        double d[P + 1], pre[P + 1];                       // t - t_k, product of the d before k
 #pragma unroll
-        for (int k = 0; k <= P; ++k) {
-            double v = gb.inv_den[k];
+        for (int k = 0; k <= P; ++k) d[k] = tl[a] - gb.t[k];
+        pre[0] = 1.0;
 #pragma unroll
-            for (int m = 0; m <= P; ++m)
-                if (m != k) v *= t - gb.t[m];
-            w[a][k] = static_cast<S>(v);
+        for (int k = 1; k <= P; ++k) pre[k] = pre[k - 1] * d[k - 1];
+        double suf = 1.0;
+#pragma unroll
+        for (int k = P; k >= 0; --k) {
+            w[a][k] = static_cast<S>(gb.inv_den[k] * (pre[k] * suf));
+            suf *= d[k];
         }
     }
-    const S *fi = in + static_cast<int64_t>(i) * N;
-    const S *gi = in + static_cast<int64_t>(Q + i) * N;
-    S sf = 0, sg = 0;
-#pragma unroll
-    for (int kz = 0; kz <= P; ++kz) {
-        int zz = ez * P + kz;
-        zz = zz >= Nz ? zz - Nz : zz;
-#pragma unroll
-        for (int ky = 0; ky <= P; ++ky) {
-            int yy = ey * P + ky;
-            yy = yy >= Ny ? yy - Ny : yy;
-            const int64_t row = (static_cast<int64_t>(zz) * Ny + yy) * Nx;
-            S af = 0, ag = 0;
-            if constexpr (V > 1) {
-                using VT = typename MVec<S, V>::T;
-                const int64_t x0 = row + ex * P;
-#pragma unroll
-                for (int k0 = 0; k0 < P; k0 += V) {
-                    const VT vf = *reinterpret_cast<const VT *>(fi + x0 + k0);
-                    const VT vg = *reinterpret_cast<const VT *>(gi + x0 + k0);
-#pragma unroll
-                    for (int c = 0; c < V; ++c) {
-                        af = fma(w[0][k0 + c], vf[c], af);
-                        ag = fma(w[0][k0 + c], vg[c], ag);
-                    }
-                }
-                int xx = ex * P + P;
-                xx = xx >= Nx ? xx - Nx : xx;
-                af = fma(w[0][P], fi[row + xx], af);
-                ag = fma(w[0][P], gi[row + xx], ag);
-            } else {
-#pragma unroll
-                for (int kx = 0; kx <= P; ++kx) {
-                    int xx = ex * P + kx;
-                    xx = xx >= Nx ? xx - Nx : xx;
-                    af = fma(w[0][kx], fi[row + xx], af);
-                    ag = fma(w[0][kx], gi[row + xx], ag);
-                }
-            }
-            const S wyz = w[1][ky] * w[2][kz];
-            sf = fma(wyz, af, sf);
-            sg = fma(wyz, ag, sg);
-        }
-    }
-    out[static_cast<int64_t>(i) * N + n] = sf;
-    out[static_cast<int64_t>(Q + i) * N + n] = sg;
 }
 
-// The same streaming with the source values staged in LDS: a block owns one
-// velocity and a tile of MAPPED_TX x MAPPED_TY x MAPPED_TZ nodes; the host
-// has found the box of cells that holds the departure cells of all of them
-// (build_mapped_windows), the block loads that window once (coalesced rows,
-// each value once from L2 instead of once per reading thread through L1),
-// f and g of a node side by side so that one LDS read returns both, and every
-// thread gathers its (P+1)^3 support pairs from LDS.  The blocks run in
+// acc += (element J of src) * w, J = the lane of its 16-lane row that holds
+// the element (row_newbcast).
+template <int J>
+__device__ __forceinline__ void fmac_row(double &acc, double src, double w)
+{
+    asm("v_fmac_f64_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(acc) : "v"(src), "v"(w), "n"(J));
+}
+template <int J>
+__device__ __forceinline__ void fmac_row(float &acc, float src, float w)
+{
+    asm("v_fmac_f32_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(acc) : "v"(src), "v"(w), "n"(J));
+}
+
+// sf, sg += sum over the cell's elements E, E + 1, ... of weight times value.
+// z: sums of the current z plane so far, two for f and two for g (element
+// pairs alternate), so that four chains are in flight: a chain's next
+// broadcast FMA must not follow within two wait states.
+template <typename S, int P, int E, int NR>
+__device__ __forceinline__ void cell_sum(const S (&vf)[NR], const S (&vg)[NR], const S (&wxy)[(P + 1) * (P + 1)],
+                                         const S (&wz)[P + 1], S (&z)[4], S &sf, S &sg)
+{
+    constexpr int K = P + 1, K2 = K * K;
+    fmac_row<E % 16>(z[E % K2 % 2], vf[E / 16], wxy[E % K2]);
+    fmac_row<E % 16>(z[2 + E % K2 % 2], vg[E / 16], wxy[E % K2]);
+    if constexpr (E % K2 == K2 - 1) {
+        sf = fma(wz[E / K2], z[0] + z[1], sf);
+        sg = fma(wz[E / K2], z[2] + z[3], sg);
+        z[0] = z[1] = z[2] = z[3] = 0;
+    }
+    if constexpr (E + 1 < K2 * K) cell_sum<S, P, E + 1>(vf, vg, wxy, wz, z, sf, sg);
+}
+
+// Streaming by departure cell.  A block owns one velocity and a run of cells
+// along x (MappedRuns): it stages the run's source rows of f and g in LDS
+// (coalesced, each value once) and takes the nodes that depart into the run.
+// A 16-lane row takes one chunk, up to 16 nodes that depart into one cell
+// (build_mapped_chunks), and holds that cell's (P+1)^3 support values of f and
+// of g once, spread over its lanes; they enter the FMAs as row broadcasts, so
+// that a support value costs one LDS read per 16 outputs and not one per output.
+// Bound by the vector pipes (about 400 instructions per 64 lanes at P = 4, 250
+// of them the FMAs of f and g; rows are 80 % full) together with the scattered
+// reads and writes; measured at 64^3 nodes, P = 4: 235 us in FP64 and 163 us in
+// FP32, against 376 and 249 us for the gather out of LDS by node tile, which
+// read 2 KB from LDS per output (P = 3, 48^3 nodes: 77 / 54 against 109 / 77 us;
+// P = 6: 184 / 126 against 518 / 219 us on 42 x 42 x 48).
+// Also measured: the support values as scalar operands through the scalar cache
+// 774 us (its misses serialise); rows loaded straight from global memory
+// 310 us (every cache line is fetched by four cells).
+// tloc: local coordinates in list order; chunk: [Q][nch] (cell in the run and
+// count, first list position); rstart: [Q][runs + 1] first chunk of a run.
+template <typename S, int P>
+__global__ void __launch_bounds__(256, P <= 4 ? 4 : 2)
+    k_stream_mapped_cells(Geometry g, GlcBasis gb, MappedRuns runs, const int32_t *__restrict__ order,
+                          const int2 *__restrict__ chunk, int nch, const int32_t *__restrict__ rstart,
+                          const S *__restrict__ tloc, const S *__restrict__ in, S *__restrict__ out)
+{
+    constexpr int K = P + 1, K3 = K * K * K, NR = (K3 + 15) / 16;
+    using S2 = typename MVec<S, 2>::T;
+    extern __shared__ __align__(16) unsigned char smem[];
+    S2 *lw = reinterpret_cast<S2 *>(smem);                 // [K][K][width] f and g of the run's window
+    const int L = __builtin_amdgcn_readfirstlane(xcd_linear(blockIdx.x, gridDim.x));
+    const int nruns = runs.nx * g.nel[1] * g.nel[2];
+    const int i = L / nruns, run = L - i * nruns;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int row = (threadIdx.x >> 4) & 3, j = threadIdx.x & 15;
+    const int64_t N = g.nodes;
+    const int Nx = g.N[0], Ny = g.N[1], Nz = g.N[2];
+    const S *__restrict__ fi = in + static_cast<int64_t>(i) * N;
+    const S *__restrict__ gi = in + static_cast<int64_t>(Q + i) * N;
+    S *__restrict__ fo = out + static_cast<int64_t>(i) * N;
+    S *__restrict__ go = out + static_cast<int64_t>(Q + i) * N;
+    const int q0 = rstart[static_cast<int64_t>(i) * (nruns + 1) + run];
+    const int q1 = rstart[static_cast<int64_t>(i) * (nruns + 1) + run + 1];
+    if (q0 == q1) return;                                  // nothing departs into this run
+    const int2 *__restrict__ ch = chunk + static_cast<int64_t>(i) * nch;
+    int2 d;
+    int n_next;
+    S tl_next[3];
+    auto load_entry = [&](int q) {                         // the row's chunk of group q, and its list entry
+        d = ch[min(q + row, q1 - 1)];
+        const int count = d.x >> 8;
+        const int64_t le = static_cast<int64_t>(i) * N + d.y + min(j, count - 1);
+        n_next = order[le];
+#pragma unroll
+        for (int a = 0; a < 3; ++a) tl_next[a] = tloc[static_cast<int64_t>(a) * Q * N + le];
+    };
+    {
+        const int rx = run % runs.nx, r1 = run / runs.nx;
+        const int ey = r1 % g.nel[1], ez = r1 / g.nel[1];
+        const int ex = rx * runs.cells;
+        const int width = min(runs.cells, g.nel[0] - ex) * P + 1;
+        const int x0 = ex * P, y0 = ey * P, z0 = ez * P;
+        const float rw = 1.0f / static_cast<float>(width);
+        for (int k = threadIdx.x; k < K * K * width; k += 256) {
+            // exact quotient: (k + 1/2) / width lies at least 1 / (2 width) from an
+            // integer, and k < 2^13
+            const int r = static_cast<int>((static_cast<float>(k) + 0.5f) * rw);
+            const int x = k - r * width;
+            int xx = x0 + x, yy = y0 + r % K, zz = z0 + r / K;
+            xx -= xx >= Nx ? Nx : 0;
+            yy -= yy >= Ny ? Ny : 0;
+            zz -= zz >= Nz ? Nz : 0;
+            const int64_t node = (static_cast<int64_t>(zz) * Ny + yy) * Nx + xx;
+            S2 v;
+            v.x = fi[node];
+            v.y = gi[node];
+            lw[r * runs.width + x] = v;
+        }
+    }
+    // elements 16 r + j of a cell: LDS offset from its first node
+    int off[NR];
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+        const int e = min(16 * r + j, K3 - 1);
+        off[r] = e / K * runs.width + e % K;
+    }
+    load_entry(q0 + wave * 4);
+    __syncthreads();
+    for (int q = q0 + wave * 4; q < q1; q += 16) {
+        const int count = q + row < q1 ? d.x >> 8 : 0;
+        const int n = n_next;
+        const double tl[3] = {static_cast<double>(tl_next[0]), static_cast<double>(tl_next[1]),
+                              static_cast<double>(tl_next[2])};
+        const S2 *cell = lw + (d.x & 255) * P;
+        S vf[NR], vg[NR];
+#pragma unroll
+        for (int r = 0; r < NR; ++r) {
+            const S2 v = cell[off[r]];
+            vf[r] = v.x;
+            vg[r] = v.y;
+        }
+        load_entry(q + 16);                                // past the run: its last chunk again
+        S w[3][K], wxy[K * K];
+        lagrange_weights<S, P>(gb, tl, w);
+#pragma unroll
+        for (int y = 0; y < K; ++y)
+#pragma unroll
+            for (int x = 0; x < K; ++x) wxy[y * K + x] = w[1][y] * w[0][x];
+        S sf = 0, sg = 0, z[4] = {0, 0, 0, 0};
+        // a broadcast may follow a vector write of its source by no less than two
+        // wait states; what writes vf and vg is finished before this
+#pragma unroll
+        for (int r = 0; r < NR; ++r) asm volatile("" : "+v"(vf[r]), "+v"(vg[r]));
+        asm volatile("s_nop 1");
+        cell_sum<S, P, 0>(vf, vg, wxy, w[2], z, sf, sg);
+        if (j < count) {
+            fo[n] = sf;
+            go[n] = sg;
+        }
+    }
+}
+
+// Streaming by node tile, for orders below MAPPED_LIST_ORDER, whose cells have
+// too few nodes (P^3 = 1 or 8) to fill the 16-lane rows of
+// k_stream_mapped_cells (64^3 nodes, P = 2, FP64: 186 against 233 us).  A block
+// owns one velocity and a tile of MAPPED_TX x MAPPED_TY x MAPPED_TZ nodes; the
+// host has found the box of cells that holds the departure cells of all of
+// them (build_mapped_windows), the block loads that window once (coalesced
+// rows), f and g of a node side by side so that one LDS read returns both, and
+// every thread gathers its (P+1)^3 support pairs from LDS.  The blocks run in
 // XCD-aware order (consecutive tiles of a velocity on one XCD, where their
 // overlapping windows and the table lines they share meet in one L2).  A
 // block whose window exceeds the LDS budget gathers from global memory
@@ -277,7 +368,8 @@ __global__ void __launch_bounds__(mt_threads<P>()) k_stream_mapped_t_cells(
             const int64_t n = order[static_cast<int64_t>(i) * N + base + tid];
 #pragma unroll
             for (int ax = 0; ax < 3; ++ax) {
-                const double tt = static_cast<double>(tloc[(static_cast<int64_t>(ax) * Q + i) * N + n]);
+                const int64_t at = P >= MAPPED_LIST_ORDER ? base + tid : n;
+                const double tt = static_cast<double>(tloc[(static_cast<int64_t>(ax) * Q + i) * N + at]);
 #pragma unroll
                 for (int k = 0; k <= P; ++k) {
                     double v = gb.inv_den[k];
@@ -377,7 +469,15 @@ hipError_t launch_mt(const Geometry &g, const MappedTables &t, const S *in, S *o
 template <typename S, int P>
 hipError_t launch_m(const Geometry &g, const MappedTables &t, const S *in, S *out, hipStream_t st)
 {
-    if (t.win) {
+    if constexpr (P >= MAPPED_LIST_ORDER) {
+        const int64_t blocks = static_cast<int64_t>(Q) * t.runs.nx * g.nel[1] * g.nel[2];
+        if (blocks > (int64_t(1) << 31) - 1) return hipErrorInvalidValue;
+        const size_t lds = 2 * static_cast<size_t>(P + 1) * (P + 1) * t.runs.width * sizeof(S);
+        hipLaunchKernelGGL((k_stream_mapped_cells<S, P>), dim3(static_cast<unsigned>(blocks)), dim3(256), lds, st, g,
+                           t.basis, t.runs, t.inv_order, reinterpret_cast<const int2 *>(t.chunk), t.nch, t.rstart,
+                           static_cast<const S *>(t.tloc), in, out);
+        return hipGetLastError();
+    } else {
         const int ntx = (g.N[0] + MAPPED_TX - 1) / MAPPED_TX, nty = (g.N[1] + MAPPED_TY - 1) / MAPPED_TY,
                   ntz = (g.N[2] + MAPPED_TZ - 1) / MAPPED_TZ;
         const int64_t ntiles = static_cast<int64_t>(ntx) * nty * ntz;
@@ -388,23 +488,6 @@ hipError_t launch_m(const Geometry &g, const MappedTables &t, const S *in, S *ou
                            nty, in, out);
         return hipGetLastError();
     }
-    const int64_t bx = (g.nodes + 255) / 256;
-    if (bx > (int64_t(1) << 31) - 1) return hipErrorInvalidValue;
-    constexpr int V = 16 / sizeof(S);
-    // 16-byte loads: every plane (N values) and row (N_x values) starts on a
-    // 16-byte boundary, and a cell's first node is a multiple of V
-    const bool aligned = (g.nodes * sizeof(S)) % 16 == 0 && (g.N[0] * sizeof(S)) % 16 == 0 &&
-                         reinterpret_cast<uintptr_t>(in) % 16 == 0;
-    if constexpr (P % V == 0) {
-        if (aligned) {
-            hipLaunchKernelGGL((k_stream_mapped<S, P, V>), dim3(static_cast<unsigned>(bx), Q), dim3(256), 0, st, g,
-                               t.basis, t.cell, static_cast<const S *>(t.tloc), in, out);
-            return hipGetLastError();
-        }
-    }
-    hipLaunchKernelGGL((k_stream_mapped<S, P, 1>), dim3(static_cast<unsigned>(bx), Q), dim3(256), 0, st, g, t.basis,
-                       t.cell, static_cast<const S *>(t.tloc), in, out);
-    return hipGetLastError();
 }
 
 }  // namespace

@@ -280,6 +280,52 @@ void build_mapped_inverse(int q, int64_t nodes, int ncells, const std::vector<in
     }
 }
 
+MappedRuns mapped_runs(int p, int nel_x, size_t elem)
+{
+    const int most = MAPPED_RUN_BYTES / static_cast<int>(2 * (p + 1) * (p + 1) * elem);   // nodes per row
+    const int cells = std::max(1, std::min(16, (most - 2) / p));
+    MappedRuns r;
+    r.nx = (nel_x + cells - 1) / cells;
+    r.cells = (nel_x + r.nx - 1) / r.nx;                  // runs of about equal length
+    r.nx = (nel_x + r.cells - 1) / r.cells;
+    r.width = (r.cells * p + 1) | 1;
+    return r;
+}
+
+int build_mapped_chunks(int q, const int nel[3], const MappedRuns &runs, const std::vector<int32_t> &start,
+                        std::vector<int32_t> &chunk, std::vector<int32_t> &rstart)
+{
+    const int ncells = nel[0] * nel[1] * nel[2], nruns = runs.nx * nel[1] * nel[2];
+    int64_t nch = 0;
+    for (int i = 0; i < q; ++i) {
+        const int32_t *st = &start[static_cast<size_t>(i) * (ncells + 1)];
+        int64_t n = 0;
+        for (int c = 0; c < ncells; ++c) n += (st[c + 1] - st[c] + 15) / 16;
+        nch = std::max(nch, n);
+    }
+    chunk.assign(static_cast<size_t>(q) * nch * 2, 0);
+    rstart.assign(static_cast<size_t>(q) * (nruns + 1), 0);
+    for (int i = 0; i < q; ++i) {
+        const int32_t *st = &start[static_cast<size_t>(i) * (ncells + 1)];
+        int32_t *o = &chunk[static_cast<size_t>(i) * nch * 2];
+        int32_t *rs = &rstart[static_cast<size_t>(i) * (nruns + 1)];
+        int32_t n = 0;
+        for (int r = 0; r < nruns; ++r) {
+            rs[r] = n;
+            const int x0 = (r % runs.nx) * runs.cells, x1 = std::min(nel[0], x0 + runs.cells);
+            for (int x = x0; x < x1; ++x) {
+                const int c = (r / runs.nx) * nel[0] + x;
+                for (int32_t b = st[c]; b < st[c + 1]; b += 16, ++n) {
+                    *o++ = (x - x0) | std::min(16, st[c + 1] - b) << 8;
+                    *o++ = b;
+                }
+            }
+        }
+        rs[nruns] = n;
+    }
+    return static_cast<int>(nch);
+}
+
 int mapped_t_chunk(int q, int p, int64_t ncells, size_t elem)
 {
     const int64_t k3 = static_cast<int64_t>(p + 1) * (p + 1) * (p + 1);

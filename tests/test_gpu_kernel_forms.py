@@ -6,7 +6,7 @@ import numpy as np
 import pytest
 import torch
 
-from gpu_common import make_pair, require_gpu, to_dev, to_np
+from gpu_common import Q, make_pair, rel_err, require_gpu, to_dev, to_np
 from paper_2012_05537_amd import inputs
 
 pytestmark = pytest.mark.gpu
@@ -68,3 +68,36 @@ def test_collision_vjp_forms_agree(oracle, precision, n_el, p):
     ref = (st[0] * fc.imag / h).sum() + (st[1] * gc.imag / h).sum()
     got = (L[0] * d[0]).sum() + (L[1] * d[1]).sum()
     assert abs(got - ref) <= (2.0 ** -23 if precision else 1e-12) * terms
+
+
+def _displacement(ctx, a):
+    xs, ys, zs = (c.numpy() for c in ctx.node_coords())
+    X, Y, Z = inputs.mesh(xs, ys, zs)
+    return a * np.stack([np.sin(X + Y) + 0.3 * np.cos(2 * Z), np.cos(Y + Z), np.sin(Z - X)])
+
+
+# orders below and from the change of kernel on; one-cell axes, a row of cells
+# longer than a run (19 cells: two runs), shifts of several cells, a ragged row
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("n_el,p,dt", [((1, 2, 1), 3, 0.3), ((19, 2, 2), 3, 0.05), ((5, 4, 3), 3, 0.4), ((17, 3, 1), 4, 0.02),
+                                       ((3, 3, 4), 4, 0.3), ((9, 2, 2), 5, 0.1), ((2, 3, 7), 6, 0.1), ((4, 3, 5), 2, 0.2)])
+def test_distorted_streaming_by_cell(oracle, precision, n_el, p, dt):
+    """Streaming on distorted cells against the oracle (1e-12, FP32 1e-5, the
+    repository's bars), and its transpose as the adjoint of it."""
+    from paper_2012_05537_amd.sllbm import SLLBM
+    ctx = SLLBM(n_el, p, dt, 0.01, precision=precision)
+    d = _displacement(ctx, 0.02)
+    ctx.set_displacement(d)
+    cfg = oracle.make_cfg(n_el, p, dt, 0.01, disp=d)
+    rng = np.random.default_rng(8)
+    x = rng.normal(size=(2, Q, ctx.nodes)).astype(np.float32).astype(np.float64)
+    y = rng.normal(size=x.shape).astype(np.float32).astype(np.float64)
+    print("distorted streaming", precision, n_el, p, flush=True)
+    S = to_np(ctx.stream(to_dev(ctx, x[0], x[1])))
+    f, g = oracle.stream(cfg, x[0], x[1])
+    tol = 1e-5 if precision else 1e-12
+    assert rel_err(S[0], f) < tol and rel_err(S[1], g) < tol
+    st = to_np(ctx.stream(to_dev(ctx, y[0], y[1]), transpose=True))
+    a, b = (f * y[0]).sum() + (g * y[1]).sum(), (x[0] * st[0]).sum() + (x[1] * st[1]).sum()
+    scale = np.abs(f * y[0]).sum() + np.abs(g * y[1]).sum()
+    assert abs(a - b) <= tol * scale
