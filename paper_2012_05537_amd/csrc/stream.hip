@@ -1,20 +1,17 @@
-// Semi-Lagrangian streaming (Sec. II A, Eqs. (8)-(9)) as a z-march per
-// (velocity, population) plane and x-y tile.
+// Semi-Lagrangian streaming (Sec. II A, Eqs. (8)-(9)) by source cell, and its
+// transpose.
 //
 // For velocity i the interpolant factorises into three 1-D operators, and
 // along an axis output node e*P + l reads source cell e + o_l, o_l = omin for
-// l < lstar and omin + 1 otherwise.  A block owns one population plane of one
-// velocity over an x-y tile of TX x TY nodes and walks the z axis:
-//   * each source z-row of the tile's window (TX + P + 1 by TY + P + 1 nodes)
-//     is loaded once (the next row's loads are in flight while the current
-//     row is processed), interpolated along x and then y in LDS, which leaves
-//     one value A per output (x, y) and source row;
-//   * a thread keeps the A values of the two source cells that output cell
-//     e reads (2P + 1 rows) in registers and forms the P outputs of the cell
-//     along z with the cell's uniform z weights, then slides by one cell.
-// Every source value is read from HBM once per plane (x-y halos of
-// neighbouring tiles are served by L2: the tiles of one plane are dealt to
-// one XCD), and the outputs are written once, x fastest.
+// l < lstar and omin + 1 otherwise.  The outputs that read source cell c thus
+// form a group of P consecutive nodes, (c - omin - 1)*P + lstar + j, j =
+// 0 .. P-1, read with weight row (lstar + j) mod P: each source cell of
+// (P + 1)^3 nodes (faces shared with its neighbours) maps to P^3 outputs of
+// its own, whatever the shift, and there is no halo beyond the shared faces.
+// A lane takes one column (x) of a source cell: it loads the P + 1 nodes along
+// y of each z-row, interpolates along y and z in registers with the
+// velocity's uniform weights, and leaves P x P values in LDS, from which the
+// block's lanes interpolate along x, one output column each.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -33,6 +30,314 @@ __device__ __forceinline__ int wrapi(int x, int n)
     int r = x % n;
     return r < 0 ? r + n : r;
 }
+
+// How an x-y plane is dealt to blocks and lanes.  A block holds tyc cells
+// along y and cx columns of each.  While x rows fit a block (N_x <= ZNT),
+// cx = N_x: the periodic row is complete and lane x writes output column x.
+// Longer rows are split into tiles of txc cells; a tile has halo columns more
+// than it writes (forward: the last cell's far face; transposed: the group
+// before the tile).
+struct ZLayout {
+    int cx, txc, tyc, ntx, nty, nt;   // nt: threads per block
+    float rcx;                        // 1 / cx
+    int zcells, nchunk;               // cells along z per block, blocks along z
+};
+
+constexpr int ZNT = 256;              // most threads per block
+
+// the split with the fewest idle lanes
+ZLayout z_layout(const Geometry &g, int halo)
+{
+    ZLayout b{};
+    double best = 0.0;
+    const bool whole = g.N[0] <= ZNT;
+    const int t0 = whole ? g.nel[0] : (64 - halo) / g.p, t1 = whole ? g.nel[0] : (ZNT - halo) / g.p;
+    for (int txc = t0; txc <= t1; ++txc) {
+        const int cx = whole ? g.N[0] : txc * g.p + halo;
+        const int ntx = (g.nel[0] + txc - 1) / txc;
+        for (int tyc = 1; tyc <= g.nel[1] && cx * tyc <= ZNT; ++tyc) {
+            const int nt = (cx * tyc + 63) / 64 * 64, nty = (g.nel[1] + tyc - 1) / tyc;
+            const double used = static_cast<double>(g.nel[1]) * g.N[0] / (static_cast<double>(nt) * ntx * nty);
+            if (used >= best) {
+                best = used;
+                b = ZLayout{cx, txc, tyc, ntx, nty, nt, 1.0f / static_cast<float>(cx), 0, 0};
+            }
+        }
+    }
+    return b;
+}
+
+// Cells along z per block: at most max_cells, fewer while the grid has fewer
+// than Z_TARGET_BLOCKS blocks of 256 threads.
+constexpr int Z_TARGET_BLOCKS = 1024;
+
+// nblocks: blocks per plane (the grid is nblocks x 90: with one dimension its
+// threads would pass 2^32 on the largest grids)
+bool z_split(const Geometry &g, int max_cells, ZLayout &b, unsigned &nblocks)
+{
+    const int64_t tiles = static_cast<int64_t>(b.ntx) * b.nty;
+    const int64_t want = (static_cast<int64_t>(Z_TARGET_BLOCKS) * ZNT / b.nt + 90 * tiles - 1) / (90 * tiles);
+    const int n = std::max(static_cast<int>(std::min<int64_t>(g.nel[2], want)), (g.nel[2] + max_cells - 1) / max_cells);
+    b.zcells = (g.nel[2] + n - 1) / n;
+    b.nchunk = (g.nel[2] + b.zcells - 1) / b.zcells;
+    nblocks = static_cast<unsigned>(tiles * b.nchunk);
+    return 90 * tiles * b.nchunk <= (int64_t(1) << 31) - 1;
+}
+
+}  // namespace
+
+// Byte offset of a node in an x-y plane: 32 bits suffice (the 90 planes of a
+// state whose x-y plane had 4 GB would not fit the card), so that an access is
+// a uniform row address plus one register per lane.
+template <typename S>
+__device__ __forceinline__ uint32_t plane_offset(int node)
+{
+    return static_cast<uint32_t>(node) * static_cast<uint32_t>(sizeof(S));
+}
+// A row of a plane as the compiler must see it, a uniform address that it does
+// not know: otherwise it keeps plane address + offset, 64 bits per lane and
+// access, across the loop.
+template <typename S>
+using GlobalRow = __attribute__((address_space(1))) S *;
+template <typename S>
+__device__ __forceinline__ GlobalRow<S> plane_row(S *base, int64_t node)
+{
+    GlobalRow<S> r = (GlobalRow<S>)(base + node);
+    asm volatile("" : "+s"(r));
+    return r;
+}
+template <typename S>
+__device__ __forceinline__ S load_at(GlobalRow<S> row, uint32_t off)
+{
+    return *(GlobalRow<S>)((__attribute__((address_space(1))) char *)row + off);
+}
+template <bool NTH, typename S>
+__device__ __forceinline__ void store_at(GlobalRow<S> row, uint32_t off, S v)
+{
+    GlobalRow<S> p = (GlobalRow<S>)((__attribute__((address_space(1))) char *)row + off);
+    if constexpr (NTH) __builtin_nontemporal_store(v, p);
+    else *p = v;
+}
+
+// Cells along z per block of the forward kernel.  One source cell from order 3
+// on: every load of a block is then in flight at once, and the blocks of an
+// XCD cover a thin slab whose shared faces meet in its L2 (256^3 nodes, P = 4,
+// FP64: 4.11 ms; marching 4, 16 or 64 cells with the next cell's rows in
+// flight 4.28, 4.38 and 4.79 ms).  Cells of order 1 and 2 are too small for
+// that and are marched (48 x 40 x 40 nodes, P = 2: 17.8 us with two cells, 20.8
+// with one; 100 x 100 x 30, P = 1, FP32: 51 us with 30, 214 with one).
+template <int P>
+constexpr int z_max_cells()
+{
+    return P >= 3 ? 1 : P == 2 ? 2 : 32;
+}
+
+template <typename S, int P>
+constexpr int z_min_waves()
+{
+    return sizeof(S) == 4 ? (P <= 4 ? 5 : P == 5 ? 4 : 3) : (P <= 3 ? 5 : P == 4 ? 4 : P == 5 ? 3 : 2);
+}
+
+// Streaming, by source cell.  Bound by HBM: every value is read from it once
+// (the (P+1)/P-fold y and z faces come from L1 and L2) and written once.  At
+// 256^3 nodes, P = 4: 4.11 ms in FP64 and 2.07 ms in FP32 (5.9 and 5.8 TB/s,
+// the rate of a copy); 64^3 71 / 29 us, 24^3 (P = 3) 7.0 us, 100^3 nodes
+// at P = 5 294 us.  The march by 32 x 8 and 32 x 16 output tiles that this
+// replaces read a window of P + 1 more rows and columns per tile out of LDS
+// and took 5.2 / 2.9 ms, 89 / 47 us, 11.4 us and 668 us.
+// NTH: non-temporal output stores (states larger than the Infinity Cache)
+template <typename S, int P, bool NTH>
+__global__ void __launch_bounds__(ZNT, (z_min_waves<S, P>())) k_stream_z(Geometry g, CellTables<S> tab,
+                                                                        const S *__restrict__ in,
+                                                                        S *__restrict__ out, ZLayout lay)
+{
+    __shared__ S buf[P * P][ZNT];                          // y-z-interpolated values of a source cell, per lane
+    const int tid = threadIdx.x;
+    const int ntiles = lay.ntx * lay.nty;
+    const int L = __builtin_amdgcn_readfirstlane(xcd_linear(static_cast<int>(blockIdx.y * gridDim.x + blockIdx.x),
+                                                                static_cast<int>(gridDim.x * gridDim.y)));
+    const int q = L / (ntiles * lay.nchunk);
+    const int rem = L - q * ntiles * lay.nchunk;
+    const int chunk = rem / ntiles, tile = rem - chunk * ntiles;
+    const int ty = tile / lay.ntx, tx = tile - ty * lay.ntx;
+    const int i = q >> 1, pop = q & 1;
+    const int Nx = g.N[0], Ny = g.N[1], Nz = g.N[2];
+    const int64_t N = g.nodes, NP = static_cast<int64_t>(Nx) * Ny;
+    const int omx = tab.omin[i * 3 + 0], omy = tab.omin[i * 3 + 1], omz = tab.omin[i * 3 + 2];
+    const int lsx = tab.lstar[i * 3 + 0], lsy = tab.lstar[i * 3 + 1], lsz = tab.lstar[i * 3 + 2];
+    const S *Wx = tab.w + (i * 3 + 0) * P * (P + 1);
+    const S *Wy = tab.w + (i * 3 + 1) * P * (P + 1);
+    const S *Wz = tab.w + (i * 3 + 2) * P * (P + 1);
+    S *src = const_cast<S *>(in) + static_cast<int64_t>(pop * 45 + i) * N;
+    S *dst = out + static_cast<int64_t>(pop * 45 + i) * N;
+
+    // this lane's source column: cell cy along y, node column x.  Lanes without
+    // an output of their own repeat lane 0, store included (the same value):
+    // stores under a branch would make every later wait for a load a wait for
+    // them.
+    const int cx0 = tx * lay.txc, cy0 = ty * lay.tyc;
+    // exact quotient: (tid + 1/2) / cx lies at least 1 / (2 cx) from an integer
+    int cyl = static_cast<int>((static_cast<float>(tid) + 0.5f) * lay.rcx), xl = tid - cyl * lay.cx;
+    const int ncx = min(lay.txc, g.nel[0] - cx0);          // cells of this tile along x
+    const bool whole = lay.ntx == 1;
+    const bool used = cyl < min(lay.tyc, g.nel[1] - cy0) && (whole || xl <= ncx * P);
+    cyl = used ? cyl : 0;
+    xl = used ? xl : 0;
+    const int cy = cy0 + cyl;
+    int xs = cx0 * P + xl;
+    xs -= xs >= Nx ? Nx : 0;
+    const uint32_t lo = plane_offset<S>(cy * P * Nx + xs);            // the cell's first row and last row
+    const uint32_t le = plane_offset<S>((cy + 1 == g.nel[1] ? 0 : cy + 1) * P * Nx + xs);
+
+    // this lane's output column and its taps in the block's row of columns
+    int xo, cell;                                          // output x; source cell (of the row, or of the tile)
+    S xw[P + 1];
+    {
+        int row;
+        if (whole) {
+            xo = xl;
+            row = xl % P;
+            cell = xl / P + wrapi(omx, g.nel[0]) + (row >= lsx ? 1 : 0);
+            cell -= cell >= g.nel[0] ? g.nel[0] : 0;
+            cell -= cell >= g.nel[0] ? g.nel[0] : 0;
+        } else {
+            cell = xl < ncx * P ? xl / P : 0;
+            const int j = lsx + xl % P;
+            row = j % P;
+            xo = wrapi((cx0 - omx - 1) * P, Nx) + cell * P + j;     // below 2 N_x + P
+            xo -= xo >= Nx ? Nx : 0;
+            xo -= xo >= Nx ? Nx : 0;
+        }
+#pragma unroll
+        for (int r = 0; r <= P; ++r) xw[r] = Wx[row * (P + 1) + r];
+    }
+    const int b0 = cyl * lay.cx + cell * P;                // first tap; the last one wraps in a whole row
+    const int bl = whole && cell + 1 == g.nel[0] ? cyl * lay.cx : b0 + P;
+    // output rows of source cell cy along y: (cy - omy - 1) P + lsy + j
+    uint32_t oo[P];
+    {
+        int y0 = wrapi((cy0 - omy - 1) * P, Ny) + cyl * P + lsy;    // below 2 N_y + P
+        y0 -= y0 >= Ny ? Ny : 0;
+        y0 -= y0 >= Ny ? Ny : 0;
+#pragma unroll
+        for (int j = 0; j < P; ++j) oo[j] = plane_offset<S>((y0 + j - (y0 + j >= Ny ? Ny : 0)) * Nx + xo);
+    }
+    S wy[P][P + 1];                                        // uniform weights: output j reads with row (lsy + j) mod P
+#pragma unroll
+    for (int j = 0; j < P; ++j)
+#pragma unroll
+        for (int r = 0; r <= P; ++r) wy[j][r] = Wy[((lsy + j) % P) * (P + 1) + r];
+    // z weights: from order 4 on they are fetched for each row through the
+    // scalar cache (beside wy they exceed the scalar registers)
+    using CS = const __attribute__((address_space(4))) S;
+    CS *wzp = (CS *)Wz;
+    int wzo[P];
+#pragma unroll
+    for (int l = 0; l < P; ++l) wzo[l] = (lsz + l) % P * (P + 1);
+    auto zweights = [&](int r, S (&w)[P]) {
+        if constexpr (P >= 4) asm volatile("" : "+s"(wzp));
+#pragma unroll
+        for (int l = 0; l < P; ++l) w[l] = wzp[wzo[l] + r];
+    };
+
+    const int zc0 = chunk * lay.zcells, zc1 = min(g.nel[2], zc0 + lay.zcells);
+    auto load_row = [&](S (&v)[P + 1], int z) {
+        const int64_t zo = static_cast<int64_t>(z >= Nz ? z - Nz : z) * NP;
+#pragma unroll
+        for (int m = 0; m < P; ++m) v[m] = load_at<S>(plane_row(src, zo + static_cast<int64_t>(m) * Nx), lo);
+        v[P] = load_at<S>(plane_row(src, zo), le);
+    };
+    S Y[P], acc[P][P];
+    auto interp_y = [&](const S (&v)[P + 1]) {
+#pragma unroll
+        for (int j = 0; j < P; ++j) {
+            Y[j] = wy[j][0] * v[0];
+#pragma unroll
+            for (int m = 1; m <= P; ++m) Y[j] = fma(wy[j][m], v[m], Y[j]);
+        }
+    };
+    auto first_row = [&] {                                 // acc of a cell from its first row
+        S w[P];
+        zweights(0, w);
+#pragma unroll
+        for (int l = 0; l < P; ++l)
+#pragma unroll
+            for (int j = 0; j < P; ++j) acc[l][j] = w[l] * Y[j];
+    };
+    S raw[P][P + 1];                                       // rows 1 .. P of the next cell, in flight
+    {
+        S v0[P + 1];
+        load_row(v0, zc0 * P);
+#pragma unroll
+        for (int r = 0; r < P; ++r) load_row(raw[r], zc0 * P + 1 + r);
+        interp_y(v0);
+        first_row();
+    }
+    auto cell_step = [&](auto last, int c) {
+#pragma unroll
+        for (int r = 0; r < P; ++r) {
+            S w[P];
+            zweights(r + 1, w);
+            interp_y(raw[r]);
+            if constexpr (!decltype(last)::value) load_row(raw[r], (c + 1) * P + 1 + r);
+#pragma unroll
+            for (int l = 0; l < P; ++l)
+#pragma unroll
+                for (int j = 0; j < P; ++j) acc[l][j] = fma(w[l], Y[j], acc[l][j]);
+        }
+#pragma unroll
+        for (int l = 0; l < P; ++l)
+#pragma unroll
+            for (int j = 0; j < P; ++j) buf[l * P + j][tid] = acc[l][j];
+        if constexpr (!decltype(last)::value) first_row();
+        __syncthreads();
+        int z = wrapi((c - omz - 1) * P + lsz, Nz);
+#pragma unroll
+        for (int l = 0; l < P; ++l) {
+            const GlobalRow<S> d = plane_row(dst, static_cast<int64_t>(z) * NP);
+#pragma unroll
+            for (int j = 0; j < P; ++j) {
+                const S *b = buf[l * P + j];
+                S v = 0;
+#pragma unroll
+                for (int r = 0; r < P; ++r) v = fma(xw[r], b[b0 + r], v);
+                v = fma(xw[P], b[bl], v);
+                store_at<NTH, S>(d, oo[j], v);
+            }
+            __builtin_amdgcn_sched_barrier(0);             // one output row's LDS reads at a time (registers)
+            z = z + 1 == Nz ? 0 : z + 1;
+        }
+    };
+    // the first cell outside the loop: entered from it, the loop's waits for a
+    // row need not assume that no stores are in flight after the row's loads
+    int c = zc0;
+    if constexpr (z_max_cells<P>() > 1) {
+        if (c < zc1 - 1) {
+            cell_step(std::false_type(), c);
+            __syncthreads();
+            for (++c; c < zc1 - 1; ++c) {
+                cell_step(std::false_type(), c);
+                __syncthreads();
+            }
+        }
+    }
+    cell_step(std::true_type(), c);
+}
+
+template <typename S, int P>
+static hipError_t launch_z(const Geometry &g, const CellTables<S> &t, const S *in, S *out, hipStream_t st)
+{
+    ZLayout lay = z_layout(g, 1);
+    unsigned nb;
+    if (!z_split(g, z_max_cells<P>(), lay, nb)) return hipErrorInvalidValue;
+    if (use_nontemporal(90 * g.nodes * static_cast<int64_t>(sizeof(S))))
+        hipLaunchKernelGGL((k_stream_z<S, P, true>), dim3(nb, 90), dim3(lay.nt), 0, st, g, t, in, out, lay);
+    else
+        hipLaunchKernelGGL((k_stream_z<S, P, false>), dim3(nb, 90), dim3(lay.nt), 0, st, g, t, in, out, lay);
+    return hipGetLastError();
+}
+
+namespace {
 
 constexpr int64_t ZCHUNK_TARGET_BLOCKS = 2048;
 constexpr int ZCHUNK_MIN_CELLS = 4;
@@ -62,23 +367,6 @@ int z_chunks(const Geometry &g, int ntiles, int max_cells)
     return (g.nel[2] + zcells - 1) / zcells;
 }
 
-// V = values per window load (1, or 16 bytes when every window row starts
-// on a 16-byte boundary: p * sizeof(S) and N_x * sizeof(S) multiples of 16)
-template <int P, int V = 1, int YN_ = 8>
-struct ZTile {
-    static constexpr int ORDER = P;
-    static constexpr int XN = 32, YN = YN_;                   // target tile extent in nodes (long x rows)
-    static constexpr int TXC = XN / P > 0 ? XN / P : 1;       // cells per tile along x and y
-    static constexpr int TYC = YN / P > 0 ? YN / P : 1;
-    static constexpr int TX = TXC * P, TY = TYC * P;          // nodes per tile
-    static constexpr int WX = TX + P + 1, WY = TY + P + 1;    // source window
-    static constexpr int WXC = (WX + V - 1) / V, WXP = WXC * V;   // loads per window row, padded row
-    static constexpr int NT = (TX * TY + 63) / 64 * 64;       // one thread per output column
-    static constexpr int LK = (WXC * WY + NT - 1) / NT;       // window loads per thread and row
-    static constexpr int NG = TXC + 1;                        // source cells of an x window row
-    static constexpr int BS = TX % 2 ? TX : TX + 1;           // odd row stride of the x-pass output (LDS banks)
-};
-
 template <typename S, int V>
 struct VecOf {
     typedef S T __attribute__((ext_vector_type(V)));
@@ -95,235 +383,7 @@ __device__ __forceinline__ auto vcomp(const VT &v, int c)
     else return v[c];
 }
 
-template <typename S, class Z>
-constexpr size_t z_lds_bytes()
-{
-    return static_cast<size_t>(Z::ORDER + 1) * (static_cast<size_t>(Z::WXP) * Z::WY + Z::WY * Z::BS) * sizeof(S);
-}
-
 }  // namespace
-
-// Rows of the x-y tile: 16 (32 x 16 nodes, 512 threads) on grids whose state
-// exceeds the Infinity Cache, where the y halo rows that a tile loads per
-// output column matter (measured at 256^3 nodes: 5 % faster in FP32, 2 % in
-// FP64), if its LDS stays within 64 KB; 8 otherwise (at 64^3 nodes the larger
-// tile has too few blocks and is 8 % slower).
-template <typename S, int P, int V, bool BIG>
-constexpr int z_tile_rows()
-{
-    return BIG && z_lds_bytes<S, ZTile<P, V, 16>>() <= 64 * 1024 ? 16 : 8;
-}
-
-template <typename S, int P, int V, bool NTH>
-using ZTileOf = ZTile<P, V, z_tile_rows<S, P, V, NTH>()>;
-
-// NTH: non-temporal output stores and the larger tile (states larger than
-// the Infinity Cache)
-template <typename S, int P, int V, bool NTH>
-__global__ void __launch_bounds__((ZTileOf<S, P, V, NTH>::NT)) k_stream_z(Geometry g, CellTables<S> tab,
-                                                                        const S *__restrict__ in,
-                                                                        S *__restrict__ out, int ntile_x,
-                                                                        int ntiles, int zcells, int nchunk)
-{
-    using Z = ZTileOf<S, P, V, NTH>;
-    using VT = typename VecOf<S, V>::T;
-    constexpr int TX = Z::TX, TY = Z::TY, WX = Z::WXP, WY = Z::WY, NT = Z::NT, LK = Z::LK;
-    constexpr int WP = WX * WY;
-    constexpr int NLD = Z::WXC * WY;                       // window loads per row
-    // one batch of source rows (P + 1 for the first cell, P afterwards); single
-    // buffers suffice with two barriers per batch: a thread stores the next
-    // batch only after the barrier that follows every thread's x-pass, and
-    // overwrites bx only after the barrier that follows every thread's y-pass
-    __shared__ __align__(16) S pl[P + 1][WP];
-    constexpr int BS = Z::BS;
-    __shared__ S bx[P + 1][WY * BS];
-
-    const int tid = threadIdx.x;
-    const int L = __builtin_amdgcn_readfirstlane(xcd_linear(blockIdx.x, gridDim.x));
-    const int q = L / (ntiles * nchunk);
-    const int rem = L - q * ntiles * nchunk;
-    const int chunk = rem / ntiles, tile = rem - chunk * ntiles;
-    const int i = q >> 1, pop = q & 1;
-    const int X0 = (tile % ntile_x) * TX, Y0 = (tile / ntile_x) * TY;
-    const int Nx = g.N[0], Ny = g.N[1], Nz = g.N[2];
-    const int64_t N = g.nodes, NP = static_cast<int64_t>(Nx) * Ny;
-    const int omx = tab.omin[i * 3 + 0], omy = tab.omin[i * 3 + 1], omz = tab.omin[i * 3 + 2];
-    const int lsx = tab.lstar[i * 3 + 0], lsy = tab.lstar[i * 3 + 1], lsz = tab.lstar[i * 3 + 2];
-    const S *Wx = tab.w + (i * 3 + 0) * P * (P + 1);
-    const S *Wy = tab.w + (i * 3 + 1) * P * (P + 1);
-    const S *Wz = tab.w + (i * 3 + 2) * P * (P + 1);
-    const S *__restrict__ src = in + static_cast<int64_t>(pop * 45 + i) * N;
-    S *__restrict__ dst = out + static_cast<int64_t>(pop * 45 + i) * N;
-
-    // window loads of this thread (V values each): x-y offsets inside a z-plane;
-    // load e covers window row e / WXC, columns V * (e % WXC) ...
-    int loff[LK];
-#pragma unroll
-    for (int k = 0; k < LK; ++k) {
-        int e = tid + k * NT;
-        e = e < NLD ? e : NLD - 1;                         // surplus lanes repeat the last load
-        const int wx = (e % Z::WXC) * V, wy = e / Z::WXC;
-        loff[k] = wrapi(Y0 + omy * P + wy, Ny) * Nx + wrapi(X0 + omx * P + wx, Nx);
-    }
-    // x-pass by source cell: window cell c = g + 1 (g = -1 .. TXC - 1) feeds the
-    // outputs g*P + lsx + j, j = 0 .. P-1 (those inside the tile), output j
-    // with weight row (lsx + j) mod P, the same for every thread
-    S xw[P][P + 1];
-#pragma unroll
-    for (int j = 0; j < P; ++j)
-#pragma unroll
-        for (int r = 0; r <= P; ++r) xw[j][r] = Wx[((lsx + j) % P) * (P + 1) + r];
-    // y-pass task and output of this thread: node (X0 + tx, Y0 + ty)
-    const int tx = tid % TX, ty = tid / TX;
-    const bool own = tid < TX * TY && X0 + tx < Nx && Y0 + ty < Ny;
-    const int ly = ty % P;
-    const int ysrc = (ty / P + (ly >= lsy ? 1 : 0)) * P * Z::BS + (tid < TX * TY ? tx : 0);
-    S yw[P + 1];
-#pragma unroll
-    for (int r = 0; r <= P; ++r) yw[r] = Wy[ly * (P + 1) + r];
-    const int64_t oxy = static_cast<int64_t>(Y0 + ty) * Nx + (X0 + tx);
-    S wz[P][P + 1];                                        // uniform z weights of this velocity
-#pragma unroll
-    for (int l = 0; l < P; ++l)
-#pragma unroll
-        for (int r = 0; r <= P; ++r) wz[l][r] = Wz[l * (P + 1) + r];
-
-    // this block's output cells [ez0, ez1) along z; source rows in march
-    // order: z = (ez0 + omz) * P + k (mod Nz), k = 0 .. P + (ez1 - ez0) * P
-    const int ez0 = chunk * zcells, ez1 = min(g.nel[2], ez0 + zcells);
-    // row k < P + 1 + (ez1 - ez0) P <= Nz + P + 1 and zb < Nz, so two
-    // conditional subtractions wrap zb + k (no integer division per row)
-    const int zb = wrapi((ez0 + omz) * P, Nz);
-    // two register buffers of source rows: the rows of the cell after next are
-    // in flight while a cell is processed
-    VT rawA[P + 1][LK], rawB[P][LK];
-    auto load_rows = [&](auto &raw, int k0, int nr) {
-#pragma unroll
-        for (int r = 0; r <= P; ++r) {
-            if (r < nr && r < static_cast<int>(sizeof(raw) / sizeof(raw[0]))) {
-                int z = zb + k0 + r;
-                z -= z >= Nz ? Nz : 0;
-                z -= z >= Nz ? Nz : 0;
-                const int64_t zo = static_cast<int64_t>(z) * NP;
-#pragma unroll
-                for (int j = 0; j < LK; ++j) raw[r][j] = *reinterpret_cast<const VT *>(src + zo + loff[j]);
-            }
-        }
-    };
-    // a batch of NR rows: registers -> LDS, the same registers reloaded with
-    // the rows two batches ahead, x-pass, y-pass
-    auto batch = [&](auto nr_c, auto &raw, int next_k0, int next_nr, S *res) {
-        constexpr int NR = decltype(nr_c)::value;
-#pragma unroll
-        for (int r = 0; r < NR; ++r)
-#pragma unroll
-            for (int j = 0; j < LK; ++j)
-                if (tid + j * NT < NLD) *reinterpret_cast<VT *>(&pl[r][V * (tid + j * NT)]) = raw[r][j];
-        if (next_nr > 0) load_rows(raw, next_k0, next_nr);
-        __syncthreads();
-        constexpr int XT = NR * WY * Z::NG;                   // (row, window row, source cell) tasks
-#pragma unroll
-        for (int k = 0; k < (XT + NT - 1) / NT; ++k) {
-            const int e = tid + k * NT;
-            if (e < XT) {
-                const int r = e / (WY * Z::NG), rem = e - r * (WY * Z::NG);
-                const int g = rem / WY - 1, wy = rem - (g + 1) * WY;   // neighbouring lanes: neighbouring rows
-                const S *c = &pl[r][wy * WX + (g + 1) * P];
-                S v[P + 1];
-#pragma unroll
-                for (int m = 0; m <= P; ++m) v[m] = c[m];
-                S *o = &bx[r][wy * BS];
-#pragma unroll
-                for (int j = 0; j < P; ++j) {
-                    const int pos = g * P + lsx + j;
-                    if (pos >= 0 && pos < TX) {
-                        S acc = 0;
-#pragma unroll
-                        for (int m = 0; m <= P; ++m) acc = fma(xw[j][m], v[m], acc);
-                        o[pos] = acc;
-                    }
-                }
-            }
-        }
-        __syncthreads();
-#pragma unroll
-        for (int r = 0; r < NR; ++r) {
-            S acc = 0;
-#pragma unroll
-            for (int m = 0; m <= P; ++m) acc = fma(yw[m], bx[r][ysrc + m * BS], acc);
-            res[r] = acc;
-        }
-    };
-    // P outputs of cell ez along z from the rows in a, then slide by one cell
-    S a[2 * P + 1];
-    auto emit = [&](int ez) {
-        if (own) {
-#pragma unroll
-            for (int l = 0; l < P; ++l) {
-                const bool hi = l >= lsz;
-                S acc = 0;
-#pragma unroll
-                for (int r = 0; r <= P; ++r) acc = fma(wz[l][r], hi ? a[P + r] : a[r], acc);
-                store_hint<NTH>(&dst[static_cast<int64_t>(ez * P + l) * NP + oxy], acc);
-            }
-        }
-#pragma unroll
-        for (int r = 0; r <= P; ++r) a[r] = a[r + P];
-    };
-
-    // rows 0 .. P (first source cell) in rawA, then the rows of cell e
-    // (P + 1 + e*P .. 2P + e*P) alternate between rawB (even e) and rawA (odd e)
-    const int nel = ez1 - ez0;
-    auto rows_of = [&](int e) { return e < nel ? P : 0; };
-    load_rows(rawA, 0, P + 1);
-    load_rows(rawB, P + 1, rows_of(0));
-    batch(std::integral_constant<int, P + 1>(), rawA, 2 * P + 1, rows_of(1), a);
-    for (int e = 0; e < nel; e += 2) {
-        batch(std::integral_constant<int, P>(), rawB, P + 1 + (e + 2) * P, rows_of(e + 2), a + P + 1);
-        emit(ez0 + e);
-        if (e + 1 < nel) {
-            batch(std::integral_constant<int, P>(), rawA, P + 1 + (e + 3) * P, rows_of(e + 3), a + P + 1);
-            emit(ez0 + e + 1);
-        }
-    }
-}
-
-template <typename S, int P, int V, bool NTH>
-static hipError_t launch_zvn(const Geometry &g, const CellTables<S> &t, const S *in, S *out, hipStream_t st)
-{
-    using Z = ZTileOf<S, P, V, NTH>;
-    const int ntx = (g.N[0] + Z::TX - 1) / Z::TX, nty = (g.N[1] + Z::TY - 1) / Z::TY;
-    const int ntiles = ntx * nty;
-    const int nchunk = z_chunks(g, ntiles, Z::YN == 16 ? ZCHUNK_MAX_CELLS_LARGE
-                                                     : ZCHUNK_MAX_CELL_BYTES / static_cast<int>(sizeof(S)));
-    const int zcells = (g.nel[2] + nchunk - 1) / nchunk;
-    const int64_t nb = static_cast<int64_t>(ntiles) * 90 * nchunk;
-    if (nb > (int64_t(1) << 31) - 1) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((k_stream_z<S, P, V, NTH>), dim3(static_cast<unsigned>(nb)), dim3(Z::NT), 0, st, g, t, in, out,
-                       ntx, ntiles, zcells, nchunk);
-    return hipGetLastError();
-}
-
-template <typename S, int P, int V>
-static hipError_t launch_zv(const Geometry &g, const CellTables<S> &t, const S *in, S *out, hipStream_t st)
-{
-    if (use_nontemporal(90 * g.nodes * static_cast<int64_t>(sizeof(S))))
-        return launch_zvn<S, P, V, true>(g, t, in, out, st);
-    return launch_zvn<S, P, V, false>(g, t, in, out, st);
-}
-
-// 16-byte window loads when every window row starts on a 16-byte boundary
-template <typename S, int P>
-static hipError_t launch_z(const Geometry &g, const CellTables<S> &t, const S *in, S *out, hipStream_t st)
-{
-    constexpr int V = 16 / sizeof(S);
-    const bool aligned = (P * sizeof(S)) % 16 == 0 && (g.N[0] * sizeof(S)) % 16 == 0 &&
-                         reinterpret_cast<uintptr_t>(in) % 16 == 0;
-    if constexpr ((P * sizeof(S)) % 16 == 0 && ZTile<P, V>::TX % V == 0) {
-        if (aligned) return launch_zv<S, P, V>(g, t, in, out, st);
-    }
-    return launch_zv<S, P, 1>(g, t, in, out, st);
-}
 
 // ---------------------------------------------------------------------------
 // Transposed streaming S^T (the adjoint of Eqs. (8)-(9)), same z-march.

@@ -101,3 +101,33 @@ def test_distorted_streaming_by_cell(oracle, precision, n_el, p, dt):
     a, b = (f * y[0]).sum() + (g * y[1]).sum(), (x[0] * st[0]).sum() + (x[1] * st[1]).sum()
     scale = np.abs(f * y[0]).sum() + np.abs(g * y[1]).sum()
     assert abs(a - b) <= tol * scale
+
+
+# whole rows up to 256 nodes and split ones beyond (a ragged last tile, two
+# tiles of one cell row), one-cell axes, ragged blocks along y, blocks of one
+# and of several cells along z, shifts of several cells
+STREAM_FORMS = [((1, 1, 1), 1, 0.9), ((256, 2, 3), 1, 0.02), ((257, 1, 2), 1, 0.05), ((3, 300, 2), 1, 0.3),
+                ((5, 4, 70), 1, 0.1), ((129, 3, 5), 2, 0.02), ((2, 2, 9), 2, 0.8), ((43, 7, 3), 3, 0.05),
+                ((86, 2, 1), 3, 0.03), ((64, 1, 2), 4, 0.01), ((65, 3, 6), 4, 0.02), ((1, 1, 9), 4, 0.7),
+                ((51, 6, 2), 5, 0.03), ((52, 1, 5), 5, 0.02), ((43, 2, 1), 6, 0.03), ((2, 3, 9), 6, 1.1)]
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("n_el,p,dt", STREAM_FORMS)
+def test_streaming_by_source_cell(oracle, precision, n_el, p, dt):
+    """Equal-cell streaming against the oracle (1e-12, FP32 1e-5: the
+    repository's bars), from and into buffers at any element offset."""
+    ctx, cfg = make_pair(oracle, n_el, p, dt, 0.01, precision=precision)
+    rng = np.random.default_rng(11)
+    x = rng.normal(size=(2, Q, ctx.nodes)).astype(np.float32).astype(np.float64)
+    xd = to_dev(ctx, x[0], x[1])
+    print("streaming form", precision, n_el, p, flush=True)
+    out = ctx.stream(xd)
+    flat = torch.zeros(2 * xd.numel() + 3, dtype=ctx.dtype, device=ctx.device)
+    a, b = flat[1:1 + xd.numel()].view(xd.shape), flat[-xd.numel() - 1:-1].view(xd.shape)
+    a.copy_(xd)
+    assert torch.equal(ctx.stream(a, out=b), out)
+    F, G = to_np(out)
+    f, g = oracle.stream(cfg, x[0], x[1])
+    tol = 1e-5 if precision else 1e-12
+    assert rel_err(F, f) < tol and rel_err(G, g) < tol
