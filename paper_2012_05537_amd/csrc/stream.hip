@@ -68,8 +68,9 @@ ZLayout z_layout(const Geometry &g, int halo)
 }
 
 // Cells along z per block: at most max_cells, fewer while the grid has fewer
-// than Z_TARGET_BLOCKS blocks of 256 threads.
-constexpr int Z_TARGET_BLOCKS = 1024;
+// than Z_TARGET_BLOCKS blocks of 256 threads, five per CU (transposed kernel,
+// 64^3 nodes, FP64: 86, 85 and 92 us with 2, 4 and 8 blocks per CU).
+constexpr int Z_TARGET_BLOCKS = 1280;
 
 // nblocks: blocks per plane (the grid is nblocks x 90: with one dimension its
 // threads would pass 2^32 on the largest grids)
@@ -337,309 +338,242 @@ static hipError_t launch_z(const Geometry &g, const CellTables<S> &t, const S *i
     return hipGetLastError();
 }
 
-namespace {
-
-constexpr int64_t ZCHUNK_TARGET_BLOCKS = 2048;
-constexpr int ZCHUNK_MIN_CELLS = 4;
-constexpr int ZCHUNK_MAX_CELL_BYTES = 64;   // cells per chunk times the element size (8 x 32-node tiles)
-constexpr int ZCHUNK_MAX_CELLS_LARGE = 32;  // cells per chunk with the 32 x 16-node tiles of large grids
-
-// Number of z-chunks of a march over ntiles x-y tiles and 90 planes.  Small
-// grids split the march until the grid has a few blocks per CU slot.  Every
-// grid caps a chunk at max_cells cells: blocks of one plane start in
-// (chunk, tile) order, so neighbouring tiles march through the same z-rows at
-// nearly the same time and more of the x-y halo rows that one tile loads are
-// still in L2 when its neighbours read them; blocks that marched the whole
-// axis drift apart on large grids.  Each chunk re-reads P + 1 rows.
-// Measured at 256^3 nodes (FP64) with 32 x 8-node tiles: reads of 1.87x the
-// algorithmic bytes with whole-axis marches, 1.31x with 8-cell chunks (1.59x
-// and 1.10x at 128^3), hence ZCHUNK_MAX_CELL_BYTES / elem cells (8 in FP64,
-// 16 in FP32).  The 32 x 16-node tiles of large grids have half the x-y halo
-// per output, and there 32-cell chunks are 2-4 % faster than 8 or 16 cells.
-int z_chunks(const Geometry &g, int ntiles, int max_cells)
-{
-    int nchunk = 1;
-    while (nchunk < g.nel[2] && static_cast<int64_t>(ntiles) * 90 * nchunk < ZCHUNK_TARGET_BLOCKS &&
-           g.nel[2] / (2 * nchunk) >= ZCHUNK_MIN_CELLS)
-        nchunk *= 2;
-    nchunk = std::max(nchunk, (g.nel[2] + max_cells - 1) / max_cells);
-    const int zcells = (g.nel[2] + nchunk - 1) / nchunk;
-    return (g.nel[2] + zcells - 1) / zcells;
-}
-
-template <typename S, int V>
-struct VecOf {
-    typedef S T __attribute__((ext_vector_type(V)));
-};
-template <typename S>
-struct VecOf<S, 1> {
-    typedef S T;
-};
-
-template <typename VT>
-__device__ __forceinline__ auto vcomp(const VT &v, int c)
-{
-    if constexpr (std::is_arithmetic_v<VT>) return v;
-    else return v[c];
-}
-
-}  // namespace
-
 // ---------------------------------------------------------------------------
-// Transposed streaming S^T (the adjoint of Eqs. (8)-(9)), same z-march.
+// Transposed streaming S^T (the adjoint of Eqs. (8)-(9)), by output cell.
 //
-// Along an axis the forward nodes that read source cell c form a group: the
-// nodes (c - omin - 1)*P + lstar + j, j = 0 .. P-1, read it with weight row
-// (lstar + j) mod P.  Transposing, node k of cell c receives
+// Transposing the group rule above, node k of cell c receives
 //   T[c*P + k] = sum_j W[(lstar + j) mod P][k] lam[group(c)_j]
 // and node 0 also, as point P of cell c - 1,
-//   + sum_j W[(lstar + j) mod P][P] lam[group(c - 1)_j].
-// So each output cell gathers two consecutive groups (2P inputs, starting at
+//   + sum_j W[(lstar + j) mod P][P] lam[group(c - 1)_j],
+// so a cell gathers two consecutive groups (2P inputs, starting at
 // (c - omin - 2)*P + lstar) with the forward weights; this holds for any
-// number of cells, wrap-around included.  The kernel is the forward one with
-// that gather along x, y (LDS) and z (a register window of 2P rows sliding by
-// one cell).
+// number of cells, wrap-around included.  A lane takes one input column of a
+// cell along y, loads both groups of each z-row, gathers along y and z in
+// registers and x through LDS, like the forward kernel.  Along z it marches:
+// what a group adds to the next cell's node 0 stays in registers, and only a
+// block's first cell reads its preceding group again.
 // ---------------------------------------------------------------------------
-template <int P, int V = 1, int YN_ = 8>
-struct ZTileT {
-    static constexpr int ORDER = P;
-    static constexpr int XN = 32, YN = YN_;
-    static constexpr int TXC = XN / P > 0 ? XN / P : 1, TYC = YN / P > 0 ? YN / P : 1;
-    static constexpr int TX = TXC * P, TY = TYC * P;
-    static constexpr int WXC = (TX + P + V - 1 + V - 1) / V;  // loads per window row (V-aligned start)
-    static constexpr int WX = WXC * V, WY = TY + P;
-    static constexpr int NT = (TX * TY + 63) / 64 * 64;
-    static constexpr int LK = (WXC * WY + NT - 1) / NT;
-    static constexpr int BS = TX % 2 ? TX : TX + 1;
-};
 
-// Tile rows of the transposed march, chosen as in the forward one: 16 on
-// grids larger than the Infinity Cache if the LDS stays within 64 KB
-template <typename S, class Z>
-constexpr size_t zt_lds_bytes()
+// Cells along z per block: the P rows read again per block against the
+// parallelism (P = 4: FP64, 256^3 nodes, 5.83, 4.98, 4.58, 4.41 and 4.37 ms with 1, 2, 4,
+// 8 and 32 cells, 128^3 615 us with 4 and 8; FP32, four rows in flight, 128^3 290 us
+// with 4 and 300 with 8; P = 1, 100 x 100 x 30: 93 us with 4, 41 us with 30)
+template <typename S, int P>
+constexpr int zt_max_cells()
 {
-    constexpr int WXO = Z::WX % 2 ? Z::WX : Z::WX + 1;
-    return static_cast<size_t>(Z::ORDER) * (static_cast<size_t>(WXO) * Z::WY + Z::WY * Z::BS) * sizeof(S);
+    return P == 1 ? 32 : sizeof(S) == 8 ? 8 : 4;
 }
 
-template <typename S, int P, int V, bool BIG>
-constexpr int zt_tile_rows()
+// Rows in flight ahead of the one being processed (divides P), as registers
+// allow: P = 4 in FP32 at 128^3 nodes 301, 299 and 290 us with 1, 2 and 4 rows,
+// in FP64 (four rows spill) 611, 627 and 873 us; P = 6 in FP64, 96^3 nodes, 368 and
+// 346 us with 1 and 2.
+template <typename S, int P>
+constexpr int zt_depth()
 {
-    return BIG && zt_lds_bytes<S, ZTileT<P, V, 16>>() <= 64 * 1024 ? 16 : 8;
+    return P <= 3 || (P == 4 && sizeof(S) == 4) ? P : P == 6 ? 2 : 1;
 }
 
-template <typename S, int P, int V, bool NTH>
-using ZTileTOf = ZTileT<P, V, zt_tile_rows<S, P, V, NTH>()>;
-
-// NTH: non-temporal output stores and the larger tile (states larger than
-// the Infinity Cache)
-template <typename S, int P, int V, bool NTH>
-__global__ void __launch_bounds__((ZTileTOf<S, P, V, NTH>::NT))
-    k_stream_zt(Geometry g, CellTables<S> tab, const S *__restrict__ in, S *__restrict__ out, int ntile_x,
-                int ntiles, int zcells, int nchunk)
+template <typename S, int P>
+constexpr int zt_min_waves()
 {
-    using Z = ZTileTOf<S, P, V, NTH>;
-    using VT = typename VecOf<S, V>::T;
-    constexpr int TX = Z::TX, TY = Z::TY, WY = Z::WY, NT = Z::NT, LK = Z::LK, BS = Z::BS;
-    constexpr int WX = Z::WX % 2 ? Z::WX : Z::WX + 1;      // odd LDS row stride
-    constexpr int NLD = Z::WXC * WY;
-    __shared__ __align__(16) S pl[P][WX * WY];
-    __shared__ S bx[P][WY * BS];
+    return sizeof(S) == 4 ? (P <= 4 ? 5 : P == 5 ? 4 : 3) : (P <= 3 ? 5 : P == 4 ? 4 : P == 5 ? 3 : 2);
+}
 
+// Bound by HBM, behind it the reads of both groups from L1 and L2 (each value
+// 2.2 to 2.5 times).  At 128^3 nodes, P = 4: 290 us in FP32 and 611 us in FP64 (5.2 and
+// 4.9 TB/s), 256^3 2.3 / 4.5 ms, 24^3 (P = 3) 8.0 us, 96^3 at P = 6 346 us; the
+// march by output tiles before it, with the windows in LDS, took 362 / 646 us,
+// 2.83 / 5.17 ms, 11.4 us and 632 us.  Skipping the second group's LDS reads on lanes
+// that are no node 0 (a branch) is 2 % slower to 2 % faster.
+// NTH: non-temporal output stores (states larger than the Infinity Cache)
+template <typename S, int P, bool NTH>
+__global__ void __launch_bounds__(ZNT, (zt_min_waves<S, P>())) k_stream_zt(Geometry g, CellTables<S> tab,
+                                                                          const S *__restrict__ in,
+                                                                          S *__restrict__ out, ZLayout lay)
+{
+    constexpr int D = zt_depth<S, P>();
+    __shared__ S buf[P * P][ZNT];                          // y-z-gathered values of an output cell, per lane
     const int tid = threadIdx.x;
-    const int L = __builtin_amdgcn_readfirstlane(xcd_linear(blockIdx.x, gridDim.x));
-    const int q = L / (ntiles * nchunk);
-    const int rem = L - q * ntiles * nchunk;
+    const int ntiles = lay.ntx * lay.nty;
+    const int L = __builtin_amdgcn_readfirstlane(xcd_linear(static_cast<int>(blockIdx.y * gridDim.x + blockIdx.x),
+                                                                static_cast<int>(gridDim.x * gridDim.y)));
+    const int q = L / (ntiles * lay.nchunk);
+    const int rem = L - q * ntiles * lay.nchunk;
     const int chunk = rem / ntiles, tile = rem - chunk * ntiles;
+    const int ty = tile / lay.ntx, tx = tile - ty * lay.ntx;
     const int i = q >> 1, pop = q & 1;
-    const int X0 = (tile % ntile_x) * TX, Y0 = (tile / ntile_x) * TY;
     const int Nx = g.N[0], Ny = g.N[1], Nz = g.N[2];
     const int64_t N = g.nodes, NP = static_cast<int64_t>(Nx) * Ny;
     const int omx = tab.omin[i * 3 + 0], omy = tab.omin[i * 3 + 1], omz = tab.omin[i * 3 + 2];
     const int lsx = tab.lstar[i * 3 + 0], lsy = tab.lstar[i * 3 + 1], lsz = tab.lstar[i * 3 + 2];
+    using CS = const __attribute__((address_space(4))) S;
     const S *Wx = tab.w + (i * 3 + 0) * P * (P + 1);
-    const S *Wy = tab.w + (i * 3 + 1) * P * (P + 1);
-    const S *Wz = tab.w + (i * 3 + 2) * P * (P + 1);
-    const S *__restrict__ src = in + static_cast<int64_t>(pop * 45 + i) * N;
-    S *__restrict__ dst = out + static_cast<int64_t>(pop * 45 + i) * N;
+    CS *Wy = (CS *)(tab.w + (i * 3 + 1) * P * (P + 1));
+    CS *Wz = (CS *)(tab.w + (i * 3 + 2) * P * (P + 1));
+    S *src = const_cast<S *>(in) + static_cast<int64_t>(pop * 45 + i) * N;
+    S *dst = out + static_cast<int64_t>(pop * 45 + i) * N;
 
-    // input window: x from X0 + (-2 - omx)*P + lsx (rounded down to V: shift sx), y from Y0 + (-2 - omy)*P + lsy
-    const int offx = (-2 - omx) * P + lsx;
-    const int offxa = offx - ((offx % V) + V) % V, sx = offx - offxa;
-    const int offy = (-2 - omy) * P + lsy;
-    int loff[LK], soff[LK];                                // HBM and LDS offsets of this thread's loads
+    // this lane's input column and output cell along y (surplus lanes repeat
+    // lane 0, as in the forward march); columns are counted in group order, so
+    // that column e P + j of a row is input j of the group of cell e
+    const int cx0 = tx * lay.txc, cy0 = ty * lay.tyc;
+    int cyl = static_cast<int>((static_cast<float>(tid) + 0.5f) * lay.rcx), xl = tid - cyl * lay.cx;
+    const bool whole = lay.ntx == 1;
+    const int ncx = min(lay.txc, g.nel[0] - cx0);
+    const bool used = cyl < min(lay.tyc, g.nel[1] - cy0) && (whole || xl < (ncx + 1) * P);
+    cyl = used ? cyl : 0;
+    xl = used ? xl : 0;
+    int xi = wrapi((cx0 - omx - (whole ? 1 : 2)) * P + lsx, Nx) + xl;   // a split row starts one group early
+    xi -= xi >= Nx ? Nx : 0;
+    // rows 0 .. 2P-1: the groups of cells cy - 1 and cy along y
+    uint32_t io[2 * P];
+    {
+        int y0 = wrapi((cy0 - omy - 2) * P + lsy, Ny) + cyl * P;       // below 2 N_y
+        y0 -= y0 >= Ny ? Ny : 0;
 #pragma unroll
-    for (int k = 0; k < LK; ++k) {
-        int e = tid + k * NT;
-        e = e < NLD ? e : NLD - 1;
-        const int wx = (e % Z::WXC) * V, wy = e / Z::WXC;
-        loff[k] = wrapi(Y0 + offy + wy, Ny) * Nx + wrapi(X0 + offxa + wx, Nx);
-        soff[k] = wy * WX + wx;
+        for (int r = 0; r < 2 * P; ++r) {
+            int y = y0 + r;
+            y -= y >= Ny ? Ny : 0;
+            y -= y >= Ny ? Ny : 0;                         // one cell along y: N_y = P
+            io[r] = plane_offset<S>(y * Nx + xi);
+        }
     }
-    // x and z weights, the same for every thread: w*[j][k] = W[(ls + j) mod P][k]
-    S wxu[P][P + 1], wzu[P][P + 1];
+    const int xe = whole || xl >= P ? xl : xl + P;         // the output column, counted like the input columns
+    const int cell = xe / P, kx = xe - cell * P;
+    const int b0 = cyl * lay.cx + cell * P;
+    const int bp = cell == 0 ? cyl * lay.cx + Nx - P : b0 - P;         // cell 0: of a whole row only
+    const uint32_t oo = plane_offset<S>((cy0 + cyl) * P * Nx + (whole ? xe : cx0 * P + xe - P));
+    S xw[P];
+#pragma unroll
+    for (int j = 0; j < P; ++j) xw[j] = Wx[(lsx + j) % P * (P + 1) + kx];
+    auto xp = [&](int j) { return ((CS *)Wx)[(lsx + j) % P * (P + 1) + P]; };   // (uniform)
+    S wy[P][P + 1];
 #pragma unroll
     for (int j = 0; j < P; ++j)
 #pragma unroll
-        for (int k = 0; k <= P; ++k) {
-            wxu[j][k] = Wx[((lsx + j) % P) * (P + 1) + k];
-            wzu[j][k] = Wz[((lsz + j) % P) * (P + 1) + k];
+        for (int k = 0; k <= P; ++k) wy[j][k] = Wy[(lsy + j) % P * (P + 1) + k];
+
+    // input rows in march order from the group of cell zc0 - 1 on
+    const int zc0 = chunk * lay.zcells, zc1 = min(g.nel[2], zc0 + lay.zcells);
+    const int zb = wrapi((zc0 - omz - 2) * P + lsz, Nz);
+    S raw[D][2 * P];
+    auto load_row = [&](S (&v)[2 * P], int k) {            // k < N_z + P
+        int z = zb + k;
+        z -= z >= Nz ? Nz : 0;
+        z -= z >= Nz ? Nz : 0;
+        const GlobalRow<S> row = plane_row(src, static_cast<int64_t>(z) * NP);
+#pragma unroll
+        for (int r = 0; r < 2 * P; ++r) v[r] = load_at<S>(row, io[r]);
+    };
+    S Y[P], acc[P][P], carry[P];
+    auto gather_y = [&](const S (&v)[2 * P]) {
+#pragma unroll
+        for (int k = 0; k < P; ++k) {
+            Y[k] = wy[0][k] * v[P];
+#pragma unroll
+            for (int j = 1; j < P; ++j) Y[k] = fma(wy[j][k], v[P + j], Y[k]);
         }
-    // output node (X0 + tx, Y0 + ty): point ky of tile cell cy along y gathers
-    // window rows (cy + 1)*P + j with yw[j], and for ky = 0 rows cy*P + j with yp[j]
-    const int tx = tid % TX, ty = tid / TX;
-    const bool own = tid < TX * TY && X0 + tx < Nx && Y0 + ty < Ny;
-    const int cy = ty / P, ky = ty % P;
-    const int ybase = cy * P * BS + (tid < TX * TY ? tx : 0);
-    S yw[P], yp[P];
+#pragma unroll
+        for (int j = 0; j < P; ++j) Y[0] = fma(wy[j][P], v[j], Y[0]);
+    };
+    // weights of row j of a group for the points k of its cell
+    int wzo[P];
+#pragma unroll
+    for (int j = 0; j < P; ++j) wzo[j] = (lsz + j) % P * (P + 1);
+    auto zweights = [&](int j, S (&w)[P + 1]) {
+        if constexpr (P >= 4) asm volatile("" : "+s"(Wz));
+#pragma unroll
+        for (int k = 0; k <= P; ++k) w[k] = Wz[wzo[j] + k];
+    };
+
+#pragma unroll
+    for (int j = 0; j < D; ++j) load_row(raw[j], j);
 #pragma unroll
     for (int j = 0; j < P; ++j) {
-        yw[j] = Wy[((lsy + j) % P) * (P + 1) + ky];
-        yp[j] = ky == 0 ? Wy[((lsy + j) % P) * (P + 1) + P] : S(0);
+        S w[P + 1];
+        zweights(j, w);
+        gather_y(raw[j % D]);
+        load_row(raw[j % D], j + D);
+#pragma unroll
+        for (int m = 0; m < P; ++m) carry[m] = j == 0 ? w[P] * Y[m] : fma(w[P], Y[m], carry[m]);
+        __builtin_amdgcn_sched_barrier(0);
     }
-    const int64_t oxy = static_cast<int64_t>(Y0 + ty) * Nx + (X0 + tx);
-
-    // input rows in march order: z = (ez0 - omz - 2)*P + lsz + k (mod Nz), k = 0 .. P + nel*P - 1
-    const int ez0 = chunk * zcells, ez1 = min(g.nel[2], ez0 + zcells);
-    // row k < P + (ez1 - ez0) P <= Nz + P and zb < Nz: two conditional
-    // subtractions wrap zb + k
-    const int zb = wrapi((ez0 - omz - 2) * P + lsz, Nz);
-    VT rawA[P][LK], rawB[P][LK];
-    auto load_rows = [&](auto &raw, int k0, int nr) {
+    auto cell_step = [&](auto last, int c) {
+        constexpr bool LAST = decltype(last)::value;
+        const int k0 = (c - zc0 + 1) * P;
 #pragma unroll
-        for (int r = 0; r < P; ++r) {
-            if (r < nr) {
-                int z = zb + k0 + r;
-                z -= z >= Nz ? Nz : 0;
-                z -= z >= Nz ? Nz : 0;
-                const int64_t zo = static_cast<int64_t>(z) * NP;
+        for (int j = 0; j < P; ++j) {
+            S w[P + 1];
+            zweights(j, w);
+            gather_y(raw[j % D]);
+            if (!LAST || j + D < P) load_row(raw[j % D], k0 + j + D);
+            if (j == 0) {
 #pragma unroll
-                for (int j = 0; j < LK; ++j) raw[r][j] = *reinterpret_cast<const VT *>(src + zo + loff[j]);
-            }
-        }
-    };
-    // P rows: registers -> LDS, reload with the rows two batches ahead, x-gather, y-gather
-    auto batch = [&](auto &raw, int next_k0, int next_nr, S *res) {
+                for (int m = 0; m < P; ++m) {
+                    acc[0][m] = fma(w[0], Y[m], carry[m]);
 #pragma unroll
-        for (int r = 0; r < P; ++r)
-#pragma unroll
-            for (int j = 0; j < LK; ++j)
-                if (tid + j * NT < NLD) {
-#pragma unroll
-                    for (int c = 0; c < V; ++c) pl[r][soff[j] + c] = vcomp(raw[r][j], c);
+                    for (int k = 1; k < P; ++k) acc[k][m] = w[k] * Y[m];
+                    carry[m] = w[P] * Y[m];
                 }
-        if (next_nr > 0) load_rows(raw, next_k0, next_nr);
-        __syncthreads();
-        // x: task (row, window row, output cell cl) reads groups cl and cl + 1 of the row
-        constexpr int XT = P * WY * Z::TXC;
+            } else {
 #pragma unroll
-        for (int k = 0; k < (XT + NT - 1) / NT; ++k) {
-            const int e = tid + k * NT;
-            if (e < XT) {
-                const int r = e / (WY * Z::TXC), rem2 = e - r * (WY * Z::TXC);
-                const int cl = rem2 / WY, wy = rem2 - cl * WY;
-                const S *c = &pl[r][wy * WX + sx + cl * P];
-                S prev[P], cur[P];
+                for (int m = 0; m < P; ++m) {
 #pragma unroll
-                for (int j = 0; j < P; ++j) {
-                    prev[j] = c[j];
-                    cur[j] = c[P + j];
-                }
-                S *o = &bx[r][wy * BS + cl * P];
-#pragma unroll
-                for (int kk = 0; kk < P; ++kk) {
-                    S acc = 0;
-#pragma unroll
-                    for (int j = 0; j < P; ++j) acc = fma(wxu[j][kk], cur[j], acc);
-                    if (kk == 0) {
-#pragma unroll
-                        for (int j = 0; j < P; ++j) acc = fma(wxu[j][P], prev[j], acc);
-                    }
-                    o[kk] = acc;
+                    for (int k = 0; k < P; ++k) acc[k][m] = fma(w[k], Y[m], acc[k][m]);
+                    carry[m] = fma(w[P], Y[m], carry[m]);
                 }
             }
+            __builtin_amdgcn_sched_barrier(0);             // D rows of loads in flight and no more (registers)
         }
+#pragma unroll
+        for (int k = 0; k < P; ++k)
+#pragma unroll
+            for (int m = 0; m < P; ++m) buf[k * P + m][tid] = acc[k][m];
         __syncthreads();
 #pragma unroll
-        for (int r = 0; r < P; ++r) {
-            S acc = 0;
+        for (int k = 0; k < P; ++k) {
+            int t0 = b0, tp = bp;
+            asm volatile("" : "+v"(t0), "+v"(tp));         // LDS addresses formed here, not kept across the loop
 #pragma unroll
-            for (int j = 0; j < P; ++j) acc = fma(yw[j], bx[r][ybase + (P + j) * BS], acc);
+            for (int m = 0; m < P; ++m) {
+                const S *b = buf[k * P + m];
+                S v = xw[0] * b[t0], e = xp(0) * b[tp];
 #pragma unroll
-            for (int j = 0; j < P; ++j) acc = fma(yp[j], bx[r][ybase + j * BS], acc);
-            res[r] = acc;
-        }
-    };
-    S a[2 * P];
-    auto emit = [&](int ez) {
-        if (own) {
-#pragma unroll
-            for (int k = 0; k < P; ++k) {
-                S acc = 0;
-#pragma unroll
-                for (int j = 0; j < P; ++j) acc = fma(wzu[j][k], a[P + j], acc);
-                if (k == 0) {
-#pragma unroll
-                    for (int j = 0; j < P; ++j) acc = fma(wzu[j][P], a[j], acc);
+                for (int j = 1; j < P; ++j) {
+                    v = fma(xw[j], b[t0 + j], v);
+                    e = fma(xp(j), b[tp + j], e);
                 }
-                store_hint<NTH>(&dst[static_cast<int64_t>(ez * P + k) * NP + oxy], acc);
+                store_at<NTH, S>(plane_row(dst, static_cast<int64_t>(c * P + k) * NP + static_cast<int64_t>(m) * Nx), oo,
+                                 kx == 0 ? v + e : v);
             }
+            __builtin_amdgcn_sched_barrier(0);             // one output row's LDS reads at a time (registers)
         }
-#pragma unroll
-        for (int j = 0; j < P; ++j) a[j] = a[P + j];
     };
-
-    const int nel = ez1 - ez0;
-    auto rows_of = [&](int e) { return e < nel ? P : 0; };
-    load_rows(rawA, 0, P);
-    load_rows(rawB, P, rows_of(0));
-    batch(rawA, 2 * P, rows_of(1), a);
-    for (int e = 0; e < nel; e += 2) {
-        batch(rawB, P + (e + 2) * P, rows_of(e + 2), a + P);
-        emit(ez0 + e);
-        if (e + 1 < nel) {
-            batch(rawA, P + (e + 3) * P, rows_of(e + 3), a + P);
-            emit(ez0 + e + 1);
+    // the first cell outside the loop, as in the forward march
+    int c = zc0;
+    if (c < zc1 - 1) {
+        cell_step(std::false_type(), c);
+        __syncthreads();
+        for (++c; c < zc1 - 1; ++c) {
+            cell_step(std::false_type(), c);
+            __syncthreads();
         }
     }
+    cell_step(std::true_type(), c);
 }
 
-template <typename S, int P, int V, bool NTH>
-static hipError_t launch_ztvn(const Geometry &g, const CellTables<S> &t, const S *in, S *out, hipStream_t st)
-{
-    using Z = ZTileTOf<S, P, V, NTH>;
-    const int ntx = (g.N[0] + Z::TX - 1) / Z::TX, nty = (g.N[1] + Z::TY - 1) / Z::TY;
-    const int ntiles = ntx * nty;
-    // each chunk re-reads P rows
-    const int nchunk = z_chunks(g, ntiles, Z::YN == 16 ? ZCHUNK_MAX_CELLS_LARGE
-                                                     : ZCHUNK_MAX_CELL_BYTES / static_cast<int>(sizeof(S)));
-    const int zcells = (g.nel[2] + nchunk - 1) / nchunk;
-    const int64_t nb = static_cast<int64_t>(ntiles) * 90 * nchunk;
-    if (nb > (int64_t(1) << 31) - 1) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((k_stream_zt<S, P, V, NTH>), dim3(static_cast<unsigned>(nb)), dim3(Z::NT), 0, st, g, t, in,
-                       out, ntx, ntiles, zcells, nchunk);
-    return hipGetLastError();
-}
-
-template <typename S, int P, int V>
-static hipError_t launch_ztv(const Geometry &g, const CellTables<S> &t, const S *in, S *out, hipStream_t st)
-{
-    if (use_nontemporal(90 * g.nodes * static_cast<int64_t>(sizeof(S))))
-        return launch_ztvn<S, P, V, true>(g, t, in, out, st);
-    return launch_ztvn<S, P, V, false>(g, t, in, out, st);
-}
-
-// 16-byte window loads need V-aligned window starts: tiles and rows of a
-// multiple of V nodes and a 16-byte aligned buffer (the start is rounded down)
 template <typename S, int P>
 static hipError_t launch_zt(const Geometry &g, const CellTables<S> &t, const S *in, S *out, hipStream_t st)
 {
-    constexpr int V = 16 / sizeof(S);
-    if constexpr (ZTileT<P, V>::TX % V == 0) {
-        if ((g.N[0] * sizeof(S)) % 16 == 0 && reinterpret_cast<uintptr_t>(in) % 16 == 0)
-            return launch_ztv<S, P, V>(g, t, in, out, st);
-    }
-    return launch_ztv<S, P, 1>(g, t, in, out, st);
+    ZLayout lay = z_layout(g, P);
+    unsigned nb;
+    if (!z_split(g, zt_max_cells<S, P>(), lay, nb)) return hipErrorInvalidValue;
+    if (use_nontemporal(90 * g.nodes * static_cast<int64_t>(sizeof(S))))
+        hipLaunchKernelGGL((k_stream_zt<S, P, true>), dim3(nb, 90), dim3(lay.nt), 0, st, g, t, in, out, lay);
+    else
+        hipLaunchKernelGGL((k_stream_zt<S, P, false>), dim3(nb, 90), dim3(lay.nt), 0, st, g, t, in, out, lay);
+    return hipGetLastError();
 }
 
 template <typename S>

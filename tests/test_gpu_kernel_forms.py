@@ -131,3 +131,13 @@ def test_streaming_by_source_cell(oracle, precision, n_el, p, dt):
     f, g = oracle.stream(cfg, x[0], x[1])
     tol = 1e-5 if precision else 1e-12
     assert rel_err(F, f) < tol and rel_err(G, g) < tol
+    # and the transpose as the adjoint of it, per velocity
+    y = rng.normal(size=x.shape).astype(np.float32).astype(np.float64)
+    yd = to_dev(ctx, y[0], y[1])
+    st = ctx.stream(yd, transpose=True)
+    a.copy_(yd)
+    assert torch.equal(ctx.stream(a, transpose=True, out=b), st)
+    st = st.cpu().double().numpy()
+    fg = np.stack([f, g])
+    lhs, rhs = (fg * y).sum(-1), (x * st).sum(-1)
+    assert np.all(np.abs(lhs - rhs) <= tol * (np.abs(fg * y).sum(-1) + np.abs(x * st).sum(-1)))
