@@ -60,6 +60,9 @@ struct sllbm_ctx {
     int32_t *d_gsrc[2][3] = {{nullptr, nullptr, nullptr}, {nullptr, nullptr, nullptr}};
     void *d_gw[2][3] = {{nullptr, nullptr, nullptr}, {nullptr, nullptr, nullptr}};
     int gk[2] = {0, 0}, gwxm[2] = {0, 0}, gwym[2] = {0, 0};
+    int32_t *d_gfirst[3] = {nullptr, nullptr, nullptr};   // outputs by departure cell (build_cell_readers)
+    void *d_gtw[2] = {nullptr, nullptr};                   // transposed weights by cell, x and y (build_cell_weights)
+    int gmy = 0, gmost = 0;
     double *d_hw = nullptr;        // graded cell widths: x cells, then y, then z (loss, diagnostics)
     // distorted mesh (sllbm_set_displacement): departure cells and local
     // coordinates per velocity and node, per-node quadrature weights
@@ -136,6 +139,8 @@ void free_ctx(sllbm_ctx *c)
             (void)hipFree(c->d_gsrc[d][a]);
             (void)hipFree(c->d_gw[d][a]);
         }
+    for (int a = 0; a < 3; ++a) (void)hipFree(c->d_gfirst[a]);
+    for (int a = 0; a < 2; ++a) (void)hipFree(c->d_gtw[a]);
     (void)hipFree(c->d_hw);
     (void)hipFree(c->d_mcell);
     (void)hipFree(c->d_mt);
@@ -205,6 +210,21 @@ NodeTables<S> node_tables(const sllbm_ctx *c, int dir)
     return t;
 }
 
+template <typename S>
+CellReaders<S> cell_readers(const sllbm_ctx *c)
+{
+    CellReaders<S> t{};
+    for (int a = 0; a < 3; ++a) {
+        t.src[a] = c->d_gsrc[0][a];
+        t.first[a] = c->d_gfirst[a];
+        t.w[a] = static_cast<const S *>(c->d_gw[0][a]);
+    }
+    for (int a = 0; a < 2; ++a) t.tw[a] = static_cast<const S *>(c->d_gtw[a]);
+    t.my = c->gmy;
+    t.most = c->gmost;
+    return t;
+}
+
 bool is_fp64(const sllbm_ctx *c) { return c->cfg.precision == SLLBM_FP64; }
 
 // calls that exist for the three-dimensional lattice only (adjoint, loss,
@@ -238,6 +258,21 @@ void *other(sllbm_ctx *c) { return c->buf[1 - c->cur]; }
 int check_launch(sllbm_ctx *c, hipError_t e, const char *what)
 {
     return e == hipSuccess ? SLLBM_OK : hip_fail(c, e, what);
+}
+
+// S (dir 0) or S^T (dir 1) on a graded mesh
+template <typename S>
+hipError_t stream_graded_as(sllbm_ctx *c, const S *in, S *out, int dir)
+{
+    if (graded_by_cell(c->geo, dir == 1, c->gmost, c->gmy, sizeof(S)))
+        return launch_graded_cells<S>(c->geo, cell_readers<S>(c), dir == 1, in, out, c->stream);
+    return launch_stream_graded<S>(c->geo, node_tables<S>(c, dir), in, out, c->stream);
+}
+
+hipError_t stream_graded_into(sllbm_ctx *c, const void *in, void *out, int dir)
+{
+    return is_fp64(c) ? stream_graded_as(c, static_cast<const double *>(in), static_cast<double *>(out), dir)
+                      : stream_graded_as(c, static_cast<const float *>(in), static_cast<float *>(out), dir);
 }
 
 // Per-node departure tables of the three axes (graded mesh) in the storage
@@ -304,6 +339,32 @@ int upload_graded(sllbm_ctx *c)
         if (smem > 160 * 1024)
             return fail(c, SLLBM_EINVAL, "graded mesh: the source window of a tile needs " + std::to_string(smem) +
                                              " bytes of LDS (more than 160 KB); the grading is too strong");
+    }
+    // the departures by source cell
+    std::vector<int32_t> first[3];
+    int readers[3];
+    for (int a = 0; a < 3; ++a) readers[a] = build_cell_readers(g.N[a], p, src[0][a], first[a]);
+    c->gmy = readers[1];
+    c->gmost = graded_cell_rows(p, std::max(readers[0], readers[1]));
+    for (int a = 0; a < 3; ++a) {
+        (void)hipFree(c->d_gfirst[a]);
+        c->d_gfirst[a] = nullptr;
+        if ((e = dalloc(&c->d_gfirst[a], first[a].size() * sizeof(int32_t))) != hipSuccess)
+            return fail(c, SLLBM_ENOMEM, std::string("graded table allocation: ") + hipGetErrorString(e));
+        if ((e = hipMemcpy(c->d_gfirst[a], first[a].data(), first[a].size() * sizeof(int32_t),
+                           hipMemcpyHostToDevice)) != hipSuccess)
+            return hip_fail(c, e, "graded table upload");
+        if (a == 2) continue;
+        (void)hipFree(c->d_gtw[a]);
+        c->d_gtw[a] = nullptr;
+        if (c->gmost == 0) continue;
+        std::vector<double> tw;
+        build_cell_weights(g.N[a], p, c->gmost, first[a], w[0][a], tw);
+        const std::vector<S> tws(tw.begin(), tw.end());
+        if ((e = dalloc(reinterpret_cast<S **>(&c->d_gtw[a]), tws.size() * sizeof(S))) != hipSuccess)
+            return fail(c, SLLBM_ENOMEM, std::string("graded table allocation: ") + hipGetErrorString(e));
+        if ((e = hipMemcpy(c->d_gtw[a], tws.data(), tws.size() * sizeof(S), hipMemcpyHostToDevice)) != hipSuccess)
+            return hip_fail(c, e, "graded table upload");
     }
     // node quadrature weights: Clenshaw-Curtis weight of the local point
     // times half the cell width; a cell's first point also carries the last
@@ -805,13 +866,7 @@ static hipError_t stream_into(sllbm_ctx *c, const void *in, void *out)
         return launch_stream_2d<float>(c->geo, cell_tables<float>(c), static_cast<const float *>(in),
                                        static_cast<float *>(out), c->stream);
     }
-    if (c->graded) {
-        if (is_fp64(c))
-            return launch_stream_graded<double>(c->geo, node_tables<double>(c, 0), static_cast<const double *>(in),
-                                                static_cast<double *>(out), c->stream);
-        return launch_stream_graded<float>(c->geo, node_tables<float>(c, 0), static_cast<const float *>(in),
-                                           static_cast<float *>(out), c->stream);
-    }
+    if (c->graded) return stream_graded_into(c, in, out, 0);
     if (is_fp64(c))
         return launch_stream_z<double>(c->geo, cell_tables<double>(c), static_cast<const double *>(in),
                                        static_cast<double *>(out), c->stream);
@@ -830,13 +885,7 @@ static hipError_t stream_t_into(sllbm_ctx *c, const void *in, void *out)
         return launch_stream_mapped_t<float>(c->geo, mapped_tables(c), static_cast<const float *>(in),
                                              static_cast<float *>(out), c->stream);
     }
-    if (c->graded) {
-        if (is_fp64(c))
-            return launch_stream_graded<double>(c->geo, node_tables<double>(c, 1), static_cast<const double *>(in),
-                                                static_cast<double *>(out), c->stream);
-        return launch_stream_graded<float>(c->geo, node_tables<float>(c, 1), static_cast<const float *>(in),
-                                           static_cast<float *>(out), c->stream);
-    }
+    if (c->graded) return stream_graded_into(c, in, out, 1);
     if (is_fp64(c))
         return launch_stream_zt<double>(c->geo, cell_tables<double>(c), static_cast<const double *>(in),
                                         static_cast<double *>(out), c->stream);

@@ -61,6 +61,16 @@ void build_node_tables(const VelocitySet &vs, int p, int ne, double length, cons
 void build_transposed_node_tables(int N, int p, const std::vector<int32_t> &src, const std::vector<double> &w,
                                   int kt, std::vector<int32_t> &srcT, std::vector<double> &wT, int &band);
 
+// Outputs by departure cell of those rows: per velocity, first[i][c], c = 0 ..
+// n_el, is the first output (not wrapped, first[n_el] = first[0] + N) that
+// departs into cell c or a later one; returns the most outputs of one cell.
+int build_cell_readers(int N, int p, const std::vector<int32_t> &src, std::vector<int32_t> &first);
+// Their weights for the transpose, [Q][n_el][rows][p + 1]: entry (c, j, k < p) is
+// what the j-th reader of cell c gives to its point k, entry (c, j, p) what the
+// j-th reader of cell c - 1 gives to that cell's last point; 0 past the last reader.
+void build_cell_weights(int N, int p, int rows, const std::vector<int32_t> &first, const std::vector<double> &w,
+                        std::vector<double> &tw);
+
 // Source windows of the distorted-mesh streaming (MAPPED_TILE node tiles, x
 // fastest): per velocity and tile, the departure cells of the tile's nodes
 // unwrapped next to each node's own cell span [lo, hi] per axis; win holds
@@ -133,6 +143,18 @@ struct NodeTables {
     const S *w[3];          // [Q][N_a][k] weights of the k consecutive input nodes
     int k;                  // taps per output node (a value graded_taps_supported returns)
     int wxm, wym;
+};
+
+// The same departures by source cell (build_cell_readers): the outputs of axis a
+// that depart into cell c are first[a][i][c] .. first[a][i][c + 1] - 1 (not
+// wrapped), first of size [Q][n_el + 1]; src and w are the forward tables.
+template <typename S>
+struct CellReaders {
+    const int32_t *src[3], *first[3];
+    const S *w[3];
+    const S *tw[2];         // transposed weights of the x and y cells (build_cell_weights)
+    int my;                 // most outputs that depart into one cell along y
+    int most;               // graded_cell_rows: room for the readers of a cell along x and y
 };
 
 // GLC points of a cell and 1 / prod_{m != k} (t_k - t_m): ell_k(t) =
@@ -288,6 +310,14 @@ hipError_t launch_stream_mapped_t(const Geometry &g, const MappedTables &t, cons
 // streaming on a graded mesh (stream_graded.hip)
 template <typename S>
 hipError_t launch_stream_graded(const Geometry &g, const NodeTables<S> &t, const S *in, S *out, hipStream_t st);
+// the same by source cell (forward and transposed), where graded_by_cell allows.
+// graded_cell_rows: the room that the transposed kernel has for the readers of
+// one cell (P + 1 or P + 3), given the most that a cell has; 0 if more.
+int graded_cell_rows(int p, int most);
+bool graded_by_cell(const Geometry &g, bool transpose, int most, int my, size_t elem);
+template <typename S>
+hipError_t launch_graded_cells(const Geometry &g, const CellReaders<S> &t, bool transpose, const S *in, S *out,
+                               hipStream_t st);
 size_t graded_smem_bytes(int taps, int wxm, int wym, size_t elem);
 int graded_window(const int32_t *src, int N, int taps, int T);
 int graded_taps_supported(int taps);      // smallest supported tap count >= taps, 0 if none

@@ -227,4 +227,48 @@ void build_transposed_node_tables(int N, int p, const std::vector<int32_t> &src,
     }
 }
 
+int build_cell_readers(int N, int p, const std::vector<int32_t> &src, std::vector<int32_t> &first)
+{
+    const int ne = N / p;
+    first.assign(static_cast<size_t>(Q) * (ne + 1), 0);
+    int most = 0;
+    for (int i = 0; i < Q; ++i) {
+        const int32_t *s = &src[static_cast<size_t>(i) * N];
+        int32_t *f = &first[static_cast<size_t>(i) * (ne + 1)];
+        // the cells after that of output 0 in turn, a period of them; cell e is
+        // cell e - k ne of the grid, reached from outputs k N earlier
+        const int e0 = s[0] / p;                           // exact: s is a multiple of p
+        int g = 0;
+        for (int e = e0 + 1; e <= e0 + ne; ++e) {
+            while (g < N && s[g] / p < e) ++g;
+            const int c = ((e % ne) + ne) % ne;
+            f[c] = g - (e - c) / ne * N;
+        }
+        f[ne] = f[0] + N;
+        for (int c = 0; c < ne; ++c) most = std::max(most, f[c + 1] - f[c]);
+    }
+    return most;
+}
+
+void build_cell_weights(int N, int p, int rows, const std::vector<int32_t> &first, const std::vector<double> &w,
+                        std::vector<double> &tw)
+{
+    const int ne = N / p;
+    tw.assign(static_cast<size_t>(Q) * ne * rows * (p + 1), 0.0);
+    for (int i = 0; i < Q; ++i) {
+        const int32_t *f = &first[static_cast<size_t>(i) * (ne + 1)];
+        auto weight = [&](int g, int k) {                  // of output g (not wrapped)
+            const int gw = ((g % N) + N) % N;
+            return w[(static_cast<size_t>(i) * N + gw) * (p + 1) + k];
+        };
+        for (int c = 0; c < ne; ++c) {
+            double *o = &tw[(static_cast<size_t>(i) * ne + c) * rows * (p + 1)];
+            for (int j = 0; j < f[c + 1] - f[c]; ++j)
+                for (int k = 0; k < p; ++k) o[j * (p + 1) + k] = weight(f[c] + j, k);
+            const int before = c > 0 ? f[c - 1] : f[ne - 1] - N;
+            for (int j = 0; j < f[c] - before; ++j) o[j * (p + 1) + p] = weight(before + j, p);
+        }
+    }
+}
+
 }  // namespace sllbm

@@ -141,3 +141,41 @@ def test_streaming_by_source_cell(oracle, precision, n_el, p, dt):
     fg = np.stack([f, g])
     lhs, rhs = (fg * y).sum(-1), (x * st).sum(-1)
     assert np.all(np.abs(lhs - rhs) <= tol * (np.abs(fg * y).sum(-1) + np.abs(x * st).sum(-1)))
+
+
+# rows of one to four waves with and without idle lanes, a row too long for a
+# block and orders that are marched, blocks ragged along y, blocks of one and of
+# several cells along z with a remainder, one-cell axes, shifts of several
+# cells, and a grading with cells that nothing departs into and cells with more
+# than P + 3 readers
+GRADED_FORMS = [((16, 5, 6), 4, 0.05, 0.4), ((17, 3, 9), 4, 0.05, 0.4), ((43, 2, 3), 3, 0.03, 0.4),
+                ((64, 1, 2), 4, 0.02, 0.4), ((65, 2, 2), 4, 0.02, 0.4), ((33, 5, 2), 6, 0.04, 0.4),
+                ((3, 9, 40), 2, 0.1, 0.4), ((1, 1, 5), 3, 0.9, 0.4), ((5, 7, 1), 5, 0.3, 0.4),
+                ((4, 6, 5), 6, 1.1, 0.3), ((9, 8, 7), 3, 0.2, 0.9), ((9, 4, 3), 1, 0.2, 0.4)]
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("n_el,p,dt,amp", GRADED_FORMS)
+def test_graded_streaming_by_source_cell(oracle, precision, n_el, p, dt, amp):
+    """Streaming on graded cells against the oracle (1e-12, FP32 1e-5: the
+    repository's bars) and its transpose as the adjoint of it, per velocity."""
+    from paper_2012_05537_amd.sllbm import SLLBM
+    rng = np.random.default_rng(sum(n_el) + p)
+    widths = []
+    for n in n_el:
+        w = 1.0 + amp * rng.uniform(-1.0, 1.0, n)
+        widths.append(w * (2 * np.pi / w.sum()))
+    ctx = SLLBM(n_el, p, dt, 0.01, precision=precision)
+    ctx.set_mesh(*widths)
+    cfg = oracle.make_cfg(n_el, p, dt, 0.01, widths=widths)
+    x = rng.normal(size=(2, Q, ctx.nodes)).astype(np.float32).astype(np.float64)
+    y = rng.normal(size=x.shape).astype(np.float32).astype(np.float64)
+    print("graded form", precision, n_el, p, flush=True)
+    F, G = to_np(ctx.stream(to_dev(ctx, x[0], x[1])))
+    f, g = oracle.stream(cfg, x[0], x[1])
+    tol = 1e-5 if precision else 1e-12
+    assert rel_err(F, f) < tol and rel_err(G, g) < tol
+    st = np.stack(to_np(ctx.stream(to_dev(ctx, y[0], y[1]), transpose=True)))
+    fg = np.stack([f, g])
+    lhs, rhs = (fg * y).sum(-1), (x * st).sum(-1)
+    assert np.all(np.abs(lhs - rhs) <= tol * (np.abs(fg * y).sum(-1) + np.abs(x * st).sum(-1)))
