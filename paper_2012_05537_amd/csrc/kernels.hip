@@ -15,9 +15,9 @@ namespace sllbm {
 
 // Collision of a whole state (Eq. (5) right-hand side with App. D), two
 // lanes per node (f on the even lane, g on the odd one), the values in
-// registers: D3Q45 in FP64, D2Q19 in FP32, and the cases that k_collide_lds
-// below does not take (N not a multiple of 16 / sizeof(S), an input not
-// 16-byte aligned).  On grids larger than the Infinity Cache the moment sums
+// registers: D3Q45 in FP64 on grids larger than the Infinity Cache, D2Q19 in
+// FP32, and the cases that k_collide_lds below does not take (N not a multiple
+// of 16 / sizeof(S), an input not 16-byte aligned).  On grids larger than the Infinity Cache the moment sums
 // are pinned before the viscosity branch (pin() in collision.h): D3Q45 then
 // needs 168 VGPRs, 3 waves per SIMD, instead of 224 and 2; in FP64 4.61 -> 4.56
 // ms at 256^3 nodes (5.3 TB/s, HBM-bound) and 556 -> 532 us at 128^3.  On
@@ -57,17 +57,18 @@ __global__ void __launch_bounds__(256) k_collide(int64_t N, CollisionParams cp, 
 
 // DMA copy of 16 bytes per lane from g into LDS at l + 16 * lane (l is
 // wave-uniform).  AUX is the copy's cache-policy operand (2: non-temporal,
-// 0: the default policy).  A device function of its own: the 16-byte form
-// exists on gfx950 only, and the host pass drops the launch stub of a
-// kernel whose body names it.
-template <int AUX, typename T>
-__device__ __forceinline__ void dma16(const T *g, T *l)
+// 0: the default policy).  Untyped, in a device function of its own: the
+// 16-byte form exists on gfx950 only, and the host pass drops the launch stub
+// of a kernel whose body names it.
+template <int AUX>
+__device__ __forceinline__ void dma16(const void *g, void *l)
 {
     __builtin_amdgcn_global_load_lds(g, l, 16, 0, AUX);
 }
 
 // The collision with its values staged in LDS; used for D3Q45 in FP32
-// storage and D2Q19 in FP64, for N a multiple of 16 / sizeof(S) and a
+// storage, and in FP64 while the state fits the Infinity Cache, and for D2Q19 in
+// FP64, for N a multiple of 16 / sizeof(S) and a
 // 16-byte aligned input.  A block collides NB = 512 / sizeof(S) consecutive
 // nodes (128 in FP32, 64 in FP64; blocks in XCD order) with NB / 32 waves.
 // Their 2Q rows of NB values (row r = pop * Q + i, 512 contiguous bytes of
@@ -81,7 +82,7 @@ __device__ __forceinline__ void dma16(const T *g, T *l)
 // in may equal out: every copy has landed before the barrier, and a block
 // writes only its own nodes.  NTH: non-temporal copies and stores.
 template <typename S, class L, bool NTH>
-__global__ void __launch_bounds__(1024 / sizeof(S), 3) k_collide_lds(int64_t N, CollisionParams cp, const S *in,
+__global__ void __launch_bounds__(1024 / sizeof(S), L::Q == 45 && sizeof(S) == 8 ? 1 : 3) k_collide_lds(int64_t N, CollisionParams cp, const S *in,
                                                                      S *out)
 {
     constexpr int NQ = L::Q, ROWS = 2 * NQ, NB = 512 / sizeof(S), NW = NB / 32, VL = 16 / sizeof(S);
@@ -300,20 +301,27 @@ static int node_grid(int64_t N)
 template <typename S, class L>
 static hipError_t collide_lat(const Geometry &g, const CollisionParams &cp, const S *in, S *out, hipStream_t st)
 {
-    if constexpr ((L::Q == 45 && sizeof(S) == 4) || (L::Q == Q2D && sizeof(S) == 8)) {
+    if constexpr (L::Q == 45 || sizeof(S) == 8) {
         // LDS-staged form, measured against the register forms: D3Q45 FP32
         // at 256^3 nodes 3.02 -> 2.29 ms, D2Q19 FP64 at 512^2 nodes 34 ->
-        // 28 us (no faster for D2Q19 in FP32, slower for D3Q45 in FP64 at
-        // 128^3 and 256^3 nodes); its 16-byte copies need aligned rows
+        // 28 us (no faster for D2Q19 in FP32); D3Q45 FP64 while the state fits
+        // the Infinity Cache (64^3 nodes 76 -> 60 us, the step 144 -> 141; 48^3 28 us
+        // either way; but 80^3 148 -> 155 and 128^3 530 -> 573); its 16-byte copies
+        // need aligned rows
         constexpr int NB = 512 / sizeof(S), VL = 16 / sizeof(S);
-        if (g.nodes % VL == 0 && reinterpret_cast<uintptr_t>(in) % 16 == 0) {
+        constexpr bool CACHED_ONLY = L::Q == 45 && sizeof(S) == 8;
+        const bool nt = use_nontemporal(2 * L::Q * g.nodes * static_cast<int64_t>(sizeof(S)));
+        if (g.nodes % VL == 0 && reinterpret_cast<uintptr_t>(in) % 16 == 0 && !(CACHED_ONLY && nt)) {
             const int64_t b = (g.nodes + NB - 1) / NB;
-            if (use_nontemporal(2 * L::Q * g.nodes * static_cast<int64_t>(sizeof(S))))
-                hipLaunchKernelGGL((k_collide_lds<S, L, true>), dim3(static_cast<unsigned>(b)), dim3(2 * NB), 0, st,
-                                   g.nodes, cp, in, out);
-            else
-                hipLaunchKernelGGL((k_collide_lds<S, L, false>), dim3(static_cast<unsigned>(b)), dim3(2 * NB), 0,
-                                   st, g.nodes, cp, in, out);
+            if constexpr (!CACHED_ONLY) {
+                if (nt) {
+                    hipLaunchKernelGGL((k_collide_lds<S, L, true>), dim3(static_cast<unsigned>(b)), dim3(2 * NB), 0, st,
+                                       g.nodes, cp, in, out);
+                    return hipGetLastError();
+                }
+            }
+            hipLaunchKernelGGL((k_collide_lds<S, L, false>), dim3(static_cast<unsigned>(b)), dim3(2 * NB), 0, st,
+                               g.nodes, cp, in, out);
             return hipGetLastError();
         }
     }
