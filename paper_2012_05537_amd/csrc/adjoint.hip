@@ -934,7 +934,8 @@ hipError_t Launch<S>::collide_vjp(const Geometry &g, const CollisionParams &cp, 
                                   double *dmu_partials, double *dmu, hipStream_t st)
 {
     // lam <- J_C(X_n)^T lam in place
-    const bool nt = use_nontemporal(90 * g.nodes * static_cast<int64_t>(sizeof(S)));
+    const int64_t plane = g.nodes * static_cast<int64_t>(sizeof(S));
+    const bool nt = use_nontemporal(90 * plane, plane);
     int blocks = 0;
     bool staged = false;
     // alpha staged in LDS (see k_collide_vjp_lds): in FP32 always; in FP64 it

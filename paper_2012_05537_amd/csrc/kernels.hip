@@ -15,8 +15,7 @@ namespace sllbm {
 
 // Collision of a whole state (Eq. (5) right-hand side with App. D), two
 // lanes per node (f on the even lane, g on the odd one), the values in
-// registers: D3Q45 in FP64 on grids larger than the Infinity Cache, D2Q19 in
-// FP32, and the cases that k_collide_lds below does not take (N not a multiple
+// registers: D3Q45 in FP64 with non-temporal accesses, D2Q19 in FP32, and the cases that k_collide_lds below does not take (N not a multiple
 // of 16 / sizeof(S), an input not 16-byte aligned).  On grids larger than the Infinity Cache the moment sums
 // are pinned before the viscosity branch (pin() in collision.h): D3Q45 then
 // needs 168 VGPRs, 3 waves per SIMD, instead of 224 and 2; in FP64 4.61 -> 4.56
@@ -67,8 +66,7 @@ __device__ __forceinline__ void dma16(const void *g, void *l)
 }
 
 // The collision with its values staged in LDS; used for D3Q45 in FP32
-// storage, and in FP64 while the state fits the Infinity Cache, and for D2Q19 in
-// FP64, for N a multiple of 16 / sizeof(S) and a
+// storage, and in FP64 without non-temporal accesses, and for D2Q19 in FP64, for N a multiple of 16 / sizeof(S) and a
 // 16-byte aligned input.  A block collides NB = 512 / sizeof(S) consecutive
 // nodes (128 in FP32, 64 in FP64; blocks in XCD order) with NB / 32 waves.
 // Their 2Q rows of NB values (row r = pop * Q + i, 512 contiguous bytes of
@@ -301,19 +299,20 @@ static int node_grid(int64_t N)
 template <typename S, class L>
 static hipError_t collide_lat(const Geometry &g, const CollisionParams &cp, const S *in, S *out, hipStream_t st)
 {
+    const int64_t plane = g.nodes * static_cast<int64_t>(sizeof(S));
     if constexpr (L::Q == 45 || sizeof(S) == 8) {
         // LDS-staged form, measured against the register forms: D3Q45 FP32
         // at 256^3 nodes 3.02 -> 2.29 ms, D2Q19 FP64 at 512^2 nodes 34 ->
-        // 28 us (no faster for D2Q19 in FP32); D3Q45 FP64 while the state fits
-        // the Infinity Cache (64^3 nodes 76 -> 60 us, the step 144 -> 141; 48^3 28 us
-        // either way; but 80^3 148 -> 155 and 128^3 530 -> 573); its 16-byte copies
-        // need aligned rows
+        // 28 us (no faster for D2Q19 in FP32); D3Q45 FP64 where the register
+        // form has no non-temporal accesses (64^3 nodes 76 -> 60 us, the step 144 ->
+        // 141; 48^3 28 us either way; 126 x 129 x 129 690 -> 620; but with them 80^3 148
+        // -> 155 and 128^3 530 -> 573); its 16-byte copies need aligned rows
         constexpr int NB = 512 / sizeof(S), VL = 16 / sizeof(S);
-        constexpr bool CACHED_ONLY = L::Q == 45 && sizeof(S) == 8;
-        const bool nt = use_nontemporal(2 * L::Q * g.nodes * static_cast<int64_t>(sizeof(S)));
-        if (g.nodes % VL == 0 && reinterpret_cast<uintptr_t>(in) % 16 == 0 && !(CACHED_ONLY && nt)) {
+        constexpr bool NO_NT = L::Q == 45 && sizeof(S) == 8;
+        const bool nt = use_nontemporal(2 * L::Q * plane, plane);
+        if (g.nodes % VL == 0 && reinterpret_cast<uintptr_t>(in) % 16 == 0 && !(NO_NT && nt)) {
             const int64_t b = (g.nodes + NB - 1) / NB;
-            if constexpr (!CACHED_ONLY) {
+            if constexpr (!NO_NT) {
                 if (nt) {
                     hipLaunchKernelGGL((k_collide_lds<S, L, true>), dim3(static_cast<unsigned>(b)), dim3(2 * NB), 0, st,
                                        g.nodes, cp, in, out);
@@ -334,7 +333,7 @@ static hipError_t collide_lat(const Geometry &g, const CollisionParams &cp, cons
         return hipGetLastError();
     }
     const int64_t blocks = (2 * g.nodes + 255) / 256;
-    if (use_nontemporal(2 * L::Q * g.nodes * static_cast<int64_t>(sizeof(S))))
+    if (use_nontemporal(2 * L::Q * plane, plane))
         hipLaunchKernelGGL((k_collide<S, L, true>), dim3(static_cast<unsigned>(blocks)), dim3(256), 0, st, g.nodes, cp,
                            in, out);
     else

@@ -299,7 +299,7 @@ static hipError_t launch_z(const Geometry &g, const CellTables<S> &t, const S *i
     ZLayout lay = z_layout(g, 1);
     unsigned nb;
     if (!z_split(g, z_max_cells<P>(), lay, nb)) return hipErrorInvalidValue;
-    if (use_nontemporal(90 * g.nodes * static_cast<int64_t>(sizeof(S))))
+    if (use_nontemporal(90 * g.nodes * static_cast<int64_t>(sizeof(S)), g.N[0] * static_cast<int64_t>(sizeof(S))))
         hipLaunchKernelGGL((k_stream_z<S, P, true>), dim3(nb, 90), dim3(lay.nt), 0, st, g, t, in, out, lay);
     else
         hipLaunchKernelGGL((k_stream_z<S, P, false>), dim3(nb, 90), dim3(lay.nt), 0, st, g, t, in, out, lay);
@@ -537,7 +537,7 @@ static hipError_t launch_zt(const Geometry &g, const CellTables<S> &t, const S *
     ZLayout lay = z_layout(g, P);
     unsigned nb;
     if (!z_split(g, zt_max_cells<S, P>(), lay, nb)) return hipErrorInvalidValue;
-    if (use_nontemporal(90 * g.nodes * static_cast<int64_t>(sizeof(S))))
+    if (use_nontemporal(90 * g.nodes * static_cast<int64_t>(sizeof(S)), g.N[0] * static_cast<int64_t>(sizeof(S))))
         hipLaunchKernelGGL((k_stream_zt<S, P, true>), dim3(nb, 90), dim3(lay.nt), 0, st, g, t, in, out, lay);
     else
         hipLaunchKernelGGL((k_stream_zt<S, P, false>), dim3(nb, 90), dim3(lay.nt), 0, st, g, t, in, out, lay);
