@@ -28,8 +28,10 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "collision.h"
+#include "dma.h"
 #include "nt.h"
 #include "sllbm_internal.h"
 #include "velset.h"
@@ -418,44 +420,31 @@ __global__ void __launch_bounds__(256, 2) k_collide_vjp(int64_t N, CollisionPara
     }
 }
 
-// DMA copy of 16 bytes per lane from g into LDS at l + 16 * lane (l is
-// wave-uniform; AUX 2: non-temporal).  Untyped, in a device function of its
-// own: the 16-byte form exists on gfx950 only.
-template <int AUX>
-__device__ __forceinline__ void dma16_adj(const void *g, void *l)
-{
-    __builtin_amdgcn_global_load_lds(g, l, 16, 0, AUX);
-}
-
 // The collision VJP with the adjoint inputs alpha staged in LDS: a block takes
 // NB = 512 / sizeof(S) consecutive nodes (blocks in XCD order), copies their
 // 90 rows of mu (row r = pop * 45 + i, 512 contiguous bytes) into LDS by
-// 16-byte DMA copies, and each lane reads its alpha_i from there (lane l of
+// DMA (stage_rows; WIDE: 16-byte copies, for aligned rows), and each lane reads
+// its alpha_i from there (lane l of
 // wave w: node w * 32 + (l & 31), population l >> 5, partner l ^ 32).
-// N % (16 / sizeof(S)) == 0 and mu 16-byte aligned; mu and lam may be the same
-// buffer (every copy has landed before the block's first write).
+// mu and lam may be the same buffer (every copy has landed before the block's
+// first write).
 // Bound by HBM: it reads X and alpha and writes lambda once, 3.53 ms at 256^3
 // nodes in FP32 (18.1 GB, 5.1 TB/s; 166 VGPRs, 3 waves per SIMD), 451 us at
 // 128^3 and 63 us at 64^3.  While the sweep's sums sank past the branch on the
 // viscosity law it needed 256 VGPRs with spills (2 waves) and took 5.73 ms.
-template <typename S, bool NTH>
+template <typename S, bool NTH, bool WIDE>
 __global__ void __launch_bounds__(1024 / sizeof(S), sizeof(S) == 4 ? 3 : 2) k_collide_vjp_lds(int64_t N, CollisionParams cp,
                                                             const S *__restrict__ X, const S *mu, S *lam,
                                                             double *__restrict__ dmu_part)
 {
-    constexpr int NB = 512 / sizeof(S), ROWS = 2 * vs::Q, NW = NB / 32, VL = 16 / sizeof(S);
+    constexpr int NB = 512 / sizeof(S), ROWS = 2 * vs::Q, NW = NB / 32;
     __shared__ S tile[ROWS][NB];
-    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int pop = lane >> 5;
     const int c = w * 32 + (lane & 31);
     const int64_t nb = static_cast<int64_t>(xcd_linear(blockIdx.x, gridDim.x)) * NB;
-    const int64_t col = nb + VL * (lane & 31);
-    if (col < N) {
-        const S *src = mu + static_cast<int64_t>(lane >> 5) * N + col;
-        for (int m = w; m < ROWS / 2; m += NW) dma16_adj<NTH ? 2 : 0>(src + static_cast<int64_t>(2 * m) * N, &tile[2 * m][0]);
-    }
-    __builtin_amdgcn_s_waitcnt(0);               // this wave's copies have landed
-    __syncthreads();                             // and every other wave's
+    stage_rows<S, ROWS, NB, NW, WIDE, NTH>(N, nb, mu, tile, w, lane);
+    __syncthreads();                             // the other waves' copies too
     const int64_t n = nb + c;
     const bool active = n < N;
     const int64_t off = static_cast<int64_t>(pop) * vs::Q * N + (active ? n : 0);
@@ -937,25 +926,29 @@ hipError_t Launch<S>::collide_vjp(const Geometry &g, const CollisionParams &cp, 
     const int64_t plane = g.nodes * static_cast<int64_t>(sizeof(S));
     const bool nt = use_nontemporal(90 * plane, plane);
     int blocks = 0;
-    bool staged = false;
     // alpha staged in LDS (see k_collide_vjp_lds): in FP32 always; in FP64 it
     // leaves 1.5 waves per SIMD, which is faster while the grid has at most two
     // blocks per CU (10.3 against 12.4 us at 512 nodes, 11.4 against 14.2 at
-    // 13,824) and 1-6 % slower from 110,592 nodes on
-    if (sizeof(S) == 4 || g.nodes <= 32768) {
+    // 13,824) and 1-6 % slower from 110,592 nodes on.  Rows that are not 16-byte
+    // aligned are staged by words on large FP32 grids (adjoint step at 63^3 nodes
+    // 112 -> 102 us, 129^3 1032 -> 948, 45^3 equal, 39 x 33 x 27 27.4 -> 29.4), otherwise not.
+    const bool wide = g.nodes % (16 / sizeof(S)) == 0 && reinterpret_cast<uintptr_t>(lam) % 16 == 0;
+    if (wide ? sizeof(S) == 4 || g.nodes <= 32768 : sizeof(S) == 4 && g.nodes > 65536) {
         constexpr int NB = 512 / sizeof(S);
-        if (g.nodes % (16 / sizeof(S)) == 0 && reinterpret_cast<uintptr_t>(lam) % 16 == 0) {
-            staged = true;
-            blocks = static_cast<int>((g.nodes + NB - 1) / NB);
-            if (nt)
-                hipLaunchKernelGGL((k_collide_vjp_lds<S, true>), dim3(static_cast<unsigned>(blocks)), dim3(2 * NB), 0, st,
-                                   g.nodes, cp, state_n, lam, lam, dmu ? dmu_partials : nullptr);
-            else
-                hipLaunchKernelGGL((k_collide_vjp_lds<S, false>), dim3(static_cast<unsigned>(blocks)), dim3(2 * NB), 0, st,
-                                   g.nodes, cp, state_n, lam, lam, dmu ? dmu_partials : nullptr);
+        blocks = static_cast<int>((g.nodes + NB - 1) / NB);
+        auto launch = [&](auto nth, auto wd) {
+            hipLaunchKernelGGL((k_collide_vjp_lds<S, decltype(nth)::value, decltype(wd)::value>),
+                               dim3(static_cast<unsigned>(blocks)), dim3(2 * NB), 0, st, g.nodes, cp, state_n, lam, lam,
+                               dmu ? dmu_partials : nullptr);
+        };
+        if constexpr (sizeof(S) == 4) {
+            if (!wide) launch(std::false_type(), std::false_type());
+            else if (nt) launch(std::true_type(), std::true_type());
+            else launch(std::false_type(), std::true_type());
+        } else {
+            launch(std::false_type(), std::true_type());
         }
-    }
-    if (!staged) {
+    } else {
         blocks = static_cast<int>((2 * g.nodes + 255) / 256);
         if (nt)
             hipLaunchKernelGGL((k_collide_vjp<S, true>), dim3(static_cast<unsigned>(blocks)), dim3(256), 0, st,

@@ -4,8 +4,10 @@
 #include <hip/hip_runtime.h>
 
 #include <cmath>
+#include <type_traits>
 
 #include "collision.h"
+#include "dma.h"
 #include "nt.h"
 #include "sllbm_internal.h"
 #include "velset.h"
@@ -15,8 +17,8 @@ namespace sllbm {
 
 // Collision of a whole state (Eq. (5) right-hand side with App. D), two
 // lanes per node (f on the even lane, g on the odd one), the values in
-// registers: D3Q45 in FP64 with non-temporal accesses, D2Q19 in FP32, and the cases that k_collide_lds below does not take (N not a multiple
-// of 16 / sizeof(S), an input not 16-byte aligned).  On grids larger than the Infinity Cache the moment sums
+// registers: D3Q45 in FP64 with non-temporal accesses, D2Q19 in FP32, and
+// smaller grids whose rows are not 16-byte aligned.  On grids larger than the Infinity Cache the moment sums
 // are pinned before the viscosity branch (pin() in collision.h): D3Q45 then
 // needs 168 VGPRs, 3 waves per SIMD, instead of 224 and 2; in FP64 4.61 -> 4.56
 // ms at 256^3 nodes (5.3 TB/s, HBM-bound) and 556 -> 532 us at 128^3.  On
@@ -54,52 +56,29 @@ __global__ void __launch_bounds__(256) k_collide(int64_t N, CollisionParams cp, 
     }
 }
 
-// DMA copy of 16 bytes per lane from g into LDS at l + 16 * lane (l is
-// wave-uniform).  AUX is the copy's cache-policy operand (2: non-temporal,
-// 0: the default policy).  Untyped, in a device function of its own: the
-// 16-byte form exists on gfx950 only, and the host pass drops the launch stub
-// of a kernel whose body names it.
-template <int AUX>
-__device__ __forceinline__ void dma16(const void *g, void *l)
-{
-    __builtin_amdgcn_global_load_lds(g, l, 16, 0, AUX);
-}
-
 // The collision with its values staged in LDS; used for D3Q45 in FP32
-// storage, and in FP64 without non-temporal accesses, and for D2Q19 in FP64, for N a multiple of 16 / sizeof(S) and a
-// 16-byte aligned input.  A block collides NB = 512 / sizeof(S) consecutive
-// nodes (128 in FP32, 64 in FP64; blocks in XCD order) with NB / 32 waves.
-// Their 2Q rows of NB values (row r = pop * Q + i, 512 contiguous bytes of
-// plane r) are copied from memory into LDS by DMA, 16 bytes per lane, so
-// one instruction moves two rows (1 KB) and no register holds them; every
-// value is then read from LDS for the moments and again for the relaxation.
+// storage, and in FP64 without non-temporal accesses, and for D2Q19 in FP64.  A block collides NB = 512 / sizeof(S) consecutive nodes (128 in FP32,
+// 64 in FP64; blocks in XCD order) with NB / 32 waves.  Their 2Q rows of NB values
+// (row r = pop * Q + i, 512 contiguous bytes of plane r) are copied from memory
+// into LDS by DMA (stage_rows); every value is then read from LDS for the moments
+// and again for the relaxation.
 // Lane l of wave w holds node w * 32 + (l & 31) of the block and population
 // l >> 5 (partner lane l ^ 32).  For D3Q45 in FP32: 136 VGPRs and 45 KB of
 // LDS per block (3 waves per SIMD), where the register form holds the 45
 // values and reads 128-byte segments per plane and half-wave.
 // in may equal out: every copy has landed before the barrier, and a block
-// writes only its own nodes.  NTH: non-temporal copies and stores.
-template <typename S, class L, bool NTH>
-__global__ void __launch_bounds__(1024 / sizeof(S), L::Q == 45 && sizeof(S) == 8 ? 1 : 3) k_collide_lds(int64_t N, CollisionParams cp, const S *in,
-                                                                     S *out)
+// writes only its own nodes.  NTH: non-temporal copies and stores.  WIDE:
+// 16-byte copies (aligned rows).
+template <typename S, class L, bool NTH, bool WIDE>
+__global__ void __launch_bounds__(1024 / sizeof(S), L::Q == 45 && sizeof(S) == 8 ? 1 : 3) k_collide_lds(
+    int64_t N, CollisionParams cp, const S *in, S *out)
 {
-    constexpr int NQ = L::Q, ROWS = 2 * NQ, NB = 512 / sizeof(S), NW = NB / 32, VL = 16 / sizeof(S);
+    constexpr int NQ = L::Q, ROWS = 2 * NQ, NB = 512 / sizeof(S), NW = NB / 32;
     __shared__ S tile[ROWS][NB];
-    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int64_t nb = static_cast<int64_t>(xcd_linear(blockIdx.x, gridDim.x)) * NB;
-    {
-        // instruction m of the block copies rows 2m (lanes 0-31) and 2m + 1
-        // (lanes 32-63), VL nodes per lane; a lane's nodes are all below N or
-        // all beyond it (N % VL == 0)
-        const int64_t col = nb + VL * (lane & 31);
-        if (col < N) {
-            const S *src = in + static_cast<int64_t>(lane >> 5) * N + col;
-            for (int m = w; m < ROWS / 2; m += NW)
-                dma16<NTH ? 2 : 0>(src + static_cast<int64_t>(2 * m) * N, &tile[2 * m][0]);
-        }
-    }
-    __builtin_amdgcn_s_waitcnt(0);               // this wave's copies have landed
-    __syncthreads();                             // and every other wave's
+    stage_rows<S, ROWS, NB, NW, WIDE, NTH>(N, nb, in, tile, w, lane);
+    __syncthreads();                             // the other waves' copies too
     const int pop = lane >> 5;
     const int c = w * 32 + (lane & 31);
     const int64_t n = nb + c;
@@ -299,29 +278,36 @@ static int node_grid(int64_t N)
 template <typename S, class L>
 static hipError_t collide_lat(const Geometry &g, const CollisionParams &cp, const S *in, S *out, hipStream_t st)
 {
-    const int64_t plane = g.nodes * static_cast<int64_t>(sizeof(S));
+    const int64_t plane = g.nodes * static_cast<int64_t>(sizeof(S)), bytes = 2 * L::Q * plane;
+    const bool nt = use_nontemporal(bytes, plane);
     if constexpr (L::Q == 45 || sizeof(S) == 8) {
         // LDS-staged form, measured against the register forms: D3Q45 FP32
         // at 256^3 nodes 3.02 -> 2.29 ms, D2Q19 FP64 at 512^2 nodes 34 ->
         // 28 us (no faster for D2Q19 in FP32); D3Q45 FP64 where the register
         // form has no non-temporal accesses (64^3 nodes 76 -> 60 us, the step 144 ->
         // 141; 48^3 28 us either way; 126 x 129 x 129 690 -> 620; but with them 80^3 148
-        // -> 155 and 128^3 530 -> 573); its 16-byte copies need aligned rows
+        // -> 155 and 128^3 530 -> 573).  Rows that are not 16-byte aligned are copied by
+        // words, 45 instructions per wave instead of 11: D3Q45 FP32 45^3 nodes 17.1 ->
+        // 14.4 us, 63^3 37.9 -> 34.5, 129^3 390 -> 348, 243^3 2.78 -> 2.24 ms, but 39 x 33 x 27
+        // the step 21.9 -> 22.7; FP64 129^3 700 -> 673 us, but 45^3 26.3 -> 28.1.
         constexpr int NB = 512 / sizeof(S), VL = 16 / sizeof(S);
-        constexpr bool NO_NT = L::Q == 45 && sizeof(S) == 8;
-        const bool nt = use_nontemporal(2 * L::Q * plane, plane);
-        if (g.nodes % VL == 0 && reinterpret_cast<uintptr_t>(in) % 16 == 0 && !(NO_NT && nt)) {
-            const int64_t b = (g.nodes + NB - 1) / NB;
-            if constexpr (!NO_NT) {
-                if (nt) {
-                    hipLaunchKernelGGL((k_collide_lds<S, L, true>), dim3(static_cast<unsigned>(b)), dim3(2 * NB), 0, st,
-                                       g.nodes, cp, in, out);
-                    return hipGetLastError();
-                }
+        constexpr bool D3 = L::Q == 45, NO_NT = D3 && sizeof(S) == 8;
+        const bool wide = g.nodes % VL == 0 && reinterpret_cast<uintptr_t>(in) % 16 == 0;
+        const bool by_words = D3 && (sizeof(S) == 4 ? g.nodes > 65536 : bytes > INFINITY_CACHE_BYTES);
+        if ((wide || by_words) && !(NO_NT && nt)) {
+            auto launch = [&](auto nth, auto wd) {
+                hipLaunchKernelGGL((k_collide_lds<S, L, decltype(nth)::value, decltype(wd)::value>),
+                                   dim3(static_cast<unsigned>((g.nodes + NB - 1) / NB)), dim3(2 * NB), 0, st, g.nodes,
+                                   cp, in, out);
+                return hipGetLastError();
+            };
+            if constexpr (D3) {
+                if (!wide) return launch(std::false_type(), std::false_type());
             }
-            hipLaunchKernelGGL((k_collide_lds<S, L, false>), dim3(static_cast<unsigned>(b)), dim3(2 * NB), 0, st,
-                               g.nodes, cp, in, out);
-            return hipGetLastError();
+            if constexpr (!NO_NT) {
+                if (nt) return launch(std::true_type(), std::true_type());
+            }
+            return launch(std::false_type(), std::true_type());
         }
     }
     if constexpr (L::Q == Q2D && sizeof(S) == 8) {
@@ -333,7 +319,7 @@ static hipError_t collide_lat(const Geometry &g, const CollisionParams &cp, cons
         return hipGetLastError();
     }
     const int64_t blocks = (2 * g.nodes + 255) / 256;
-    if (use_nontemporal(2 * L::Q * plane, plane))
+    if (nt)
         hipLaunchKernelGGL((k_collide<S, L, true>), dim3(static_cast<unsigned>(blocks)), dim3(256), 0, st, g.nodes, cp,
                            in, out);
     else

@@ -179,3 +179,46 @@ def test_graded_streaming_by_source_cell(oracle, precision, n_el, p, dt, amp):
     fg = np.stack([f, g])
     lhs, rhs = (fg * y).sum(-1), (x * st).sum(-1)
     assert np.all(np.abs(lhs - rhs) <= tol * (np.abs(fg * y).sum(-1) + np.abs(x * st).sum(-1)))
+
+
+# rows that are not 16-byte aligned, staged by words: 41 x 41 x 41 (FP32; a last block
+# of one node) and 73 x 73 x 73 nodes (FP64, larger than the Infinity Cache; of
+# 9 nodes)
+@pytest.mark.parametrize("precision,n", [(1, 41), (0, 73)])
+def test_collision_staged_by_words(oracle, precision, n):
+    """Collision and its VJP of an odd grid against the same nodes in a small
+    grid, whose collision is another kernel form: equal to rounding (the moments
+    are summed in the same order: 1e-13 in FP64, one rounding in FP32)."""
+    ctx, _ = make_pair(oracle, (n, n, n), 1, 0.05, 0.02, precision=precision)
+    small, cfg = make_pair(oracle, (3, 3, 3), 1, 0.05, 0.02, precision=precision)
+    f, g = _noisy(oracle, cfg, 5)
+    s = to_dev(small, f, g)
+    k = small.nodes
+    reps = -(-ctx.nodes // k)
+    x = s.repeat(1, 1, reps)[:, :, :ctx.nodes].contiguous()
+    print("staged by words", precision, n, flush=True)
+    want = small.collide(s.clone()).repeat(1, 1, reps)[:, :, :ctx.nodes]
+    got = ctx.collide(x.clone())
+    tol = 2.0 ** -23 if precision else 1e-13
+    assert float(((got - want).abs() / want.abs().amax()).max()) <= tol
+    lam = torch.from_numpy(np.random.default_rng(6).normal(size=s.shape)).to(ctx.device, ctx.dtype)
+    lam = lam.repeat(1, 1, reps)[:, :, :ctx.nodes].contiguous()
+    out = ctx.adjoint_step(x, lam)
+    # the same VJP of the streamed adjoint, node by node, in the small grid's form
+    st = ctx.stream(lam, transpose=True)
+    i0 = (ctx.nodes // k - 2) * k
+    y = torch.empty_like(s)
+    dmu = torch.zeros(1, dtype=torch.float64, device=ctx.device)
+    small_out = _vjp_of(small, s, st[:, :, i0:i0 + k].contiguous(), y, dmu)
+    sel = out[:, :, i0:i0 + k]
+    assert float((sel - small_out).abs().max() / small_out.abs().max()) <= 4 * tol
+
+
+def _vjp_of(ctx, x, alpha, out, dmu):
+    """Collision VJP alone: the transposed streaming undone by a zero shift (dt
+    tiny leaves every node on itself), so that adjoint_step is the VJP."""
+    from paper_2012_05537_amd.sllbm import SLLBM
+    c = ctx.cfg
+    still = SLLBM(tuple(c.n_el), c.order, c.dt, c.mu_inf, precision=c.precision,
+                  length=tuple(1e16 for _ in range(3)))
+    return still.adjoint_step(x, alpha, out, dmu).clone()
