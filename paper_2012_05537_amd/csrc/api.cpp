@@ -811,13 +811,36 @@ int sllbm_init_equilibrium(sllbm_ctx *ctx, const double *rho, const double *u, c
     return SLLBM_OK;
 }
 
+// dst <- src, one of them this context's memory and the other, user, the caller's.
+// States of which two do not fit the Infinity Cache are copied by a kernel
+// (256^3 nodes, FP64: 5.27 -> 4.24 ms, 5.7 TB/s; 64^3 70.5 -> 60.9 us, but FP32 26.7 -> 31.2)
+// if the caller's memory is wholly on this device;
+// anything else (host or peer memory, too small a buffer) is hipMemcpyAsync's
+// to copy or to refuse.
+static hipError_t copy_state(sllbm_ctx *c, void *dst, const void *src, const void *user)
+{
+    const size_t bytes = static_cast<size_t>(sllbm_state_bytes(c));
+    if (use_copy_kernel(bytes, dst, src)) {
+        hipPointerAttribute_t at{};
+        hipDeviceptr_t base = nullptr;
+        size_t size = 0;
+        if (hipPointerGetAttributes(&at, user) != hipSuccess) {
+            (void)hipGetLastError();                       // (not this call's error)
+        } else if (at.type == hipMemoryTypeDevice && at.device == c->cfg.device) {
+            if (hipMemGetAddressRange(&base, &size, const_cast<void *>(user)) != hipSuccess) (void)hipGetLastError();
+            else if (static_cast<const char *>(user) + bytes <= static_cast<const char *>(base) + size)
+                return launch_copy_state(dst, src, bytes, c->stream);
+        }
+    }
+    return hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToDevice, c->stream);
+}
+
 int sllbm_set_state(sllbm_ctx *ctx, const void *state)
 {
     if (!ctx) return SLLBM_EINVAL;
     if (!state) return fail(ctx, SLLBM_EINVAL, "NULL state");
     DeviceGuard guard(ctx->cfg.device);
-    hipError_t e = hipMemcpyAsync(ctx->buf[ctx->cur], state, sllbm_state_bytes(ctx), hipMemcpyDeviceToDevice,
-                                  ctx->stream);
+    hipError_t e = copy_state(ctx, ctx->buf[ctx->cur], state, state);
     if (e != hipSuccess) return hip_fail(ctx, e, "set_state");
     ctx->has_state = true;
     return SLLBM_OK;
@@ -829,8 +852,7 @@ int sllbm_get_state(sllbm_ctx *ctx, void *state)
     if (!state) return fail(ctx, SLLBM_EINVAL, "NULL state");
     if (!ctx->has_state) return fail(ctx, SLLBM_ESTATE, "no state set");
     DeviceGuard guard(ctx->cfg.device);
-    hipError_t e =
-        hipMemcpyAsync(state, ctx->buf[ctx->cur], sllbm_state_bytes(ctx), hipMemcpyDeviceToDevice, ctx->stream);
+    hipError_t e = copy_state(ctx, state, ctx->buf[ctx->cur], state);
     return check_launch(ctx, e, "get_state");
 }
 
@@ -937,8 +959,8 @@ static int step_impl(sllbm_ctx *ctx, int32_t n, char *record, int64_t stride)
         mark(1, 1);
     }
     if (record) {
-        hipError_t e = hipMemcpyAsync(state, record + static_cast<int64_t>(n - 1) * stride, sllbm_state_bytes(ctx),
-                                      hipMemcpyDeviceToDevice, ctx->stream);
+        const char *last = record + static_cast<int64_t>(n - 1) * stride;
+        hipError_t e = copy_state(ctx, state, last, last);
         if (e != hipSuccess) return hip_fail(ctx, e, "record copy");
     }
     return SLLBM_OK;

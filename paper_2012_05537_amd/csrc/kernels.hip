@@ -130,6 +130,26 @@ __global__ void __launch_bounds__(256) k_collide_pf(int64_t N, CollisionParams c
     }
 }
 
+// Copy of a state: 64 bytes per thread in flight, non-temporal both ways.
+__global__ void __launch_bounds__(256) k_copy_state(int64_t n, int words, const uint32_t *__restrict__ src,
+                                                    uint32_t *__restrict__ dst)
+{
+    using V4 = uint32_t __attribute__((ext_vector_type(4)));
+    const V4 *s = reinterpret_cast<const V4 *>(src);       // n vectors, then words single words
+    V4 *d = reinterpret_cast<V4 *>(dst);
+    const int64_t b = blockIdx.x * int64_t(1024) + threadIdx.x;
+    if (b + 768 < n) {
+        V4 v[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) v[k] = __builtin_nontemporal_load(s + b + 256 * k);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) __builtin_nontemporal_store(v[k], d + b + 256 * k);
+    } else {
+        for (int64_t k = b; k < n; k += 256) d[k] = s[k];
+    }
+    if (b < words) dst[4 * n + b] = src[4 * n + b];
+}
+
 // u: [D][N] (the lattice's dimension)
 template <typename S, class L>
 __global__ void __launch_bounds__(256) k_init_equilibrium(int64_t N, CollisionParams cp,
@@ -273,6 +293,20 @@ static int node_grid(int64_t N)
 {
     int64_t b = (N + 255) / 256;
     return static_cast<int>(b < 8192 ? (b < 1 ? 1 : b) : 8192);
+}
+
+bool use_copy_kernel(size_t bytes, const void *dst, const void *src)
+{
+    return static_cast<int64_t>(bytes) > INFINITY_CACHE_BYTES / 2 &&
+           (reinterpret_cast<uintptr_t>(dst) | reinterpret_cast<uintptr_t>(src)) % 16 == 0;
+}
+
+hipError_t launch_copy_state(void *dst, const void *src, size_t bytes, hipStream_t st)
+{
+    const int64_t n = static_cast<int64_t>(bytes / 16);
+    hipLaunchKernelGGL(k_copy_state, dim3(static_cast<unsigned>((n + 1023) / 1024)), dim3(256), 0, st, n,
+                       static_cast<int>(bytes % 16 / 4), static_cast<const uint32_t *>(src), static_cast<uint32_t *>(dst));
+    return hipGetLastError();
 }
 
 template <typename S, class L>

@@ -300,6 +300,10 @@ hipError_t launch_stream_z(const Geometry &g, const CellTables<S> &t, const S *i
 // with the forward cell tables (stream.hip); any number of cells per axis
 template <typename S>
 hipError_t launch_stream_zt(const Geometry &g, const CellTables<S> &t, const S *in, S *out, hipStream_t st);
+// copy of a state (this device's memory, 16-byte aligned, bytes a multiple of 4),
+// and when it is used
+bool use_copy_kernel(size_t bytes, const void *dst, const void *src);
+hipError_t launch_copy_state(void *dst, const void *src, size_t bytes, hipStream_t st);
 // streaming on a distorted mesh (stream_mapped.hip)
 template <typename S>
 hipError_t launch_stream_mapped(const Geometry &g, const MappedTables &t, const S *in, S *out, hipStream_t st);

@@ -222,3 +222,21 @@ def _vjp_of(ctx, x, alpha, out, dmu):
     still = SLLBM(tuple(c.n_el), c.order, c.dt, c.mu_inf, precision=c.precision,
                   length=tuple(1e16 for _ in range(3)))
     return still.adjoint_step(x, alpha, out, dmu).clone()
+
+
+# the copy kernel (64^3 nodes, FP64, and 97 x 97 x 65 FP32: 8 bytes past whole
+# vectors) and hipMemcpyAsync (a buffer one element off)
+@pytest.mark.parametrize("n_el,precision", [((64, 64, 64), 0), ((97, 97, 65), 1)])
+def test_large_state_copies(n_el, precision):
+    from paper_2012_05537_amd.sllbm import SLLBM
+    ctx = SLLBM(n_el, 1, 0.01, 0.01, precision=precision)
+    x = torch.rand((2, Q, ctx.nodes), dtype=ctx.dtype, device=ctx.device)
+    guard = torch.zeros(x.numel() + 8, dtype=ctx.dtype, device=ctx.device)
+    print("state copies", n_el, precision, flush=True)
+    ctx.set_state(x)
+    for off in (4, 3):
+        out = guard[off:off + x.numel()].view(x.shape)
+        ctx.get_state(out)
+        assert torch.equal(out, x)
+        assert not guard[:off].any() and not guard[off + x.numel():].any()
+        guard.zero_()
