@@ -8,7 +8,7 @@
 // node is non-decreasing in the output node, so the source window of an x-y
 // tile is one contiguous (wrapped) range per axis.
 //
-// Two kernels, forward and transposed, work by source cell (k_graded_cells);
+// Two kernels, forward and transposed, work by source cell (k_stream_graded_cells);
 // what they do not take (graded_by_cell) is marched, in either direction:
 // a block owns one (velocity, population) plane over a 32 x 8 x-y tile and a
 // range of output z-rows.  It walks the source z-rows in order, two at a
@@ -197,7 +197,7 @@ __host__ __device__ __forceinline__ int gc_row_waves(int Nx) { return (Nx + 63) 
 // 77 us in FP64 and 44 us in FP32.  The march above interpolates every source row out of
 // LDS with per-thread taps: 139 and 84 us.
 template <typename S, int P>
-__global__ void __launch_bounds__(64 * GCW) k_graded_cells(Geometry g, CellReaders<S> tab, const S *__restrict__ in,
+__global__ void __launch_bounds__(64 * GCW) k_stream_graded_cells(Geometry g, CellReaders<S> tab, const S *__restrict__ in,
                                                            S *__restrict__ out, int cw, int tyc, int nty, int rows)
 {
     constexpr int K = P + 1;
@@ -296,7 +296,7 @@ __global__ void __launch_bounds__(64 * GCW) k_graded_cells(Geometry g, CellReade
 // carried in registers (a block marches zcells cells and first reads the group
 // before them).  x is gathered out of LDS.
 template <typename S, int P, int MO>
-__global__ void __launch_bounds__(64 * GCW) k_graded_cells_t(Geometry g, CellReaders<S> tab, const S *__restrict__ in,
+__global__ void __launch_bounds__(64 * GCW) k_stream_graded_cells_t(Geometry g, CellReaders<S> tab, const S *__restrict__ in,
                                                              S *__restrict__ out, int cw, int tyc, int nty, int zcells,
                                                              int nchunk)
 {
@@ -446,7 +446,7 @@ hipError_t launch_gc(const Geometry &g, const CellReaders<S> &t, const S *in, S 
     const int rows = (t.my + 1) / 2 * 2;
     const int64_t nb = static_cast<int64_t>(b.nty) * g.nel[2];
     if (90 * nb > (int64_t(1) << 31) - 1) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((k_graded_cells<S, P>), dim3(static_cast<unsigned>(nb), 90), dim3(64 * b.cw * b.tyc),
+    hipLaunchKernelGGL((k_stream_graded_cells<S, P>), dim3(static_cast<unsigned>(nb), 90), dim3(64 * b.cw * b.tyc),
                        2 * sizeof(S) * b.tyc * rows * b.cw * 64, st, g, t, in, out, b.cw, b.tyc, b.nty, rows);
     return hipGetLastError();
 }
@@ -466,7 +466,7 @@ hipError_t launch_gct(const Geometry &g, const CellReaders<S> &t, const S *in, S
     const int nchunk = (g.nel[2] + zcells - 1) / zcells;
     const int64_t nb = static_cast<int64_t>(b.nty) * nchunk;
     if (90 * nb > (int64_t(1) << 31) - 1) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((k_graded_cells_t<S, P, MO>), dim3(static_cast<unsigned>(nb), 90), dim3(64 * b.cw * b.tyc),
+    hipLaunchKernelGGL((k_stream_graded_cells_t<S, P, MO>), dim3(static_cast<unsigned>(nb), 90), dim3(64 * b.cw * b.tyc),
                        0, st, g, t, in, out, b.cw, b.tyc, b.nty, zcells, nchunk);
     return hipGetLastError();
 }
