@@ -1,27 +1,20 @@
 // Two-dimensional semi-Lagrangian streaming (Sec. II A, Eqs. (8)-(9) with
-// D = 2) on a periodic mesh of equal cells: the D2Q19 counterpart of the
-// z-march of stream.hip, marching along y.
+// D = 2) on a periodic mesh of equal cells, by source cell: the D2Q19
+// counterpart of stream.hip.
 //
-// For velocity i the interpolant factorises into two 1-D operators; along an
-// axis output node e*P + l reads source cell e + o_l (o_l = omin for l <
-// lstar, omin + 1 otherwise) with the weight row of l.  A block owns one
-// (velocity, population) plane over an x-strip of TX nodes (whole cells) and
-// a chunk of cells along y:
-//   * each source row of the strip's window (TX + P + 1 nodes, 16-byte loads
-//     when the rows allow) is loaded once, the next batch of rows being in
-//     flight while the current one is interpolated along x out of LDS (one
-//     output column per thread, two LDS buffers, one barrier per batch);
-//   * a thread keeps the x-interpolated values of the two source cells that
-//     output cell e reads along y (2P + 1 rows) in registers, forms the P
-//     outputs of the cell with the velocity's uniform y weights and slides
-//     by one cell.
-// Rows are 2 KB long (FP64), so every load and store is a long coalesced
-// run; the x halo (P + 1 nodes) and the P + 1 rows a y-chunk re-reads are
-// the only reads beyond the algorithmic ones.
+// The outputs that read source cell c along an axis are P consecutive nodes,
+// (c - omin - 1)*P + lstar + j, j = 0 .. P-1, with weight row (lstar + j) mod P.
+// A lane takes one column (x) of NC source cells in a row along y: it loads their
+// NC*P + 1 nodes (all in flight at once), interpolates along y in registers with
+// the velocity's uniform weights and leaves NC*P values in LDS, from which the
+// block's lanes interpolate along x, one output column each.  While N_x <= 512 a
+// block holds whole periodic rows; longer rows are split into tiles of whole
+// cells (N_x <= 256 up to 65536 nodes).
 #include <hip/hip_runtime.h>
 
-#include <type_traits>
+#include <algorithm>
 
+#include "rows.h"
 #include "sllbm_internal.h"
 #include "xcd.h"
 
@@ -29,8 +22,7 @@ namespace sllbm {
 
 namespace {
 
-constexpr int Y_TARGET_BLOCKS = 1024;      // 512^2 nodes: 16-cell chunks, 608 blocks (2048: 5 % slower in FP64)
-constexpr int Y_MIN_CELLS = 4;
+constexpr int YNT = 512;                   // most threads per block
 
 __device__ __forceinline__ int wrap2(int x, int n)
 {
@@ -38,173 +30,151 @@ __device__ __forceinline__ int wrap2(int x, int n)
     return r < 0 ? r + n : r;
 }
 
-template <int P, int V>
-struct YStrip {
-    static constexpr int NT = 256;                        // threads: one output column each
-    static constexpr int TXC = NT / P;                    // cells per strip
-    static constexpr int TX = TXC * P;                    // nodes per strip
-    static constexpr int WX = TX + P + 1;                 // source window of a row
-    static constexpr int WXC = (WX + V - 1) / V;          // loads per row
-    static constexpr int WXP = WXC * V;                   // padded LDS row
-    static constexpr int LK = (WXC + NT - 1) / NT;        // loads per thread and row
+// source cells per lane
+template <int P>
+constexpr int y_cells()
+{
+    return P >= 5 ? 1 : P >= 3 ? 2 : P == 2 ? 4 : 8;
+}
+
+// tyg groups of NC cells along y and cx columns of each per block; txc cells
+// along x per tile (the whole row if ntx = 1); nt threads
+struct YLayout {
+    int cx, txc, tyg, ntx, nty, nt;
+    float rcx;
 };
 
-template <typename S, int V>
-struct Vec2 {
-    typedef S T __attribute__((ext_vector_type(V)));
-};
-template <typename S>
-struct Vec2<S, 1> {
-    typedef S T;
-};
+// the split with the fewest idle lanes
+YLayout y_layout(const Geometry &g, int nc)
+{
+    YLayout b{};
+    double best = 0.0;
+    const int most = g.nodes <= 65536 ? 256 : YNT;         // lanes; small grids need the blocks
+    const bool whole = g.N[0] <= most;
+    const int groups = (g.nel[1] + nc - 1) / nc;
+    const int t0 = whole ? g.nel[0] : 63 / g.p, t1 = whole ? g.nel[0] : (most - 1) / g.p;
+    for (int txc = t0; txc <= t1; ++txc) {
+        const int cx = whole ? g.N[0] : txc * g.p + 1, ntx = (g.nel[0] + txc - 1) / txc;
+        for (int tyg = 1; tyg <= groups && cx * tyg <= std::max(cx, 256); ++tyg) {
+            const int nt = (cx * tyg + 63) / 64 * 64, nty = (groups + tyg - 1) / tyg;
+            const double used = static_cast<double>(groups) * g.N[0] / (static_cast<double>(nt) * ntx * nty);
+            if (used >= best) {
+                best = used;
+                b = YLayout{cx, txc, tyg, ntx, nty, nt, 1.0f / static_cast<float>(cx)};
+            }
+        }
+    }
+    return b;
+}
 
 }  // namespace
 
-template <typename S, int P, int V>
-__global__ void __launch_bounds__(256) k_stream_y(Geometry g, CellTables<S> tab, const S *__restrict__ in,
-                                                  S *__restrict__ out, int nstrip, int ycells, int nchunk)
+// Bound by HBM and, while two states fit it, the Infinity Cache: 512^2 nodes, P =
+// 4, 24 us in FP64 (6.5 TB/s) and 14 us in FP32; 1024^2 115 us; 510^2 at P = 6 25 us.
+// The march along y that this replaces (strips of 256 columns, chunks of 16
+// cells, each row interpolated along x out of LDS) took 26, 17, 127 and 33 us.
+template <typename S, int P>
+__global__ void __launch_bounds__(YNT) k_stream_y(Geometry g, CellTables<S> tab, const S *__restrict__ in,
+                                                  S *__restrict__ out, YLayout lay)
 {
-    using Y = YStrip<P, V>;
-    using VT = typename Vec2<S, V>::T;
-    constexpr int NT = Y::NT, TX = Y::TX, WXP = Y::WXP, WXC = Y::WXC, LK = Y::LK;
-    // two buffers of one batch of rows (P + 1 for the first cell, P afterwards)
-    __shared__ __align__(16) S pl[2][P + 1][WXP];
-
+    constexpr int NC = y_cells<P>(), R = NC * P + 1;
+    __shared__ S buf[NC * P][YNT];
     const int tid = threadIdx.x;
-    const int L = __builtin_amdgcn_readfirstlane(xcd_linear(blockIdx.x, gridDim.x));
-    const int q = L / (nstrip * nchunk);
-    const int rem = L - q * nstrip * nchunk;
-    const int chunk = rem / nstrip, strip = rem - chunk * nstrip;
+    const int tiles = lay.ntx * lay.nty;
+    const int L = __builtin_amdgcn_readfirstlane(xcd_linear(static_cast<int>(blockIdx.y * gridDim.x + blockIdx.x),
+                                                            static_cast<int>(gridDim.x * gridDim.y)));
+    const int q = L / tiles, tile = L - q * tiles;
+    const int ty = tile / lay.ntx, tx = tile - ty * lay.ntx;
     const int i = q % Q2D, pop = q / Q2D;
-    const int X0 = strip * TX;
     const int Nx = g.N[0], Ny = g.N[1];
     const int64_t N = g.nodes;
     const int omx = tab.omin[i * 3 + 0], omy = tab.omin[i * 3 + 1];
     const int lsx = tab.lstar[i * 3 + 0], lsy = tab.lstar[i * 3 + 1];
     const S *Wx = tab.w + (i * 3 + 0) * P * (P + 1);
-    const S *Wy = tab.w + (i * 3 + 1) * P * (P + 1);
-    const S *__restrict__ src = in + static_cast<int64_t>(pop * Q2D + i) * N;
-    S *__restrict__ dst = out + static_cast<int64_t>(pop * Q2D + i) * N;
+    using CS = const __attribute__((address_space(4))) S;
+    CS *Wy = (CS *)(tab.w + (i * 3 + 1) * P * (P + 1));
+    const GlobalRow<S> src = plane_row(const_cast<S *>(in), static_cast<int64_t>(pop * Q2D + i) * N);
+    const GlobalRow<S> dst = plane_row(out, static_cast<int64_t>(pop * Q2D + i) * N);
 
-    // window loads of this thread: columns V*e .. V*e + V-1 of the window,
-    // which starts at source cell X0/P + omx
-    int loff[LK];
+    // exact quotient: (tid + 1/2) / cx lies at least 1 / (2 cx) from an integer
+    const int gl = static_cast<int>((static_cast<float>(tid) + 0.5f) * lay.rcx), xl = tid - gl * lay.cx;
+    const int cx0 = tx * lay.txc, ncx = min(lay.txc, g.nel[0] - cx0);
+    const bool whole = lay.ntx == 1;
+    const int c0 = (ty * lay.tyg + gl) * NC;               // this lane's cells along y: c0 .. c0 + NC - 1
+    int xs = cx0 * P + min(xl, whole ? Nx - 1 : ncx * P);
+    xs -= xs >= Nx ? Nx : 0;
+    S v[R];
 #pragma unroll
-    for (int k = 0; k < LK; ++k) {
-        int e = tid + k * NT;
-        e = e < WXC ? e : WXC - 1;                         // surplus lanes repeat the last load
-        loff[k] = wrap2(X0 + omx * P + V * e, Nx);
+    for (int r = 0; r < R; ++r) {
+        const int y = min(c0 * P + r, Ny);                 // past the last cell: its far face again, unused
+        v[r] = load_at<S>(src, plane_offset<S>((y == Ny ? 0 : y) * Nx + xs));
     }
-    // x-pass of this thread's output column X0 + tid: LDS offset of its
-    // source cell and its weight row
-    const int lx = tid % P;
-    const int xsrc = tid < TX ? (tid / P + (lx >= lsx ? 1 : 0)) * P : 0;   // surplus lanes read row start
-    const bool own = tid < TX && X0 + tid < Nx;
+    // output column and its taps in the block's row of columns
+    int xo, cell, row;
+    if (whole) {
+        xo = xl;
+        row = xl % P;
+        cell = xl / P + wrap2(omx, g.nel[0]) + (row >= lsx ? 1 : 0);
+        cell -= cell >= g.nel[0] ? g.nel[0] : 0;
+        cell -= cell >= g.nel[0] ? g.nel[0] : 0;
+    } else {
+        cell = xl / P;
+        const int j = lsx + xl % P;
+        row = j % P;
+        xo = wrap2((cx0 - omx - 1) * P, Nx) + cell * P + j;          // below 2 N_x + P
+        xo -= xo >= Nx ? Nx : 0;
+        xo -= xo >= Nx ? Nx : 0;
+    }
+    const bool own = gl < lay.tyg && xl < (whole ? Nx : ncx * P);
+    const int b0 = own ? gl * lay.cx + cell * P : 0;
+    const int bl = own && whole && cell + 1 == g.nel[0] ? gl * lay.cx : b0 + P;
     S xw[P + 1];
 #pragma unroll
-    for (int r = 0; r <= P; ++r) xw[r] = Wx[lx * (P + 1) + r];
-    S wy[P][P + 1];                                       // uniform y weights of this velocity
+    for (int r = 0; r <= P; ++r) xw[r] = Wx[row * (P + 1) + r];
 #pragma unroll
-    for (int l = 0; l < P; ++l)
+    for (int j = 0; j < P; ++j) {
+        S w[P + 1];
 #pragma unroll
-        for (int r = 0; r <= P; ++r) wy[l][r] = Wy[l * (P + 1) + r];
-
-    // output cells [ey0, ey1) along y; source rows in march order:
-    // y = (ey0 + omy) * P + k (mod Ny), k = 0 .. P + (ey1 - ey0) * P
-    const int ey0 = chunk * ycells, ey1 = min(g.nel[1], ey0 + ycells);
-    const int yb = (ey0 + omy) * P;
-    VT raw[P + 1][LK];
-    auto load_rows = [&](int k0, int nr) {
+        for (int m = 0; m <= P; ++m) w[m] = Wy[(lsy + j) % P * (P + 1) + m];
 #pragma unroll
-        for (int r = 0; r <= P; ++r) {
-            if (r < nr) {
-                const int64_t yo = static_cast<int64_t>(wrap2(yb + k0 + r, Ny)) * Nx;
+        for (int k = 0; k < NC; ++k) {
+            S a = w[0] * v[k * P];
 #pragma unroll
-                for (int j = 0; j < LK; ++j) raw[r][j] = *reinterpret_cast<const VT *>(src + yo + loff[j]);
-            }
+            for (int m = 1; m <= P; ++m) a = fma(w[m], v[k * P + m], a);
+            buf[k * P + j][tid] = a;
         }
-    };
-    // a batch of nr rows: registers -> LDS buffer b, the registers reloaded
-    // with the next batch, one barrier, the x-pass of every row
-    int b = 0;
-    auto batch = [&](auto nr_c, int next_k0, int next_nr, S *res) {
-        constexpr int NR = decltype(nr_c)::value;
+    }
+    __syncthreads();
+    int y = wrap2((ty * lay.tyg * NC - omy - 1) * P, Ny) + gl * NC * P + lsy;   // first output row
+    y -= y >= Ny ? Ny : 0;
+    y -= y >= Ny ? Ny : 0;
 #pragma unroll
-        for (int r = 0; r < NR; ++r)
+    for (int k = 0; k < NC; ++k) {
+        if (!own || c0 + k >= g.nel[1]) break;
 #pragma unroll
-            for (int j = 0; j < LK; ++j)
-                if (tid + j * NT < WXC) *reinterpret_cast<VT *>(&pl[b][r][V * (tid + j * NT)]) = raw[r][j];
-        if (next_nr > 0) load_rows(next_k0, next_nr);
-        __syncthreads();
+        for (int j = 0; j < P; ++j) {
+            const S *b = buf[k * P + j];
+            S a = 0;
 #pragma unroll
-        for (int r = 0; r < NR; ++r) {
-            const S *c = &pl[b][r][xsrc];
-            S acc = 0;
-#pragma unroll
-            for (int m = 0; m <= P; ++m) acc = fma(xw[m], c[m], acc);
-            res[r] = acc;
+            for (int r = 0; r < P; ++r) a = fma(xw[r], b[b0 + r], a);
+            a = fma(xw[P], b[bl], a);
+            store_at<false, S>(dst, plane_offset<S>(y * Nx + xo), a);
+            y = y + 1 == Ny ? 0 : y + 1;
         }
-        b ^= 1;
-    };
-    // P outputs of cell ey along y from the rows in a, then slide by one cell
-    S a[2 * P + 1];
-    auto emit = [&](int ey) {
-        if (own) {
-#pragma unroll
-            for (int l = 0; l < P; ++l) {
-                const bool hi = l >= lsy;
-                S acc = 0;
-#pragma unroll
-                for (int r = 0; r <= P; ++r) acc = fma(wy[l][r], hi ? a[P + r] : a[r], acc);
-                dst[static_cast<int64_t>(ey * P + l) * Nx + X0 + tid] = acc;
-            }
-        }
-#pragma unroll
-        for (int r = 0; r <= P; ++r) a[r] = a[r + P];
-    };
-
-    const int nel = ey1 - ey0;
-    auto rows_of = [&](int e) { return e < nel ? P : 0; };
-    load_rows(0, P + 1);
-    batch(std::integral_constant<int, P + 1>(), P + 1, rows_of(0), a);
-    for (int e = 0; e < nel; ++e) {
-        batch(std::integral_constant<int, P>(), P + 1 + (e + 1) * P, rows_of(e + 1), a + P + 1);
-        emit(ey0 + e);
     }
 }
 
 namespace {
 
-template <typename S, int P, int V>
-hipError_t launch_yv(const Geometry &g, const CellTables<S> &t, const S *in, S *out, hipStream_t st)
-{
-    using Y = YStrip<P, V>;
-    const int nstrip = (g.N[0] + Y::TX - 1) / Y::TX;
-    // split the y-march into chunks until the grid has a few blocks per CU
-    // slot (each chunk re-reads P + 1 source rows)
-    int nchunk = 1;
-    while (nchunk < g.nel[1] && static_cast<int64_t>(nstrip) * 2 * Q2D * nchunk < Y_TARGET_BLOCKS &&
-           g.nel[1] / (2 * nchunk) >= Y_MIN_CELLS)
-        nchunk *= 2;
-    const int ycells = (g.nel[1] + nchunk - 1) / nchunk;
-    nchunk = (g.nel[1] + ycells - 1) / ycells;
-    const int64_t nb = static_cast<int64_t>(nstrip) * 2 * Q2D * nchunk;
-    if (nb > (int64_t(1) << 31) - 1) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((k_stream_y<S, P, V>), dim3(static_cast<unsigned>(nb)), dim3(Y::NT), 0, st, g, t, in, out,
-                       nstrip, ycells, nchunk);
-    return hipGetLastError();
-}
-
-// 16-byte window loads when every window row starts on a 16-byte boundary
 template <typename S, int P>
 hipError_t launch_y(const Geometry &g, const CellTables<S> &t, const S *in, S *out, hipStream_t st)
 {
-    constexpr int V = 16 / sizeof(S);
-    const bool aligned = (g.N[0] * sizeof(S)) % 16 == 0 && reinterpret_cast<uintptr_t>(in) % 16 == 0;
-    if constexpr ((P * sizeof(S)) % 16 == 0 && YStrip<P, V>::TX % V == 0) {
-        if (aligned) return launch_yv<S, P, V>(g, t, in, out, st);
-    }
-    return launch_yv<S, P, 1>(g, t, in, out, st);
+    const YLayout lay = y_layout(g, y_cells<P>());
+    const int64_t nb = static_cast<int64_t>(lay.ntx) * lay.nty;
+    if (2 * Q2D * nb > (int64_t(1) << 31) - 1) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((k_stream_y<S, P>), dim3(static_cast<unsigned>(nb), 2 * Q2D), dim3(lay.nt), 0, st, g, t, in, out,
+                       lay);
+    return hipGetLastError();
 }
 
 }  // namespace

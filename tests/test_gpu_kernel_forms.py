@@ -240,3 +240,27 @@ def test_large_state_copies(n_el, precision):
         assert torch.equal(out, x)
         assert not guard[:off].any() and not guard[off + x.numel():].any()
         guard.zero_()
+
+
+# whole rows up to 256 nodes (512 beyond 65536 nodes in all) and split ones, a
+# ragged last tile, groups of cells along y with a remainder, one-cell axes,
+# shifts of several cells
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("n_el,p,shift", [((1, 1), 4, 0.7), ((64, 2), 4, 0.3), ((65, 3), 4, 2.3), ((512, 130), 1, 0.4),
+                                          ((513, 130), 1, 1.7), ((129, 5), 2, 0.2), ((2, 41), 2, 3.1), ((13, 11), 3, 0.9),
+                                          ((86, 3), 3, 0.1), ((103, 2), 5, 0.6), ((3, 70), 6, 1.2), ((43, 2), 6, 0.1)])
+def test_streaming_2d_by_source_cell(precision, n_el, p, shift):
+    """Two-dimensional streaming against its oracle (1e-12, FP32 1e-5: the
+    repository's bars); shift: largest displacement in cells along x."""
+    from oracle import oracle2d as O2
+    from paper_2012_05537_amd.sllbm import CONSTANT, D2Q19, SLLBM
+    dt = shift / n_el[0] / 3.5
+    length = (1.0, 0.7 * n_el[1] / n_el[0])
+    ctx = SLLBM(n_el, p, dt, 1e-3, length=length, viscosity_law=CONSTANT, precision=precision, velocity_set=D2Q19)
+    cfg = O2.make_cfg(n_el, p, dt, 1e-3, length=length, viscosity_law=O2.CONSTANT)
+    x = np.random.default_rng(9).normal(size=(2, 19, ctx.nodes)).astype(np.float32).astype(np.float64)
+    print("2-D streaming form", precision, n_el, p, flush=True)
+    F, G = to_np(ctx.stream(to_dev(ctx, x[0], x[1])))
+    f, g = O2.stream(cfg, x[0], x[1])
+    tol = 1e-5 if precision else 1e-12
+    assert rel_err(F, f) < tol and rel_err(G, g) < tol
