@@ -48,36 +48,66 @@ __device__ __forceinline__ void lagrange_weights(const GlcBasis &gb, const doubl
     }
 }
 
-// acc += (element J of src) * w, J = the lane of its 16-lane row that holds
-// the element (row_newbcast).
-template <int J>
-__device__ __forceinline__ void fmac_row(double &acc, double src, double w)
-{
-    asm("v_fmac_f64_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(acc) : "v"(src), "v"(w), "n"(J));
-}
-template <int J>
-__device__ __forceinline__ void fmac_row(float &acc, float src, float w)
-{
-    asm("v_fmac_f32_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(acc) : "v"(src), "v"(w), "n"(J));
-}
+// G elements (4 or 5) of a cell and their weights: f into a0, a1 in turn, g into
+// b0, b1.  Element k sits in lane (E + k) % 16 of its 16-lane row and enters its
+// FMAs as a row broadcast (row_newbcast).  A register that a vector instruction
+// wrote may be read by such an FMA no less than two wait states later, and the
+// compiler does not see into the block: the s_nop covers whatever is written before
+// it (values, weights, cleared sums, copies, reloads), and inside it the FMAs of
+// one sum have three others between them.
+#define SLLBM_ROW_FMA(OP, ACC, SRC, W, LANE) \
+    OP " %" #ACC ", %" #SRC ", %" #W " row_newbcast:%" #LANE " row_mask:0xf bank_mask:0xf\n\t"
+#define SLLBM_ROW_FMAS(S, OP)                                                                                         \
+    template <int E, int G, int NR, int NW>                                                                           \
+    __device__ __forceinline__ void fma_rows(S &a0, S &a1, S &b0, S &b1, const S (&vf)[NR], const S (&vg)[NR],        \
+                                             const S (&w)[NW], int wi)                                                \
+    {                                                                                                                 \
+        static_assert(G == 4 || G == 5, "elements per block");                                                        \
+        if constexpr (G == 4)                                                                                         \
+            asm("s_nop 1\n\t"                                                                                         \
+                SLLBM_ROW_FMA(OP, 0, 4, 12, 16) SLLBM_ROW_FMA(OP, 2, 8, 12, 16)                                       \
+                SLLBM_ROW_FMA(OP, 1, 5, 13, 17) SLLBM_ROW_FMA(OP, 3, 9, 13, 17)                                       \
+                SLLBM_ROW_FMA(OP, 0, 6, 14, 18) SLLBM_ROW_FMA(OP, 2, 10, 14, 18)                                      \
+                SLLBM_ROW_FMA(OP, 1, 7, 15, 19) SLLBM_ROW_FMA(OP, 3, 11, 15, 19)                                      \
+                : "+&v"(a0), "+&v"(a1), "+&v"(b0), "+&v"(b1)                                                          \
+                : "v"(vf[E / 16]), "v"(vf[(E + 1) / 16]), "v"(vf[(E + 2) / 16]), "v"(vf[(E + 3) / 16]),               \
+                  "v"(vg[E / 16]), "v"(vg[(E + 1) / 16]), "v"(vg[(E + 2) / 16]), "v"(vg[(E + 3) / 16]),               \
+                  "v"(w[wi]), "v"(w[wi + 1]), "v"(w[wi + 2]), "v"(w[wi + 3]),                                         \
+                  "n"(E % 16), "n"((E + 1) % 16), "n"((E + 2) % 16), "n"((E + 3) % 16));                              \
+        else                                                                                                          \
+            asm("s_nop 1\n\t"                                                                                         \
+                SLLBM_ROW_FMA(OP, 0, 4, 14, 19) SLLBM_ROW_FMA(OP, 2, 9, 14, 19)                                       \
+                SLLBM_ROW_FMA(OP, 1, 5, 15, 20) SLLBM_ROW_FMA(OP, 3, 10, 15, 20)                                      \
+                SLLBM_ROW_FMA(OP, 0, 6, 16, 21) SLLBM_ROW_FMA(OP, 2, 11, 16, 21)                                      \
+                SLLBM_ROW_FMA(OP, 1, 7, 17, 22) SLLBM_ROW_FMA(OP, 3, 12, 17, 22)                                      \
+                SLLBM_ROW_FMA(OP, 0, 8, 18, 23) SLLBM_ROW_FMA(OP, 2, 13, 18, 23)                                      \
+                : "+&v"(a0), "+&v"(a1), "+&v"(b0), "+&v"(b1)                                                          \
+                : "v"(vf[E / 16]), "v"(vf[(E + 1) / 16]), "v"(vf[(E + 2) / 16]), "v"(vf[(E + 3) / 16]),               \
+                  "v"(vf[(E + 4) / 16]), "v"(vg[E / 16]), "v"(vg[(E + 1) / 16]), "v"(vg[(E + 2) / 16]),               \
+                  "v"(vg[(E + 3) / 16]), "v"(vg[(E + 4) / 16]), "v"(w[wi]), "v"(w[wi + 1]), "v"(w[wi + 2]),           \
+                  "v"(w[wi + 3]), "v"(w[wi + 4]), "n"(E % 16), "n"((E + 1) % 16), "n"((E + 2) % 16),                  \
+                  "n"((E + 3) % 16), "n"((E + 4) % 16));                                                              \
+    }
+SLLBM_ROW_FMAS(double, "v_fmac_f64_dpp")
+SLLBM_ROW_FMAS(float, "v_fmac_f32_dpp")
+#undef SLLBM_ROW_FMAS
+#undef SLLBM_ROW_FMA
 
 // sf, sg += sum over the cell's elements E, E + 1, ... of weight times value.
 // z: sums of the current z plane so far, two for f and two for g (element
-// pairs alternate), so that four chains are in flight: a chain's next
-// broadcast FMA must not follow within two wait states.
+// pairs alternate).
 template <typename S, int P, int E, int NR>
 __device__ __forceinline__ void cell_sum(const S (&vf)[NR], const S (&vg)[NR], const S (&wxy)[(P + 1) * (P + 1)],
                                          const S (&wz)[P + 1], S (&z)[4], S &sf, S &sg)
 {
-    constexpr int K = P + 1, K2 = K * K;
-    fmac_row<E % 16>(z[E % K2 % 2], vf[E / 16], wxy[E % K2]);
-    fmac_row<E % 16>(z[2 + E % K2 % 2], vg[E / 16], wxy[E % K2]);
-    if constexpr (E % K2 == K2 - 1) {
+    constexpr int K = P + 1, K2 = K * K, e = E % K2, G = (K2 - e) % 4 == 0 ? 4 : 5;
+    fma_rows<E, G>(z[e % 2], z[1 - e % 2], z[2 + e % 2], z[3 - e % 2], vf, vg, wxy, e);
+    if constexpr (e + G == K2) {
         sf = fma(wz[E / K2], z[0] + z[1], sf);
         sg = fma(wz[E / K2], z[2] + z[3], sg);
         z[0] = z[1] = z[2] = z[3] = 0;
     }
-    if constexpr (E + 1 < K2 * K) cell_sum<S, P, E + 1>(vf, vg, wxy, wz, z, sf, sg);
+    if constexpr (E + G < K2 * K) cell_sum<S, P, E + G>(vf, vg, wxy, wz, z, sf, sg);
 }
 
 // Streaming by departure cell.  A block owns one velocity and a run of cells
@@ -187,11 +217,6 @@ __global__ void __launch_bounds__(256, P <= 4 ? 4 : 2)
 #pragma unroll
             for (int x = 0; x < K; ++x) wxy[y * K + x] = w[1][y] * w[0][x];
         S sf = 0, sg = 0, z[4] = {0, 0, 0, 0};
-        // a broadcast may follow a vector write of its source by no less than two
-        // wait states; what writes vf and vg is finished before this
-#pragma unroll
-        for (int r = 0; r < NR; ++r) asm volatile("" : "+v"(vf[r]), "+v"(vg[r]));
-        asm volatile("s_nop 1");
         cell_sum<S, P, 0>(vf, vg, wxy, w[2], z, sf, sg);
         if (j < count) {
             fo[n] = sf;
