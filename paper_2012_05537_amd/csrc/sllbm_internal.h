@@ -181,6 +181,9 @@ struct MappedRuns {
     int width;      // nodes of a staged row: cells * p + 1, made odd (LDS banks)
 };
 MappedRuns mapped_runs(int p, int nel_x, size_t elem);
+// Its grid, runs x Q blocks of 256 threads; false where HIP cannot launch it (a
+// grid dimension has less than 2^32 threads, and the kernel counts blocks in 31 bits).
+bool mapped_run_grid(const MappedRuns &r, const int nel[3], unsigned &runs);
 // Chunks of the streaming by departure cell: the inverse lists (start of
 // build_mapped_inverse) cut into pieces of up to 16 nodes of one cell, as pairs
 // (cell in its run | count << 8, first list position), nch (returned) places

@@ -138,7 +138,8 @@ __global__ void __launch_bounds__(256, P <= 4 ? 4 : 2)
     using S2 = typename MVec<S, 2>::T;
     extern __shared__ __align__(16) unsigned char smem[];
     S2 *lw = reinterpret_cast<S2 *>(smem);                 // [K][K][width] f and g of the run's window
-    const int L = __builtin_amdgcn_readfirstlane(xcd_linear(blockIdx.x, gridDim.x));
+    const int L = __builtin_amdgcn_readfirstlane(xcd_linear(static_cast<int>(blockIdx.y * gridDim.x + blockIdx.x),
+                                                            static_cast<int>(gridDim.x * gridDim.y)));
     const int nruns = runs.nx * g.nel[1] * g.nel[2];
     const int i = L / nruns, run = L - i * nruns;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -495,11 +496,11 @@ template <typename S, int P>
 hipError_t launch_m(const Geometry &g, const MappedTables &t, const S *in, S *out, hipStream_t st)
 {
     if constexpr (P >= MAPPED_LIST_ORDER) {
-        const int64_t blocks = static_cast<int64_t>(Q) * t.runs.nx * g.nel[1] * g.nel[2];
-        if (blocks > (int64_t(1) << 31) - 1) return hipErrorInvalidValue;
+        unsigned runs;
+        if (!mapped_run_grid(t.runs, g.nel, runs)) return hipErrorInvalidValue;
         const size_t lds = 2 * static_cast<size_t>(P + 1) * (P + 1) * t.runs.width * sizeof(S);
-        hipLaunchKernelGGL((k_stream_mapped_cells<S, P>), dim3(static_cast<unsigned>(blocks)), dim3(256), lds, st, g,
-                           t.basis, t.runs, t.inv_order, reinterpret_cast<const int2 *>(t.chunk), t.nch, t.rstart,
+        hipLaunchKernelGGL((k_stream_mapped_cells<S, P>), dim3(runs, Q), dim3(256), lds, st, g, t.basis,
+                           t.runs, t.inv_order, reinterpret_cast<const int2 *>(t.chunk), t.nch, t.rstart,
                            static_cast<const S *>(t.tloc), in, out);
         return hipGetLastError();
     } else {

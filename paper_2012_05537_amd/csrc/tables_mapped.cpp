@@ -292,6 +292,13 @@ MappedRuns mapped_runs(int p, int nel_x, size_t elem)
     return r;
 }
 
+bool mapped_run_grid(const MappedRuns &r, const int nel[3], unsigned &runs)
+{
+    const int64_t n = static_cast<int64_t>(r.nx) * nel[1] * nel[2];
+    runs = static_cast<unsigned>(n);
+    return n * 256 < (int64_t(1) << 32) && n * Q <= (int64_t(1) << 31) - 1;
+}
+
 int build_mapped_chunks(int q, const int nel[3], const MappedRuns &runs, const std::vector<int32_t> &start,
                         std::vector<int32_t> &chunk, std::vector<int32_t> &rstart)
 {
