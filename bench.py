@@ -35,10 +35,10 @@ Q = 45
 # sources that determine each timed kernel, besides the headers of csrc/ that
 # they include (a change in any of them voids committed counters)
 KERNEL_SOURCES = {
-    "k_stream_z": ("stream.hip", "tables.cpp"),
+    "k_stream_z": ("stream.hip", "layouts.cpp", "tables.cpp"),
     "k_stream_graded": ("stream_graded.hip", "tables.cpp"),
     "k_collide": ("kernels.hip", "collision.h", "velset.h"),
-    "k_stream_y": ("stream2d.hip", "tables.cpp"),
+    "k_stream_y": ("stream2d.hip", "layouts.cpp", "tables.cpp"),
     "k_stream_mapped": ("stream_mapped.hip", "tables_mapped.cpp"),
 }
 

@@ -10,6 +10,7 @@
 #include <string>
 #include <vector>
 
+#include "layouts.h"
 #include "sllbm_internal.h"
 
 using namespace sllbm;
@@ -25,6 +26,8 @@ std::string g_create_error;
 struct sllbm_ctx {
     sllbm_config cfg{};
     Geometry geo{};
+    ZLayout zlay[2]{};            // S and S^T on equal cells
+    YLayout ylay{};               // S in two dimensions
     VelocitySet vs{};
     CollisionParams cp{};
     int32_t *d_omin = nullptr, *d_lstar = nullptr;
@@ -486,6 +489,10 @@ int sllbm_create(const sllbm_config *cfg, sllbm_ctx **out)
     }
     if (d2) g.N[2] = 1;                       // one node across z
     g.nodes = nodes;
+    if (d2)
+        c->ylay = y_layout(g);
+    else
+        for (int t = 0; t < 2; ++t) c->zlay[t] = z_layout(g, t == 1, c->elem);
     c->cp.dt = cfg->dt;
     c->cp.Cv = 1.0 / (cfg->gamma - 1.0);
     c->cp.beta = 2.0 * c->cp.Cv - (d2 ? 2.0 : 3.0);   // g^eq = (2 C_v - D) T f^eq
@@ -883,16 +890,16 @@ static hipError_t stream_into(sllbm_ctx *c, const void *in, void *out)
     }
     if (c->d2) {
         if (is_fp64(c))
-            return launch_stream_2d<double>(c->geo, cell_tables<double>(c), static_cast<const double *>(in),
+            return launch_stream_2d<double>(c->geo, cell_tables<double>(c), c->ylay, static_cast<const double *>(in),
                                             static_cast<double *>(out), c->stream);
-        return launch_stream_2d<float>(c->geo, cell_tables<float>(c), static_cast<const float *>(in),
+        return launch_stream_2d<float>(c->geo, cell_tables<float>(c), c->ylay, static_cast<const float *>(in),
                                        static_cast<float *>(out), c->stream);
     }
     if (c->graded) return stream_graded_into(c, in, out, 0);
     if (is_fp64(c))
-        return launch_stream_z<double>(c->geo, cell_tables<double>(c), static_cast<const double *>(in),
+        return launch_stream_z<double>(c->geo, cell_tables<double>(c), c->zlay[0], static_cast<const double *>(in),
                                        static_cast<double *>(out), c->stream);
-    return launch_stream_z<float>(c->geo, cell_tables<float>(c), static_cast<const float *>(in),
+    return launch_stream_z<float>(c->geo, cell_tables<float>(c), c->zlay[0], static_cast<const float *>(in),
                                   static_cast<float *>(out), c->stream);
 }
 
@@ -909,9 +916,9 @@ static hipError_t stream_t_into(sllbm_ctx *c, const void *in, void *out)
     }
     if (c->graded) return stream_graded_into(c, in, out, 1);
     if (is_fp64(c))
-        return launch_stream_zt<double>(c->geo, cell_tables<double>(c), static_cast<const double *>(in),
+        return launch_stream_zt<double>(c->geo, cell_tables<double>(c), c->zlay[1], static_cast<const double *>(in),
                                         static_cast<double *>(out), c->stream);
-    return launch_stream_zt<float>(c->geo, cell_tables<float>(c), static_cast<const float *>(in),
+    return launch_stream_zt<float>(c->geo, cell_tables<float>(c), c->zlay[1], static_cast<const float *>(in),
                                    static_cast<float *>(out), c->stream);
 }
 

@@ -278,8 +278,6 @@ struct Launch2D {
                              double *out5, hipStream_t st);
 };
 
-// two-dimensional streaming (stream2d.hip): per (velocity, population)
-// plane, x-strips marching along y
 // Mode algebra of the gradient workload (modes.hip).
 constexpr int MAX_MODES = 64;
 struct ModeAmplitudes {
@@ -293,16 +291,22 @@ hipError_t launch_superpose(int64_t n, int m, const ModeAmplitudes &am, const do
 hipError_t launch_project_chunk(int64_t n, int m0, int mc, const double *basis, const double *v, double *partials,
                                 int nblocks, double *out8, hipStream_t st);
 
+// Streaming on equal cells; the layouts (layouts.h) are of g, the kernel and S.
+struct ZLayout;
+struct YLayout;
+// two-dimensional streaming by source cell (stream2d.hip)
 template <typename S>
-hipError_t launch_stream_2d(const Geometry &g, const CellTables<S> &t, const S *in, S *out, hipStream_t st);
-
-// forward streaming, z-march per (velocity, population) plane and x-y tile (stream.hip)
+hipError_t launch_stream_2d(const Geometry &g, const CellTables<S> &t, const YLayout &lay, const S *in, S *out,
+                            hipStream_t st);
+// forward streaming by source cell (stream.hip)
 template <typename S>
-hipError_t launch_stream_z(const Geometry &g, const CellTables<S> &t, const S *in, S *out, hipStream_t st);
-// transposed streaming S^T, the same march gathering over source-cell groups
-// with the forward cell tables (stream.hip); any number of cells per axis
+hipError_t launch_stream_z(const Geometry &g, const CellTables<S> &t, const ZLayout &lay, const S *in, S *out,
+                           hipStream_t st);
+// transposed streaming S^T by output cell, with the forward cell tables
+// (stream.hip); any number of cells per axis
 template <typename S>
-hipError_t launch_stream_zt(const Geometry &g, const CellTables<S> &t, const S *in, S *out, hipStream_t st);
+hipError_t launch_stream_zt(const Geometry &g, const CellTables<S> &t, const ZLayout &lay, const S *in, S *out,
+                           hipStream_t st);
 // copy of a state (this device's memory, 16-byte aligned, bytes a multiple of 4),
 // and when it is used
 bool use_copy_kernel(size_t bytes, const void *dst, const void *src);

@@ -14,9 +14,9 @@
 // block's lanes interpolate along x, one output column each.
 #include <hip/hip_runtime.h>
 
-#include <algorithm>
 #include <type_traits>
 
+#include "layouts.h"
 #include "nt.h"
 #include "rows.h"
 #include "sllbm_internal.h"
@@ -32,74 +32,7 @@ __device__ __forceinline__ int wrapi(int x, int n)
     return r < 0 ? r + n : r;
 }
 
-// How an x-y plane is dealt to blocks and lanes.  A block holds tyc cells
-// along y and cx columns of each.  While x rows fit a block (N_x <= ZNT),
-// cx = N_x: the periodic row is complete and lane x writes output column x.
-// Longer rows are split into tiles of txc cells; a tile has halo columns more
-// than it writes (forward: the last cell's far face; transposed: the group
-// before the tile).
-struct ZLayout {
-    int cx, txc, tyc, ntx, nty, nt;   // nt: threads per block
-    float rcx;                        // 1 / cx
-    int zcells, nchunk;               // cells along z per block, blocks along z
-};
-
-constexpr int ZNT = 256;              // most threads per block
-
-// the split with the fewest idle lanes
-ZLayout z_layout(const Geometry &g, int halo)
-{
-    ZLayout b{};
-    double best = 0.0;
-    const bool whole = g.N[0] <= ZNT;
-    const int t0 = whole ? g.nel[0] : (64 - halo) / g.p, t1 = whole ? g.nel[0] : (ZNT - halo) / g.p;
-    for (int txc = t0; txc <= t1; ++txc) {
-        const int cx = whole ? g.N[0] : txc * g.p + halo;
-        const int ntx = (g.nel[0] + txc - 1) / txc;
-        for (int tyc = 1; tyc <= g.nel[1] && cx * tyc <= ZNT; ++tyc) {
-            const int nt = (cx * tyc + 63) / 64 * 64, nty = (g.nel[1] + tyc - 1) / tyc;
-            const double used = static_cast<double>(g.nel[1]) * g.N[0] / (static_cast<double>(nt) * ntx * nty);
-            if (used >= best) {
-                best = used;
-                b = ZLayout{cx, txc, tyc, ntx, nty, nt, 1.0f / static_cast<float>(cx), 0, 0};
-            }
-        }
-    }
-    return b;
-}
-
-// Cells along z per block: at most max_cells, fewer while the grid has fewer
-// than Z_TARGET_BLOCKS blocks of 256 threads, five per CU (transposed kernel,
-// 64^3 nodes, FP64: 86, 85 and 92 us with 2, 4 and 8 blocks per CU).
-constexpr int Z_TARGET_BLOCKS = 1280;
-
-// nblocks: blocks per plane (the grid is nblocks x 90: with one dimension its
-// threads would pass 2^32 on the largest grids)
-bool z_split(const Geometry &g, int max_cells, ZLayout &b, unsigned &nblocks)
-{
-    const int64_t tiles = static_cast<int64_t>(b.ntx) * b.nty;
-    const int64_t want = (static_cast<int64_t>(Z_TARGET_BLOCKS) * ZNT / b.nt + 90 * tiles - 1) / (90 * tiles);
-    const int n = std::max(static_cast<int>(std::min<int64_t>(g.nel[2], want)), (g.nel[2] + max_cells - 1) / max_cells);
-    b.zcells = (g.nel[2] + n - 1) / n;
-    b.nchunk = (g.nel[2] + b.zcells - 1) / b.zcells;
-    nblocks = static_cast<unsigned>(tiles * b.nchunk);
-    return 90 * tiles * b.nchunk <= (int64_t(1) << 31) - 1;
-}
-
 }  // namespace
-
-// Cells along z per block of the forward kernel.  One source cell from order 3
-// on: every load of a block is then in flight at once, and the blocks of an
-// XCD cover a thin slab whose shared faces meet in its L2 (256^3 nodes, P = 4,
-// FP64: 4.11 ms; marching 4, 16 or 64 cells with the next cell's rows in
-// flight 4.28, 4.38 and 4.79 ms).  Cells of order 1 and 2 are too small for
-// that and are marched (48 x 40 x 40 nodes, P = 2: 17.8 us with two cells, 20.8
-// with one; 100 x 100 x 30, P = 1, FP32: 51 us with 30, 214 with one).
-template <int P>
-constexpr int z_max_cells()
-{
-    return P >= 3 ? 1 : P == 2 ? 2 : 32;
-}
 
 template <typename S, int P>
 constexpr int z_min_waves()
@@ -280,7 +213,7 @@ __global__ void __launch_bounds__(ZNT, (z_min_waves<S, P>())) k_stream_z(Geometr
     // the first cell outside the loop: entered from it, the loop's waits for a
     // row need not assume that no stores are in flight after the row's loads
     int c = zc0;
-    if constexpr (z_max_cells<P>() > 1) {
+    if constexpr (z_max_cells(P) > 1) {
         if (c < zc1 - 1) {
             cell_step(std::false_type(), c);
             __syncthreads();
@@ -294,15 +227,14 @@ __global__ void __launch_bounds__(ZNT, (z_min_waves<S, P>())) k_stream_z(Geometr
 }
 
 template <typename S, int P>
-static hipError_t launch_z(const Geometry &g, const CellTables<S> &t, const S *in, S *out, hipStream_t st)
+static hipError_t launch_z(const Geometry &g, const CellTables<S> &t, const ZLayout &lay, const S *in, S *out,
+                           hipStream_t st)
 {
-    ZLayout lay = z_layout(g, 1);
-    unsigned nb;
-    if (!z_split(g, z_max_cells<P>(), lay, nb)) return hipErrorInvalidValue;
+    if (lay.blocks == 0) return hipErrorInvalidValue;
     if (use_nontemporal(90 * g.nodes * static_cast<int64_t>(sizeof(S)), g.N[0] * static_cast<int64_t>(sizeof(S))))
-        hipLaunchKernelGGL((k_stream_z<S, P, true>), dim3(nb, 90), dim3(lay.nt), 0, st, g, t, in, out, lay);
+        hipLaunchKernelGGL((k_stream_z<S, P, true>), dim3(lay.blocks, 90), dim3(lay.nt), 0, st, g, t, in, out, lay);
     else
-        hipLaunchKernelGGL((k_stream_z<S, P, false>), dim3(nb, 90), dim3(lay.nt), 0, st, g, t, in, out, lay);
+        hipLaunchKernelGGL((k_stream_z<S, P, false>), dim3(lay.blocks, 90), dim3(lay.nt), 0, st, g, t, in, out, lay);
     return hipGetLastError();
 }
 
@@ -321,16 +253,6 @@ static hipError_t launch_z(const Geometry &g, const CellTables<S> &t, const S *i
 // what a group adds to the next cell's node 0 stays in registers, and only a
 // block's first cell reads its preceding group again.
 // ---------------------------------------------------------------------------
-
-// Cells along z per block: the P rows read again per block against the
-// parallelism (P = 4: FP64, 256^3 nodes, 5.83, 4.98, 4.58, 4.41 and 4.37 ms with 1, 2, 4,
-// 8 and 32 cells, 128^3 615 us with 4 and 8; FP32, four rows in flight, 128^3 290 us
-// with 4 and 300 with 8; P = 1, 100 x 100 x 30: 93 us with 4, 41 us with 30)
-template <typename S, int P>
-constexpr int zt_max_cells()
-{
-    return P == 1 ? 32 : sizeof(S) == 8 ? 8 : 4;
-}
 
 // Rows in flight ahead of the one being processed (divides P), as registers
 // allow: P = 4 in FP32 at 128^3 nodes 301, 299 and 290 us with 1, 2 and 4 rows,
@@ -532,54 +454,55 @@ __global__ void __launch_bounds__(ZNT, (zt_min_waves<S, P>())) k_stream_zt(Geome
 }
 
 template <typename S, int P>
-static hipError_t launch_zt(const Geometry &g, const CellTables<S> &t, const S *in, S *out, hipStream_t st)
+static hipError_t launch_zt(const Geometry &g, const CellTables<S> &t, const ZLayout &lay, const S *in, S *out,
+                           hipStream_t st)
 {
-    ZLayout lay = z_layout(g, P);
-    unsigned nb;
-    if (!z_split(g, zt_max_cells<S, P>(), lay, nb)) return hipErrorInvalidValue;
+    if (lay.blocks == 0) return hipErrorInvalidValue;
     if (use_nontemporal(90 * g.nodes * static_cast<int64_t>(sizeof(S)), g.N[0] * static_cast<int64_t>(sizeof(S))))
-        hipLaunchKernelGGL((k_stream_zt<S, P, true>), dim3(nb, 90), dim3(lay.nt), 0, st, g, t, in, out, lay);
+        hipLaunchKernelGGL((k_stream_zt<S, P, true>), dim3(lay.blocks, 90), dim3(lay.nt), 0, st, g, t, in, out, lay);
     else
-        hipLaunchKernelGGL((k_stream_zt<S, P, false>), dim3(nb, 90), dim3(lay.nt), 0, st, g, t, in, out, lay);
+        hipLaunchKernelGGL((k_stream_zt<S, P, false>), dim3(lay.blocks, 90), dim3(lay.nt), 0, st, g, t, in, out, lay);
     return hipGetLastError();
 }
 
 template <typename S>
-hipError_t launch_stream_zt(const Geometry &g, const CellTables<S> &t, const S *in, S *out, hipStream_t st)
+hipError_t launch_stream_zt(const Geometry &g, const CellTables<S> &t, const ZLayout &lay, const S *in, S *out,
+                           hipStream_t st)
 {
     switch (g.p) {
-    case 1: return launch_zt<S, 1>(g, t, in, out, st);
-    case 2: return launch_zt<S, 2>(g, t, in, out, st);
-    case 3: return launch_zt<S, 3>(g, t, in, out, st);
-    case 4: return launch_zt<S, 4>(g, t, in, out, st);
-    case 5: return launch_zt<S, 5>(g, t, in, out, st);
-    case 6: return launch_zt<S, 6>(g, t, in, out, st);
+    case 1: return launch_zt<S, 1>(g, t, lay, in, out, st);
+    case 2: return launch_zt<S, 2>(g, t, lay, in, out, st);
+    case 3: return launch_zt<S, 3>(g, t, lay, in, out, st);
+    case 4: return launch_zt<S, 4>(g, t, lay, in, out, st);
+    case 5: return launch_zt<S, 5>(g, t, lay, in, out, st);
+    case 6: return launch_zt<S, 6>(g, t, lay, in, out, st);
     default: return hipErrorInvalidValue;
     }
 }
 
-template hipError_t launch_stream_zt<double>(const Geometry &, const CellTables<double> &, const double *, double *,
-                                             hipStream_t);
-template hipError_t launch_stream_zt<float>(const Geometry &, const CellTables<float> &, const float *, float *,
-                                            hipStream_t);
+template hipError_t launch_stream_zt<double>(const Geometry &, const CellTables<double> &, const ZLayout &, const double *,
+                                           double *, hipStream_t);
+template hipError_t launch_stream_zt<float>(const Geometry &, const CellTables<float> &, const ZLayout &, const float *,
+                                           float *, hipStream_t);
 
 template <typename S>
-hipError_t launch_stream_z(const Geometry &g, const CellTables<S> &t, const S *in, S *out, hipStream_t st)
+hipError_t launch_stream_z(const Geometry &g, const CellTables<S> &t, const ZLayout &lay, const S *in, S *out,
+                           hipStream_t st)
 {
     switch (g.p) {
-    case 1: return launch_z<S, 1>(g, t, in, out, st);
-    case 2: return launch_z<S, 2>(g, t, in, out, st);
-    case 3: return launch_z<S, 3>(g, t, in, out, st);
-    case 4: return launch_z<S, 4>(g, t, in, out, st);
-    case 5: return launch_z<S, 5>(g, t, in, out, st);
-    case 6: return launch_z<S, 6>(g, t, in, out, st);
+    case 1: return launch_z<S, 1>(g, t, lay, in, out, st);
+    case 2: return launch_z<S, 2>(g, t, lay, in, out, st);
+    case 3: return launch_z<S, 3>(g, t, lay, in, out, st);
+    case 4: return launch_z<S, 4>(g, t, lay, in, out, st);
+    case 5: return launch_z<S, 5>(g, t, lay, in, out, st);
+    case 6: return launch_z<S, 6>(g, t, lay, in, out, st);
     default: return hipErrorInvalidValue;
     }
 }
 
-template hipError_t launch_stream_z<double>(const Geometry &, const CellTables<double> &, const double *, double *,
-                                            hipStream_t);
-template hipError_t launch_stream_z<float>(const Geometry &, const CellTables<float> &, const float *, float *,
-                                           hipStream_t);
+template hipError_t launch_stream_z<double>(const Geometry &, const CellTables<double> &, const ZLayout &, const double *,
+                                           double *, hipStream_t);
+template hipError_t launch_stream_z<float>(const Geometry &, const CellTables<float> &, const ZLayout &, const float *,
+                                           float *, hipStream_t);
 
 }  // namespace sllbm

@@ -12,8 +12,7 @@
 // cells (N_x <= 256 up to 65536 nodes).
 #include <hip/hip_runtime.h>
 
-#include <algorithm>
-
+#include "layouts.h"
 #include "rows.h"
 #include "sllbm_internal.h"
 #include "xcd.h"
@@ -22,49 +21,10 @@ namespace sllbm {
 
 namespace {
 
-constexpr int YNT = 512;                   // most threads per block
-
 __device__ __forceinline__ int wrap2(int x, int n)
 {
     int r = x % n;
     return r < 0 ? r + n : r;
-}
-
-// source cells per lane
-template <int P>
-constexpr int y_cells()
-{
-    return P >= 5 ? 1 : P >= 3 ? 2 : P == 2 ? 4 : 8;
-}
-
-// tyg groups of NC cells along y and cx columns of each per block; txc cells
-// along x per tile (the whole row if ntx = 1); nt threads
-struct YLayout {
-    int cx, txc, tyg, ntx, nty, nt;
-    float rcx;
-};
-
-// the split with the fewest idle lanes
-YLayout y_layout(const Geometry &g, int nc)
-{
-    YLayout b{};
-    double best = 0.0;
-    const int most = g.nodes <= 65536 ? 256 : YNT;         // lanes; small grids need the blocks
-    const bool whole = g.N[0] <= most;
-    const int groups = (g.nel[1] + nc - 1) / nc;
-    const int t0 = whole ? g.nel[0] : 63 / g.p, t1 = whole ? g.nel[0] : (most - 1) / g.p;
-    for (int txc = t0; txc <= t1; ++txc) {
-        const int cx = whole ? g.N[0] : txc * g.p + 1, ntx = (g.nel[0] + txc - 1) / txc;
-        for (int tyg = 1; tyg <= groups && cx * tyg <= std::max(cx, 256); ++tyg) {
-            const int nt = (cx * tyg + 63) / 64 * 64, nty = (groups + tyg - 1) / tyg;
-            const double used = static_cast<double>(groups) * g.N[0] / (static_cast<double>(nt) * ntx * nty);
-            if (used >= best) {
-                best = used;
-                b = YLayout{cx, txc, tyg, ntx, nty, nt, 1.0f / static_cast<float>(cx)};
-            }
-        }
-    }
-    return b;
 }
 
 }  // namespace
@@ -77,7 +37,7 @@ template <typename S, int P>
 __global__ void __launch_bounds__(YNT) k_stream_y(Geometry g, CellTables<S> tab, const S *__restrict__ in,
                                                   S *__restrict__ out, YLayout lay)
 {
-    constexpr int NC = y_cells<P>(), R = NC * P + 1;
+    constexpr int NC = y_cells(P), R = NC * P + 1;
     __shared__ S buf[NC * P][YNT];
     const int tid = threadIdx.x;
     const int tiles = lay.ntx * lay.nty;
@@ -167,35 +127,33 @@ __global__ void __launch_bounds__(YNT) k_stream_y(Geometry g, CellTables<S> tab,
 namespace {
 
 template <typename S, int P>
-hipError_t launch_y(const Geometry &g, const CellTables<S> &t, const S *in, S *out, hipStream_t st)
+hipError_t launch_y(const Geometry &g, const CellTables<S> &t, const YLayout &lay, const S *in, S *out, hipStream_t st)
 {
-    const YLayout lay = y_layout(g, y_cells<P>());
-    const int64_t nb = static_cast<int64_t>(lay.ntx) * lay.nty;
-    if (2 * Q2D * nb > (int64_t(1) << 31) - 1) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((k_stream_y<S, P>), dim3(static_cast<unsigned>(nb), 2 * Q2D), dim3(lay.nt), 0, st, g, t, in, out,
-                       lay);
+    if (lay.blocks == 0) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((k_stream_y<S, P>), dim3(lay.blocks, 2 * Q2D), dim3(lay.nt), 0, st, g, t, in, out, lay);
     return hipGetLastError();
 }
 
 }  // namespace
 
 template <typename S>
-hipError_t launch_stream_2d(const Geometry &g, const CellTables<S> &t, const S *in, S *out, hipStream_t st)
+hipError_t launch_stream_2d(const Geometry &g, const CellTables<S> &t, const YLayout &lay, const S *in, S *out,
+                            hipStream_t st)
 {
     switch (g.p) {
-    case 1: return launch_y<S, 1>(g, t, in, out, st);
-    case 2: return launch_y<S, 2>(g, t, in, out, st);
-    case 3: return launch_y<S, 3>(g, t, in, out, st);
-    case 4: return launch_y<S, 4>(g, t, in, out, st);
-    case 5: return launch_y<S, 5>(g, t, in, out, st);
-    case 6: return launch_y<S, 6>(g, t, in, out, st);
+    case 1: return launch_y<S, 1>(g, t, lay, in, out, st);
+    case 2: return launch_y<S, 2>(g, t, lay, in, out, st);
+    case 3: return launch_y<S, 3>(g, t, lay, in, out, st);
+    case 4: return launch_y<S, 4>(g, t, lay, in, out, st);
+    case 5: return launch_y<S, 5>(g, t, lay, in, out, st);
+    case 6: return launch_y<S, 6>(g, t, lay, in, out, st);
     default: return hipErrorInvalidValue;
     }
 }
 
-template hipError_t launch_stream_2d<double>(const Geometry &, const CellTables<double> &, const double *, double *,
-                                             hipStream_t);
-template hipError_t launch_stream_2d<float>(const Geometry &, const CellTables<float> &, const float *, float *,
-                                            hipStream_t);
+template hipError_t launch_stream_2d<double>(const Geometry &, const CellTables<double> &, const YLayout &,
+                                             const double *, double *, hipStream_t);
+template hipError_t launch_stream_2d<float>(const Geometry &, const CellTables<float> &, const YLayout &,
+                                             const float *, float *, hipStream_t);
 
 }  // namespace sllbm

@@ -3,7 +3,7 @@
 #include <algorithm>
 #include <cstdio>
 #include <cstring>
-#include "sllbm_internal.h"
+#include "layouts.h"
 using namespace sllbm;
 
 static int fail(const char *what, const int n[3], int p)
@@ -34,9 +34,62 @@ static int run_grids()
     return 0;
 }
 
+static bool covers(int parts, int size, int n) { return parts * size >= n && (parts - 1) * size < n; }
+
+static Geometry geometry(const int n[3], int p)
+{
+    Geometry g{};
+    g.p = p;
+    g.nodes = 1;
+    for (int a = 0; a < 3; ++a) {
+        g.nel[a] = n[a];
+        g.N[a] = n[a] * p;
+        g.nodes *= g.N[a];
+    }
+    return g;
+}
+
+// blocks cover every cell once, along each axis, with no block of them empty
+static int layouts()
+{
+    const int sides[] = {1, 2, 3, 5, 8, 13, 32, 43, 64, 65, 86, 129, 256, 257, 512, 513, 2400};
+    for (int p = 1; p <= 6; ++p)
+        for (int a : sides)
+            for (int b : sides) {
+                for (int c : {1, 2, 12, 33, 70}) {
+                    const int n[3] = {a, b, c};
+                    const Geometry g = geometry(n, p);
+                    for (int t = 0; t < 2; ++t)
+                        for (size_t elem : {sizeof(float), sizeof(double)}) {
+                            const ZLayout l = z_layout(g, t == 1, elem);
+                            const bool whole = g.N[0] <= ZNT;
+                            if (!covers(l.ntx, l.txc, a) || !covers(l.nty, l.tyc, b) || !covers(l.nchunk, l.zcells, c))
+                                return fail("cells", n, p);
+                            if (l.nt > ZNT || l.nt % 64 || l.cx * l.tyc > l.nt || l.nt - 64 >= l.cx * l.tyc)
+                                return fail("threads", n, p);
+                            if (l.cx != (whole ? g.N[0] : l.txc * p + (t ? p : 1)) || (whole && l.ntx != 1))
+                                return fail("columns", n, p);
+                            if (l.blocks != static_cast<unsigned>(l.ntx * l.nty * l.nchunk)) return fail("blocks", n, p);
+                            if (l.zcells > (t ? zt_max_cells(p, elem) : z_max_cells(p))) return fail("march", n, p);
+                        }
+                }
+                const int n[3] = {a, b, 1};
+                Geometry g = geometry(n, p);
+                g.nodes = static_cast<int64_t>(g.N[0]) * g.N[1];
+                const YLayout l = y_layout(g);
+                const int groups = (b + y_cells(p) - 1) / y_cells(p);
+                if (!covers(l.ntx, l.txc, a) || !covers(l.nty, l.tyg, groups)) return fail("cells (2-D)", n, p);
+                if (l.nt > YNT || l.nt % 64 || l.cx * l.tyg > l.nt) return fail("threads (2-D)", n, p);
+                if (l.cx != (l.ntx == 1 ? g.N[0] : l.txc * p + 1)) return fail("columns (2-D)", n, p);
+                if (l.blocks != static_cast<unsigned>(l.ntx * l.nty)) return fail("blocks (2-D)", n, p);
+            }
+    return 0;
+}
+
 int main(int argc, char **argv)
 {
     if (argc == 2 && !std::strcmp(argv[1], "run_grids")) return run_grids();
+    if (argc == 2 && !std::strcmp(argv[1], "layouts")) return layouts();
     std::printf("unknown check\n");
     return 1;
 }

@@ -18,11 +18,12 @@ def driver(tmp_path_factory):
     subprocess.check_call([HIPCC, "-O1", "-std=c++17", "-x", "hip", "--offload-arch=gfx950",
                            "-I", os.path.join(ROOT, "include"), "-I", csrc,
                            os.path.join(ROOT, "tests", "host", "launch_check.cpp"),
-                           os.path.join(csrc, "tables.cpp"), os.path.join(csrc, "tables_mapped.cpp"), "-o", exe])
+                           os.path.join(csrc, "tables.cpp"), os.path.join(csrc, "tables_mapped.cpp"),
+                           os.path.join(csrc, "layouts.cpp"), "-o", exe])
     return exe
 
 
-@pytest.mark.parametrize("check", ["run_grids"])
+@pytest.mark.parametrize("check", ["run_grids", "layouts"])
 def test_launch(driver, check):
     out = subprocess.run([driver, check], capture_output=True, text=True)
     assert out.returncode == 0, out.stdout + out.stderr
