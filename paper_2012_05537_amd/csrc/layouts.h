@@ -36,6 +36,9 @@ constexpr int z_max_cells(int p) { return p >= 3 ? 1 : p == 2 ? 2 : 32; }
 // with 4 and 300 with 8; P = 1, 100 x 100 x 30: 93 us with 4, 41 us with 30)
 constexpr int zt_max_cells(int p, size_t elem) { return p == 1 ? 32 : elem == 8 ? 8 : 4; }
 
+// columns that the LDS of a block of nt threads holds (one P x P column per thread)
+constexpr int z_columns(int nt) { return nt <= 64 ? 64 : nt <= 128 ? 128 : ZNT; }
+
 ZLayout z_layout(const Geometry &g, bool transpose, size_t elem);
 
 // Two dimensions (k_stream_y): tyg groups of y_cells(p) cells along y and cx

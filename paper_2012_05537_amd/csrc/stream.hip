@@ -48,12 +48,11 @@ constexpr int z_min_waves()
 // replaces read a window of P + 1 more rows and columns per tile out of LDS
 // and took 5.2 / 2.9 ms, 89 / 47 us, 11.4 us and 668 us.
 // NTH: non-temporal output stores (states larger than the Infinity Cache)
-template <typename S, int P, bool NTH>
-__global__ void __launch_bounds__(ZNT, (z_min_waves<S, P>())) k_stream_z(Geometry g, CellTables<S> tab,
-                                                                        const S *__restrict__ in,
-                                                                        S *__restrict__ out, ZLayout lay)
+template <typename S, int P, bool NTH, int NT>
+__global__ void __launch_bounds__(NT, (z_min_waves<S, P>()))
+    k_stream_z(Geometry g, CellTables<S> tab, const S *__restrict__ in, S *__restrict__ out, ZLayout lay)
 {
-    __shared__ S buf[P * P][ZNT];                          // y-z-interpolated values of a source cell, per lane
+    __shared__ S buf[P * P][NT];                           // y-z-interpolated values of a source cell, per lane
     const int tid = threadIdx.x;
     const int ntiles = lay.ntx * lay.nty;
     const int L = __builtin_amdgcn_readfirstlane(xcd_linear(static_cast<int>(blockIdx.y * gridDim.x + blockIdx.x),
@@ -226,16 +225,35 @@ __global__ void __launch_bounds__(ZNT, (z_min_waves<S, P>())) k_stream_z(Geometr
     cell_step(std::true_type(), c);
 }
 
+// NT: LDS columns of a block, 64, 128 or 256, the fewest that hold its threads.
+// A block of one wave that kept 256 columns left a CU five waves at order 4 in FP64
+// (32 x 52 x 40 nodes: forward 24.9 us, transposed 34.2 us; 17.4 and 22.6 with its own
+// LDS).  Strides known only at run time cost the transposed kernel registers (128^3
+// FP32 299 -> 348 us).
+template <class Launch>
+static hipError_t launch_columns(const ZLayout &lay, Launch &&launch)
+{
+    if (lay.blocks == 0) return hipErrorInvalidValue;
+    switch (z_columns(lay.nt)) {
+    case 64: launch(std::integral_constant<int, 64>()); break;
+    case 128: launch(std::integral_constant<int, 128>()); break;
+    default: launch(std::integral_constant<int, 256>());
+    }
+    return hipGetLastError();
+}
+
 template <typename S, int P>
 static hipError_t launch_z(const Geometry &g, const CellTables<S> &t, const ZLayout &lay, const S *in, S *out,
                            hipStream_t st)
 {
-    if (lay.blocks == 0) return hipErrorInvalidValue;
-    if (use_nontemporal(90 * g.nodes * static_cast<int64_t>(sizeof(S)), g.N[0] * static_cast<int64_t>(sizeof(S))))
-        hipLaunchKernelGGL((k_stream_z<S, P, true>), dim3(lay.blocks, 90), dim3(lay.nt), 0, st, g, t, in, out, lay);
-    else
-        hipLaunchKernelGGL((k_stream_z<S, P, false>), dim3(lay.blocks, 90), dim3(lay.nt), 0, st, g, t, in, out, lay);
-    return hipGetLastError();
+    const bool nt = use_nontemporal(90 * g.nodes * static_cast<int64_t>(sizeof(S)), g.N[0] * static_cast<int64_t>(sizeof(S)));
+    return launch_columns(lay, [&](auto c) {
+        constexpr int NT = decltype(c)::value;
+        if (nt)
+            hipLaunchKernelGGL((k_stream_z<S, P, true, NT>), dim3(lay.blocks, 90), dim3(lay.nt), 0, st, g, t, in, out, lay);
+        else
+            hipLaunchKernelGGL((k_stream_z<S, P, false, NT>), dim3(lay.blocks, 90), dim3(lay.nt), 0, st, g, t, in, out, lay);
+    });
 }
 
 // ---------------------------------------------------------------------------
@@ -277,13 +295,12 @@ constexpr int zt_min_waves()
 // 2.83 / 5.17 ms, 11.4 us and 632 us.  Skipping the second group's LDS reads on lanes
 // that are no node 0 (a branch) is 2 % slower to 2 % faster.
 // NTH: non-temporal output stores (states larger than the Infinity Cache)
-template <typename S, int P, bool NTH>
-__global__ void __launch_bounds__(ZNT, (zt_min_waves<S, P>())) k_stream_zt(Geometry g, CellTables<S> tab,
-                                                                          const S *__restrict__ in,
-                                                                          S *__restrict__ out, ZLayout lay)
+template <typename S, int P, bool NTH, int NT>
+__global__ void __launch_bounds__(NT, (zt_min_waves<S, P>()))
+    k_stream_zt(Geometry g, CellTables<S> tab, const S *__restrict__ in, S *__restrict__ out, ZLayout lay)
 {
     constexpr int D = zt_depth<S, P>();
-    __shared__ S buf[P * P][ZNT];                          // y-z-gathered values of an output cell, per lane
+    __shared__ S buf[P * P][NT];                           // y-z-gathered values of an output cell, per lane
     const int tid = threadIdx.x;
     const int ntiles = lay.ntx * lay.nty;
     const int L = __builtin_amdgcn_readfirstlane(xcd_linear(static_cast<int>(blockIdx.y * gridDim.x + blockIdx.x),
@@ -457,12 +474,14 @@ template <typename S, int P>
 static hipError_t launch_zt(const Geometry &g, const CellTables<S> &t, const ZLayout &lay, const S *in, S *out,
                            hipStream_t st)
 {
-    if (lay.blocks == 0) return hipErrorInvalidValue;
-    if (use_nontemporal(90 * g.nodes * static_cast<int64_t>(sizeof(S)), g.N[0] * static_cast<int64_t>(sizeof(S))))
-        hipLaunchKernelGGL((k_stream_zt<S, P, true>), dim3(lay.blocks, 90), dim3(lay.nt), 0, st, g, t, in, out, lay);
-    else
-        hipLaunchKernelGGL((k_stream_zt<S, P, false>), dim3(lay.blocks, 90), dim3(lay.nt), 0, st, g, t, in, out, lay);
-    return hipGetLastError();
+    const bool nt = use_nontemporal(90 * g.nodes * static_cast<int64_t>(sizeof(S)), g.N[0] * static_cast<int64_t>(sizeof(S)));
+    return launch_columns(lay, [&](auto c) {
+        constexpr int NT = decltype(c)::value;
+        if (nt)
+            hipLaunchKernelGGL((k_stream_zt<S, P, true, NT>), dim3(lay.blocks, 90), dim3(lay.nt), 0, st, g, t, in, out, lay);
+        else
+            hipLaunchKernelGGL((k_stream_zt<S, P, false, NT>), dim3(lay.blocks, 90), dim3(lay.nt), 0, st, g, t, in, out, lay);
+    });
 }
 
 template <typename S>

@@ -86,10 +86,26 @@ static int layouts()
     return 0;
 }
 
+// a block's LDS holds no more columns than its threads round up to: at least four
+// waves per SIMD fit a CU (160 KB) at order 4, two at order 6, whatever the block
+static int lds_of_block()
+{
+    for (int nt = 64; nt <= ZNT; nt += 64) {
+        const int n[3] = {nt, 1, 1};
+        if (z_columns(nt) < nt || z_columns(nt) >= 2 * nt) return fail("columns", n, 1);
+        for (int p = 4; p <= 6; ++p) {
+            const int blocks = 160 * 1024 / static_cast<int>(p * p * z_columns(nt) * sizeof(double));
+            if (blocks * nt / 256 < (p == 4 ? 4 : p == 5 ? 3 : 2) - (nt == 192 ? 1 : 0)) return fail("waves", n, p);
+        }
+    }
+    return 0;
+}
+
 int main(int argc, char **argv)
 {
     if (argc == 2 && !std::strcmp(argv[1], "run_grids")) return run_grids();
     if (argc == 2 && !std::strcmp(argv[1], "layouts")) return layouts();
+    if (argc == 2 && !std::strcmp(argv[1], "lds_of_block")) return lds_of_block();
     std::printf("unknown check\n");
     return 1;
 }

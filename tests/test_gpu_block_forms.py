@@ -1,0 +1,101 @@
+"""Forms of the streaming kernels by the size of their blocks, and the forms for
+states larger than the Infinity Cache, against the FP64 oracle or the form that small
+grids take."""
+import math
+
+import numpy as np
+import pytest
+import torch
+
+from gpu_common import Q, make_pair, rel_err, require_gpu, to_dev, to_np
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(autouse=True)
+def _gpu():
+    require_gpu()
+
+
+@pytest.fixture(scope="module")
+def oracle():
+    from oracle import oracle as O
+    return O
+
+
+# blocks of 64, 128, 192 and 256 threads (rows of 32 to 36 nodes, their cells along y
+# dealt 2, 4, 6 and 7 to a block), the last one ragged along y
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("n_el,p", [((8, 13, 3), 4), ((8, 4, 3), 4), ((8, 6, 2), 4), ((8, 7, 2), 4), ((12, 5, 2), 3),
+                                    ((6, 3, 2), 6), ((10, 1, 4), 6), ((7, 11, 2), 5), ((7, 3, 3), 5), ((32, 3, 5), 1)])
+def test_streaming_by_block_size(oracle, precision, n_el, p):
+    """S against the oracle (1e-12, FP32 1e-5: the repository's bars), S^T as its
+    adjoint per velocity."""
+    ctx, cfg = make_pair(oracle, n_el, p, 0.06, 0.01, precision=precision)
+    rng = np.random.default_rng(17)
+    x, y = (rng.normal(size=(2, Q, ctx.nodes)).astype(np.float32).astype(np.float64) for _ in range(2))
+    print("block form", precision, n_el, p, flush=True)
+    F, G = to_np(ctx.stream(to_dev(ctx, x[0], x[1])))
+    f, g = oracle.stream(cfg, x[0], x[1])
+    tol = 1e-5 if precision else 1e-12
+    assert rel_err(F, f) < tol and rel_err(G, g) < tol
+    st = np.stack(to_np(ctx.stream(to_dev(ctx, y[0], y[1]), transpose=True)))
+    fg = np.stack([f, g])
+    lhs, rhs = (fg * y).sum(-1), (x * st).sum(-1)
+    assert np.all(np.abs(lhs - rhs) <= tol * (np.abs(fg * y).sum(-1) + np.abs(x * st).sum(-1)))
+
+
+# states larger than the Infinity Cache whose x rows are whole cache lines: non-temporal
+# stores, at every order in both precisions, blocks of 64 to 256 threads
+LARGE = [((80, 70, 70), 1, 0), ((40, 36, 37), 2, 0), ((16, 32, 31), 3, 0), ((20, 20, 20), 4, 0), ((8, 13, 57), 4, 0),
+         ((8, 4, 183), 4, 0), ((16, 14, 14), 5, 0), ((16, 12, 12), 6, 0), ((96, 90, 87), 1, 1), ((48, 46, 45), 2, 1),
+         ((32, 30, 31), 3, 1), ((24, 23, 24), 4, 1), ((8, 13, 120), 4, 1), ((32, 14, 14), 5, 1), ((16, 16, 15), 6, 1)]
+
+
+@pytest.mark.parametrize("n_el,p,precision", LARGE)
+def test_large_grid_streaming_with_whole_lines(oracle, n_el, p, precision):
+    """Two z-planes of S against the oracle (1e-12, FP32 1e-5), S^T by <S x, y> = <x, S^T y>
+    per population and velocity, relative to the sums of the terms' magnitudes."""
+    dt = 3.0 * (2 * math.pi / (max(n_el) * p)) / math.sqrt(15.0)
+    ctx, cfg = make_pair(oracle, n_el, p, dt, 1e-3, precision=precision)
+    elem = 4 if precision else 8
+    assert 90 * ctx.nodes * elem > 256 << 20 and n_el[0] * p * elem % 128 == 0
+    print("large grid", precision, n_el, p, flush=True)
+    gen = torch.Generator(device=ctx.device).manual_seed(p)
+    x, y = (torch.randn((2, Q, ctx.nodes), generator=gen, device=ctx.device, dtype=ctx.dtype) for _ in range(2))
+    s = ctx.stream(x)
+    f0, g0 = to_np(x)
+    plane = ctx.shape[1] * ctx.shape[2]
+    tol = 1e-5 if precision else 1e-12
+    for z in (0, ctx.shape[0] // 2 + 1):
+        fs, gs = oracle.stream_at_nodes(cfg, f0, g0, z * plane + np.arange(plane))
+        F, G = (v[:, z * plane:(z + 1) * plane].double().cpu().numpy().T for v in s)
+        assert np.max(np.abs(F - fs)) / np.abs(fs).max() < tol and np.max(np.abs(G - gs)) / np.abs(gs).max() < tol
+    st = ctx.stream(y, transpose=True)
+    lhs, rhs = (s.double() * y.double()), (x.double() * st.double())
+    scale = lhs.abs().sum(2) + rhs.abs().sum(2)
+    assert float(((lhs.sum(2) - rhs.sum(2)).abs() / scale).max()) < tol
+    ctx.close()
+
+
+def test_large_fp64_reverse_step_matches_the_small_form():
+    """Reverse step of 80^3 nodes in FP64 (369 MB, registers and non-temporal accesses) with
+    8000 copies of a 4^3-node grid's state and adjoint, whose own reverse step is another
+    form of the kernel.  Cells of length 5e14 leave every node on itself, so that the
+    step is the collision's VJP: equal node by node to rounding (4e-13 of the largest
+    value), and dL/dmu 8000 times the small grid's (1e-10)."""
+    from paper_2012_05537_amd.sllbm import SLLBM
+    small, large = (SLLBM((n,) * 3, 4, 0.05, 0.02, length=1e16) for n in (1, 20))
+    assert 90 * large.nodes * 8 > 256 << 20 and large.nodes * 8 % 128 == 0 and large.nodes % small.nodes == 0
+    gen = torch.Generator(device=small.device).manual_seed(3)
+    rnd = lambda *s: torch.randn(s, generator=gen, device=small.device, dtype=torch.float64)
+    small.init_equilibrium(1 + 0.1 * rnd(64), 0.2 * rnd(3, 64), 1 + 0.05 * rnd(64))
+    x = small.get_state() * (1 + 0.02 * rnd(2, Q, 64))
+    lam = rnd(2, Q, 64) + 0.5
+    print("large FP64 reverse step", flush=True)
+    dmu = torch.zeros(2, dtype=torch.float64, device=small.device)
+    want = small.adjoint_step(x, lam, dmu=dmu[:1])
+    reps = large.nodes // small.nodes
+    got = large.adjoint_step(x.repeat(1, 1, reps), lam.repeat(1, 1, reps), dmu=dmu[1:])
+    assert float((got.view(2, Q, reps, 64) - want[:, :, None]).abs().max() / want.abs().max()) <= 4e-13
+    assert float(dmu[1]) == pytest.approx(reps * float(dmu[0]), rel=1e-10)
