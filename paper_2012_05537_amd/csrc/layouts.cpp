@@ -3,6 +3,8 @@
 
 #include <algorithm>
 
+#include "nt.h"
+
 namespace sllbm {
 
 ZLayout z_layout(const Geometry &g, bool transpose, size_t elem)
@@ -21,7 +23,7 @@ ZLayout z_layout(const Geometry &g, bool transpose, size_t elem)
             const double used = static_cast<double>(g.nel[1]) * g.N[0] / (static_cast<double>(nt) * ntx * nty);
             if (used >= best) {
                 best = used;
-                b = ZLayout{cx, txc, tyc, ntx, nty, nt, 1.0f / static_cast<float>(cx), 0, 0, 0};
+                b = ZLayout{cx, txc, tyc, ntx, nty, nt, 1.0f / static_cast<float>(cx), 0, 0, 0, false};
             }
         }
     }
@@ -37,6 +39,11 @@ ZLayout z_layout(const Geometry &g, bool transpose, size_t elem)
     // (the grid is blocks x 90: with one dimension its threads would pass 2^32 on
     // the largest grids)
     if (90 * tiles * b.nchunk <= (int64_t(1) << 31) - 1) b.blocks = static_cast<unsigned>(tiles * b.nchunk);
+    // Tiles of a split row end inside a cache line, which the next tile's block
+    // completes (FP64, p = 4: 384 x 64 x 64 nodes, S 492 us, with the hint 558; 512 x
+    // 64 x 64 579 and 614, S^T 704 and 715)
+    const int64_t value = static_cast<int64_t>(elem);
+    b.nontemporal = b.ntx == 1 && use_nontemporal(90 * g.nodes * value, g.N[0] * value);
     return b;
 }
 

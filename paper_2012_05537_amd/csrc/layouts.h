@@ -19,6 +19,7 @@ struct ZLayout {
     float rcx;                        // 1 / cx
     int zcells, nchunk;               // cells along z per block, blocks along z
     unsigned blocks;                  // per plane (0: too many)
+    bool nontemporal;                 // output stores (use_nontemporal)
 };
 
 // Cells along z per block of the forward kernel.  One source cell from order 3

@@ -17,7 +17,6 @@
 #include <type_traits>
 
 #include "layouts.h"
-#include "nt.h"
 #include "rows.h"
 #include "sllbm_internal.h"
 #include "xcd.h"
@@ -246,10 +245,9 @@ template <typename S, int P>
 static hipError_t launch_z(const Geometry &g, const CellTables<S> &t, const ZLayout &lay, const S *in, S *out,
                            hipStream_t st)
 {
-    const bool nt = use_nontemporal(90 * g.nodes * static_cast<int64_t>(sizeof(S)), g.N[0] * static_cast<int64_t>(sizeof(S)));
     return launch_columns(lay, [&](auto c) {
         constexpr int NT = decltype(c)::value;
-        if (nt)
+        if (lay.nontemporal)
             hipLaunchKernelGGL((k_stream_z<S, P, true, NT>), dim3(lay.blocks, 90), dim3(lay.nt), 0, st, g, t, in, out, lay);
         else
             hipLaunchKernelGGL((k_stream_z<S, P, false, NT>), dim3(lay.blocks, 90), dim3(lay.nt), 0, st, g, t, in, out, lay);
@@ -474,10 +472,9 @@ template <typename S, int P>
 static hipError_t launch_zt(const Geometry &g, const CellTables<S> &t, const ZLayout &lay, const S *in, S *out,
                            hipStream_t st)
 {
-    const bool nt = use_nontemporal(90 * g.nodes * static_cast<int64_t>(sizeof(S)), g.N[0] * static_cast<int64_t>(sizeof(S)));
     return launch_columns(lay, [&](auto c) {
         constexpr int NT = decltype(c)::value;
-        if (nt)
+        if (lay.nontemporal)
             hipLaunchKernelGGL((k_stream_zt<S, P, true, NT>), dim3(lay.blocks, 90), dim3(lay.nt), 0, st, g, t, in, out, lay);
         else
             hipLaunchKernelGGL((k_stream_zt<S, P, false, NT>), dim3(lay.blocks, 90), dim3(lay.nt), 0, st, g, t, in, out, lay);

@@ -101,11 +101,32 @@ static int lds_of_block()
     return 0;
 }
 
+// non-temporal stores only where no two blocks share a cache line of an output row
+static int nontemporal_rows()
+{
+    bool seen = false;
+    for (int p = 1; p <= 6; ++p)
+        for (int a : {16, 32, 48, 64, 72, 80, 96, 128, 256, 512, 1024})
+            for (int b : {4, 32, 64}) {
+                const int n[3] = {a, b, 64};
+                const Geometry g = geometry(n, p);
+                for (int t = 0; t < 2; ++t)
+                    for (int elem : {4, 8}) {
+                        const ZLayout l = z_layout(g, t == 1, elem);
+                        const bool large = 90 * g.nodes * elem > int64_t(256) << 20;
+                        if (l.nontemporal != (large && l.ntx == 1 && g.N[0] * elem % 128 == 0)) return fail("hint", n, p);
+                        seen = seen || l.nontemporal;
+                    }
+            }
+    return seen ? 0 : 1;
+}
+
 int main(int argc, char **argv)
 {
     if (argc == 2 && !std::strcmp(argv[1], "run_grids")) return run_grids();
     if (argc == 2 && !std::strcmp(argv[1], "layouts")) return layouts();
     if (argc == 2 && !std::strcmp(argv[1], "lds_of_block")) return lds_of_block();
+    if (argc == 2 && !std::strcmp(argv[1], "nontemporal_rows")) return nontemporal_rows();
     std::printf("unknown check\n");
     return 1;
 }
