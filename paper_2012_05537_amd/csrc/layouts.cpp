@@ -7,26 +7,42 @@
 
 namespace sllbm {
 
+// Whether x rows may be blocks: a whole row has no halo, and its stores are whole
+// lines.  FP64, p = 4, rows of 280 and 384 nodes (as many lanes idle as in tiles): S 542 ->
+// 506 and 492 -> 416 us, S^T 637 -> 619 and 576 -> 490; 260 nodes (19 % idle against 10 %):
+// S 322 -> 317, S^T 376 -> 398, in FP32 212 -> 160 and 222 -> 206.  Rows of more than 256
+// nodes make few blocks of small grids: 288 x 32 x 32 S^T 113 -> 118 us, in FP32 42 -> 50,
+// 384 x 16 x 16 S 24 -> 27.  Rows of more than 512 leave a CU one block (p = 4) and
+// gain where the tiles break their lines (1024 x 32 x 32, p = 2, FP64: S 328 -> 288, S^T 357
+// -> 308; 1024 x 40 x 40, p = 4, FP32: 287 -> 217, 337 -> 286; but 600 x 48 x 48, p = 4, FP64,
+// S 399 -> 460).
+static bool whole_rows(const Geometry &g, size_t elem)
+{
+    if (g.N[0] <= ZNT) return true;
+    if (g.N[0] > z_row(g.p) || 90 * g.nodes * static_cast<int64_t>(elem) <= INFINITY_CACHE_BYTES) return false;
+    return g.N[0] <= 512 || g.N[0] * elem % 128 == 0;
+}
+
 ZLayout z_layout(const Geometry &g, bool transpose, size_t elem)
 {
     const int halo = transpose ? g.p : 1, max_cells = transpose ? zt_max_cells(g.p, elem) : z_max_cells(g.p);
     // the split with the fewest idle lanes
     ZLayout b{};
     double best = 0.0;
-    const bool whole = g.N[0] <= ZNT;
-    const int t0 = whole ? g.nel[0] : (64 - halo) / g.p, t1 = whole ? g.nel[0] : (ZNT - halo) / g.p;
-    for (int txc = t0; txc <= t1; ++txc) {
-        const int cx = whole ? g.N[0] : txc * g.p + halo;
+    auto consider = [&](int txc, int cx, double weight) {
         const int ntx = (g.nel[0] + txc - 1) / txc;
-        for (int tyc = 1; tyc <= g.nel[1] && cx * tyc <= ZNT; ++tyc) {
+        for (int tyc = 1; tyc <= g.nel[1] && (tyc == 1 || cx * tyc <= ZNT); ++tyc) {
             const int nt = (cx * tyc + 63) / 64 * 64, nty = (g.nel[1] + tyc - 1) / tyc;
-            const double used = static_cast<double>(g.nel[1]) * g.N[0] / (static_cast<double>(nt) * ntx * nty);
+            const double used = weight * g.nel[1] * g.N[0] / (static_cast<double>(nt) * ntx * nty);
             if (used >= best) {
                 best = used;
                 b = ZLayout{cx, txc, tyc, ntx, nty, nt, 1.0f / static_cast<float>(cx), 0, 0, 0, false};
             }
         }
-    }
+    };
+    if (g.N[0] > ZNT)
+        for (int txc = (64 - halo) / g.p; txc <= (ZNT - halo) / g.p; ++txc) consider(txc, txc * g.p + halo, 1.0);
+    if (whole_rows(g, elem)) consider(g.nel[0], g.N[0], 1.12);
     // Cells along z per block: at most max_cells, fewer while the grid has fewer
     // than 1280 blocks of 256 threads, five per CU (transposed kernel, 64^3 nodes,
     // FP64: 86, 85 and 92 us with 2, 4 and 8 blocks per CU).

@@ -9,11 +9,11 @@
 namespace sllbm {
 
 // Three dimensions (k_stream_z, k_stream_zt).  A block holds tyc cells along y
-// and cx columns of each.  While x rows fit a block (N_x <= ZNT), cx = N_x: the
+// and cx columns of each.  While x rows are blocks (whole_rows), cx = N_x: the
 // periodic row is complete and lane x writes output column x.  Longer rows are
 // split into tiles of txc cells; a tile has halo columns more than it writes
 // (forward: the last cell's far face; transposed: the group before the tile).
-constexpr int ZNT = 256;              // most threads per block
+constexpr int ZNT = 256;              // most threads per block, but for one row of more nodes
 struct ZLayout {
     int cx, txc, tyc, ntx, nty, nt;   // nt: threads per block
     float rcx;                        // 1 / cx
@@ -37,8 +37,18 @@ constexpr int z_max_cells(int p) { return p >= 3 ? 1 : p == 2 ? 2 : 32; }
 // with 4 and 300 with 8; P = 1, 100 x 100 x 30: 93 us with 4, 41 us with 30)
 constexpr int zt_max_cells(int p, size_t elem) { return p == 1 ? 32 : elem == 8 ? 8 : 4; }
 
+// Longest row that may be a block of its own.  From order 5 on such a block's LDS
+// (102 KB for 512 columns in FP64) leaves a CU one of them: 260 x 70 x 70 nodes, p = 5,
+// FP64, S 364 us split and 491 whole, S^T 458 and 660.
+constexpr int z_row(int p) { return p <= 4 ? 1024 : ZNT; }
+
 // columns that the LDS of a block of nt threads holds (one P x P column per thread)
-constexpr int z_columns(int nt) { return nt <= 64 ? 64 : nt <= 128 ? 128 : ZNT; }
+constexpr int z_columns(int nt)
+{
+    for (int n : {64, 128, 256, 384, 512, 768})
+        if (nt <= n) return n;
+    return 1024;
+}
 
 ZLayout z_layout(const Geometry &g, bool transpose, size_t elem);
 

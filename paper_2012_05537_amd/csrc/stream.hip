@@ -33,9 +33,10 @@ __device__ __forceinline__ int wrapi(int x, int n)
 
 }  // namespace
 
-template <typename S, int P>
+template <typename S, int P, int NT>
 constexpr int z_min_waves()
 {
+    if (NT > 512) return 4;                                // one block of 1024 threads
     return sizeof(S) == 4 ? (P <= 4 ? 5 : P == 5 ? 4 : 3) : (P <= 3 ? 5 : P == 4 ? 4 : P == 5 ? 3 : 2);
 }
 
@@ -48,7 +49,7 @@ constexpr int z_min_waves()
 // and took 5.2 / 2.9 ms, 89 / 47 us, 11.4 us and 668 us.
 // NTH: non-temporal output stores (states larger than the Infinity Cache)
 template <typename S, int P, bool NTH, int NT>
-__global__ void __launch_bounds__(NT, (z_min_waves<S, P>()))
+__global__ void __launch_bounds__(NT, (z_min_waves<S, P, NT>()))
     k_stream_z(Geometry g, CellTables<S> tab, const S *__restrict__ in, S *__restrict__ out, ZLayout lay)
 {
     __shared__ S buf[P * P][NT];                           // y-z-interpolated values of a source cell, per lane
@@ -224,19 +225,30 @@ __global__ void __launch_bounds__(NT, (z_min_waves<S, P>()))
     cell_step(std::true_type(), c);
 }
 
-// NT: LDS columns of a block, 64, 128 or 256, the fewest that hold its threads.
+// NT: LDS columns of a block (z_columns), the fewest that hold its threads.
 // A block of one wave that kept 256 columns left a CU five waves at order 4 in FP64
 // (32 x 52 x 40 nodes: forward 24.9 us, transposed 34.2 us; 17.4 and 22.6 with its own
 // LDS).  Strides known only at run time cost the transposed kernel registers (128^3
 // FP32 299 -> 348 us).
-template <class Launch>
+template <int P, class Launch>
 static hipError_t launch_columns(const ZLayout &lay, Launch &&launch)
 {
     if (lay.blocks == 0) return hipErrorInvalidValue;
     switch (z_columns(lay.nt)) {
     case 64: launch(std::integral_constant<int, 64>()); break;
     case 128: launch(std::integral_constant<int, 128>()); break;
-    default: launch(std::integral_constant<int, 256>());
+    case 256: launch(std::integral_constant<int, 256>()); break;
+    default:
+        if constexpr (z_row(P) > ZNT) {
+            switch (z_columns(lay.nt)) {
+            case 384: launch(std::integral_constant<int, 384>()); break;
+            case 512: launch(std::integral_constant<int, 512>()); break;
+            case 768: launch(std::integral_constant<int, 768>()); break;
+            default: launch(std::integral_constant<int, 1024>());
+            }
+        } else {
+            return hipErrorInvalidValue;
+        }
     }
     return hipGetLastError();
 }
@@ -245,11 +257,11 @@ template <typename S, int P>
 static hipError_t launch_z(const Geometry &g, const CellTables<S> &t, const ZLayout &lay, const S *in, S *out,
                            hipStream_t st)
 {
-    return launch_columns(lay, [&](auto c) {
+    return launch_columns<P>(lay, [&](auto c) {
         constexpr int NT = decltype(c)::value;
-        if (lay.nontemporal)
+        if (NT > 512 || lay.nontemporal)                   // (such rows are whole lines of large states)
             hipLaunchKernelGGL((k_stream_z<S, P, true, NT>), dim3(lay.blocks, 90), dim3(lay.nt), 0, st, g, t, in, out, lay);
-        else
+        else if constexpr (NT <= 512)
             hipLaunchKernelGGL((k_stream_z<S, P, false, NT>), dim3(lay.blocks, 90), dim3(lay.nt), 0, st, g, t, in, out, lay);
     });
 }
@@ -280,9 +292,10 @@ constexpr int zt_depth()
     return P <= 3 || (P == 4 && sizeof(S) == 4) ? P : P == 6 ? 2 : 1;
 }
 
-template <typename S, int P>
+template <typename S, int P, int NT>
 constexpr int zt_min_waves()
 {
+    if (NT > 512) return 4;                                // one block of 1024 threads
     return sizeof(S) == 4 ? (P <= 4 ? 5 : P == 5 ? 4 : 3) : (P <= 3 ? 5 : P == 4 ? 4 : P == 5 ? 3 : 2);
 }
 
@@ -294,7 +307,7 @@ constexpr int zt_min_waves()
 // that are no node 0 (a branch) is 2 % slower to 2 % faster.
 // NTH: non-temporal output stores (states larger than the Infinity Cache)
 template <typename S, int P, bool NTH, int NT>
-__global__ void __launch_bounds__(NT, (zt_min_waves<S, P>()))
+__global__ void __launch_bounds__(NT, (zt_min_waves<S, P, NT>()))
     k_stream_zt(Geometry g, CellTables<S> tab, const S *__restrict__ in, S *__restrict__ out, ZLayout lay)
 {
     constexpr int D = zt_depth<S, P>();
@@ -472,11 +485,11 @@ template <typename S, int P>
 static hipError_t launch_zt(const Geometry &g, const CellTables<S> &t, const ZLayout &lay, const S *in, S *out,
                            hipStream_t st)
 {
-    return launch_columns(lay, [&](auto c) {
+    return launch_columns<P>(lay, [&](auto c) {
         constexpr int NT = decltype(c)::value;
-        if (lay.nontemporal)
+        if (NT > 512 || lay.nontemporal)                   // (such rows are whole lines of large states)
             hipLaunchKernelGGL((k_stream_zt<S, P, true, NT>), dim3(lay.blocks, 90), dim3(lay.nt), 0, st, g, t, in, out, lay);
-        else
+        else if constexpr (NT <= 512)
             hipLaunchKernelGGL((k_stream_zt<S, P, false, NT>), dim3(lay.blocks, 90), dim3(lay.nt), 0, st, g, t, in, out, lay);
     });
 }

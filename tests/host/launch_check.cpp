@@ -56,20 +56,21 @@ static int layouts()
     for (int p = 1; p <= 6; ++p)
         for (int a : sides)
             for (int b : sides) {
-                for (int c : {1, 2, 12, 33, 70}) {
+                for (int c : {1, 2, 12, 33, 70, 900}) {
                     const int n[3] = {a, b, c};
                     const Geometry g = geometry(n, p);
                     for (int t = 0; t < 2; ++t)
                         for (size_t elem : {sizeof(float), sizeof(double)}) {
                             const ZLayout l = z_layout(g, t == 1, elem);
-                            const bool whole = g.N[0] <= ZNT;
+                            const bool whole = l.ntx == 1;
                             if (!covers(l.ntx, l.txc, a) || !covers(l.nty, l.tyc, b) || !covers(l.nchunk, l.zcells, c))
                                 return fail("cells", n, p);
-                            if (l.nt > ZNT || l.nt % 64 || l.cx * l.tyc > l.nt || l.nt - 64 >= l.cx * l.tyc)
+                            if (l.nt > std::max(ZNT, l.tyc == 1 && whole ? z_row(p) : 0) || l.nt % 64 || l.cx * l.tyc > l.nt || l.nt - 64 >= l.cx * l.tyc)
                                 return fail("threads", n, p);
-                            if (l.cx != (whole ? g.N[0] : l.txc * p + (t ? p : 1)) || (whole && l.ntx != 1))
+                            if (l.cx != (whole ? g.N[0] : l.txc * p + (t ? p : 1)) || (g.N[0] <= ZNT && !whole))
                                 return fail("columns", n, p);
-                            if (l.blocks != static_cast<unsigned>(l.ntx * l.nty * l.nchunk)) return fail("blocks", n, p);
+                            const int64_t blocks = static_cast<int64_t>(l.ntx) * l.nty * l.nchunk;
+                            if (l.blocks != (90 * blocks >> 31 ? 0 : blocks)) return fail("blocks", n, p);
                             if (l.zcells > (t ? zt_max_cells(p, elem) : z_max_cells(p))) return fail("march", n, p);
                         }
                 }
@@ -90,8 +91,10 @@ static int layouts()
 // waves per SIMD fit a CU (160 KB) at order 4, two at order 6, whatever the block
 static int lds_of_block()
 {
-    for (int nt = 64; nt <= ZNT; nt += 64) {
+    for (int nt = 64; nt <= z_row(4); nt += 64) {
         const int n[3] = {nt, 1, 1};
+        if (nt > ZNT && static_cast<size_t>(4 * 4 * z_columns(nt)) * sizeof(double) > 160 * 1024) return fail("LDS", n, 4);
+        if (nt > ZNT) continue;
         if (z_columns(nt) < nt || z_columns(nt) >= 2 * nt) return fail("columns", n, 1);
         for (int p = 4; p <= 6; ++p) {
             const int blocks = 160 * 1024 / static_cast<int>(p * p * z_columns(nt) * sizeof(double));
