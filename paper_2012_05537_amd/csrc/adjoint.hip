@@ -927,13 +927,14 @@ hipError_t Launch<S>::collide_vjp(const Geometry &g, const CollisionParams &cp, 
     const bool nt = use_nontemporal(90 * plane, plane);
     int blocks = 0;
     // alpha staged in LDS (see k_collide_vjp_lds): in FP32 always; in FP64 it
-    // leaves 1.5 waves per SIMD, which is faster while the grid has at most two
-    // blocks per CU (10.3 against 12.4 us at 512 nodes, 11.4 against 14.2 at
-    // 13,824) and 1-6 % slower from 110,592 nodes on.  Rows that are not 16-byte
+    // leaves 1.5 waves per SIMD, which is faster while the grid has at most one
+    // block per CU (10.3 against 12.4 us at 512 nodes, 11.4 against 14.2 at
+    // 13,824; the adjoint step at 16,250 nodes 24.9 us either way, at 17,576 29.9 and
+    // 25.4, at 32,768 31.8 and 29.5).  Rows that are not 16-byte
     // aligned are staged by words on large FP32 grids (adjoint step at 63^3 nodes
     // 112 -> 102 us, 129^3 1032 -> 948, 45^3 equal, 39 x 33 x 27 27.4 -> 29.4), otherwise not.
     const bool wide = g.nodes % (16 / sizeof(S)) == 0 && reinterpret_cast<uintptr_t>(lam) % 16 == 0;
-    if (wide ? sizeof(S) == 4 || g.nodes <= 32768 : sizeof(S) == 4 && g.nodes > 65536) {
+    if (wide ? sizeof(S) == 4 || g.nodes <= 16384 : sizeof(S) == 4 && g.nodes > 65536) {
         constexpr int NB = 512 / sizeof(S);
         blocks = static_cast<int>((g.nodes + NB - 1) / NB);
         auto launch = [&](auto nth, auto wd) {

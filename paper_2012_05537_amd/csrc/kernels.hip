@@ -326,10 +326,14 @@ static hipError_t collide_lat(const Geometry &g, const CollisionParams &cp, cons
         // 14.4 us, 63^3 37.9 -> 34.5, 129^3 390 -> 348, 243^3 2.78 -> 2.24 ms, but 39 x 33 x 27
         // the step 21.9 -> 22.7; FP64 129^3 700 -> 673 us, but 45^3 26.3 -> 28.1.
         constexpr int NB = 512 / sizeof(S), VL = 16 / sizeof(S);
+        // D3Q45 in FP64 keeps the register form between one block per CU and two rounds
+        // of three (26^3 nodes 9.4 us staged and 8.0, 30^3 10.0 and 8.5, 40^3 19.5 and 15.9,
+        // 46^3 27.4 and 24.8; 24^3 6.8 and 8.8, 48^3 28.4 and 28.6; steps alike).
         constexpr bool D3 = L::Q == 45, NO_NT = D3 && sizeof(S) == 8;
+        const bool few_rounds = NO_NT && g.nodes > 256 * NB && g.nodes <= 2 * 3 * 256 * NB;
         const bool wide = g.nodes % VL == 0 && reinterpret_cast<uintptr_t>(in) % 16 == 0;
         const bool by_words = D3 && (sizeof(S) == 4 ? g.nodes > 65536 : bytes > INFINITY_CACHE_BYTES);
-        if ((wide || by_words) && !(NO_NT && nt)) {
+        if ((wide || by_words) && !(NO_NT && nt) && !few_rounds) {
             auto launch = [&](auto nth, auto wd) {
                 hipLaunchKernelGGL((k_collide_lds<S, L, decltype(nth)::value, decltype(wd)::value>),
                                    dim3(static_cast<unsigned>((g.nodes + NB - 1) / NB)), dim3(2 * NB), 0, st, g.nodes,

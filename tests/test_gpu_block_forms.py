@@ -88,24 +88,49 @@ def test_large_grid_streaming(oracle, n_el, p, precision):
     ctx.close()
 
 
-def test_large_fp64_reverse_step_matches_the_small_form():
-    """Reverse step of 80^3 nodes in FP64 (369 MB, registers and non-temporal accesses) with
-    8000 copies of a 4^3-node grid's state and adjoint, whose own reverse step is another
-    form of the kernel.  Cells of length 5e14 leave every node on itself, so that the
-    step is the collision's VJP: equal node by node to rounding (4e-13 of the largest
-    value), and dL/dmu 8000 times the small grid's (1e-10)."""
+# staged up to one block of 64 nodes per CU, in registers beyond, there with
+# non-temporal accesses above 256 MiB (80^3 nodes)
+@pytest.mark.parametrize("n_el,p", [((32, 32, 16), 1), ((114, 48, 3), 1), ((20, 20, 20), 4)])
+def test_fp64_reverse_step_forms_agree(n_el, p):
+    """FP64 reverse step of copies of a 32-node grid's state and adjoint.  Cells of
+    length 1e14 and more leave every node on itself, so that the step is the
+    collision's VJP: equal node by node to rounding (4e-13 of the largest value), and
+    dL/dmu the number of copies times the small grid's (1e-10)."""
     from paper_2012_05537_amd.sllbm import SLLBM
-    small, large = (SLLBM((n,) * 3, 4, 0.05, 0.02, length=1e16) for n in (1, 20))
-    assert 90 * large.nodes * 8 > 256 << 20 and large.nodes * 8 % 128 == 0 and large.nodes % small.nodes == 0
+    small, large = SLLBM((4, 4, 2), 1, 0.05, 0.02, length=1e16), SLLBM(n_el, p, 0.05, 0.02, length=1e16)
+    assert large.nodes % 32 == 0 and (p == 1 or 90 * large.nodes * 8 > 256 << 20)
     gen = torch.Generator(device=small.device).manual_seed(3)
     rnd = lambda *s: torch.randn(s, generator=gen, device=small.device, dtype=torch.float64)
-    small.init_equilibrium(1 + 0.1 * rnd(64), 0.2 * rnd(3, 64), 1 + 0.05 * rnd(64))
-    x = small.get_state() * (1 + 0.02 * rnd(2, Q, 64))
-    lam = rnd(2, Q, 64) + 0.5
-    print("large FP64 reverse step", flush=True)
+    small.init_equilibrium(1 + 0.1 * rnd(32), 0.2 * rnd(3, 32), 1 + 0.05 * rnd(32))
+    x = small.get_state() * (1 + 0.02 * rnd(2, Q, 32))
+    lam = rnd(2, Q, 32) + 0.5
+    print("FP64 reverse step", n_el, flush=True)
     dmu = torch.zeros(2, dtype=torch.float64, device=small.device)
     want = small.adjoint_step(x, lam, dmu=dmu[:1])
-    reps = large.nodes // small.nodes
+    reps = large.nodes // 32
     got = large.adjoint_step(x.repeat(1, 1, reps), lam.repeat(1, 1, reps), dmu=dmu[1:])
-    assert float((got.view(2, Q, reps, 64) - want[:, :, None]).abs().max() / want.abs().max()) <= 4e-13
+    assert float((got.view(2, Q, reps, 32) - want[:, :, None]).abs().max() / want.abs().max()) <= 4e-13
     assert float(dmu[1]) == pytest.approx(reps * float(dmu[0]), rel=1e-10)
+
+
+# FP64 collision: staged up to one block of 64 nodes per CU, in registers up to two
+# rounds of three blocks, staged beyond
+@pytest.mark.parametrize("n_el", [(32, 32, 16), (114, 48, 3), (64, 48, 32), (114, 62, 14)])
+def test_fp64_collision_forms_agree(oracle, n_el):
+    """Collision of a grid of copies of a small one, whose collision is checked against
+    the oracle (1e-12, the repository's bar): equal to rounding (1e-13)."""
+    ctx, _ = make_pair(oracle, n_el, 1, 0.05, 0.02)
+    small, cfg = make_pair(oracle, (4, 4, 2), 1, 0.05, 0.02)
+    rng = np.random.default_rng(23)
+    f, g = oracle.init_equilibrium(cfg, 1 + 0.1 * rng.normal(size=32), 0.2 * rng.normal(size=(3, 32)),
+                                   1 + 0.05 * rng.normal(size=32))
+    f, g = f * (1 + 0.02 * rng.normal(size=f.shape)), g * (1 + 0.02 * rng.normal(size=g.shape))
+    x = to_dev(small, f, g)
+    print("FP64 collision form", n_el, flush=True)
+    want = small.collide(x.clone())
+    fo, go = oracle.collide(cfg, f, g)
+    F, G = to_np(want)
+    assert rel_err(F, fo) < 1e-12 and rel_err(G, go) < 1e-12
+    reps = -(-ctx.nodes // 32)
+    got = ctx.collide(x.repeat(1, 1, reps)[:, :, :ctx.nodes].contiguous())
+    assert float((got - want.repeat(1, 1, reps)[:, :, :ctx.nodes]).abs().max() / want.abs().max()) <= 1e-13
