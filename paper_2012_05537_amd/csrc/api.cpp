@@ -694,7 +694,7 @@ int sllbm_set_displacement(sllbm_ctx *ctx, const double *d)
     build_mapped_inverse(ctx->vs.q, N, ncells, cell, minv, minv_start);
     std::vector<int32_t> mchunk, mrstart;
     int nch = 0;
-    const MappedRuns runs = mapped_runs(ctx->geo.p, ctx->geo.nel[0], ctx->elem);
+    const MappedRuns runs = mapped_runs(ctx->geo.p, ctx->geo.nel, ctx->elem);
     if (by_cell) {
         // the local coordinates in list order, as the kernels read them
         std::vector<double> sorted(tloc.size());

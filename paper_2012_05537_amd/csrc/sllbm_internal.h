@@ -175,12 +175,17 @@ constexpr int MAPPED_MIN_WAVES = 5;                           // waves per SIMD 
 constexpr int MAPPED_LIST_ORDER = 3;
 // It runs over runs of cells along x; a run's source rows fit MAPPED_RUN_BYTES.
 constexpr int MAPPED_RUN_BYTES = 32 * 1024;
+// and they are shorter while the grid has fewer than MAPPED_TARGET_RUNS of them: two
+// blocks per CU (4 x 1 x 1 cells, p = 6, FP64: 45 blocks 12.4 us, 180 6.9; 16 x 2 x 2, p = 4:
+// 9.7, 7.2 and 9.1 us with 360, 720 and 2880; 6 x 6 x 6, p = 3: 7.4 and 9.5 with 1620 and
+// 4860).
+constexpr int MAPPED_TARGET_RUNS = 512;
 struct MappedRuns {
     int cells;      // cells of a run (the last one of a row may be shorter), at most 16
     int nx;         // runs per row of cells
     int width;      // nodes of a staged row: cells * p + 1, made odd (LDS banks)
 };
-MappedRuns mapped_runs(int p, int nel_x, size_t elem);
+MappedRuns mapped_runs(int p, const int nel[3], size_t elem);
 // Its grid, runs x Q blocks of 256 threads; false where HIP cannot launch it (a
 // grid dimension has less than 2^32 threads, and the kernel counts blocks in 31 bits).
 bool mapped_run_grid(const MappedRuns &r, const int nel[3], unsigned &runs);

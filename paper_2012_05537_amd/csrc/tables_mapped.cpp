@@ -280,14 +280,17 @@ void build_mapped_inverse(int q, int64_t nodes, int ncells, const std::vector<in
     }
 }
 
-MappedRuns mapped_runs(int p, int nel_x, size_t elem)
+MappedRuns mapped_runs(int p, const int nel[3], size_t elem)
 {
     const int most = MAPPED_RUN_BYTES / static_cast<int>(2 * (p + 1) * (p + 1) * elem);   // nodes per row
-    const int cells = std::max(1, std::min(16, (most - 2) / p));
+    int cells = std::max(1, std::min(16, (most - 2) / p));
+    const int64_t rows = static_cast<int64_t>(nel[1]) * nel[2];
+    const int64_t want = (MAPPED_TARGET_RUNS + Q * rows - 1) / (Q * rows);    // runs per row of cells
+    cells = std::min<int64_t>(cells, std::max<int64_t>(1, nel[0] / want));
     MappedRuns r;
-    r.nx = (nel_x + cells - 1) / cells;
-    r.cells = (nel_x + r.nx - 1) / r.nx;                  // runs of about equal length
-    r.nx = (nel_x + r.cells - 1) / r.cells;
+    r.nx = (nel[0] + cells - 1) / cells;
+    r.cells = (nel[0] + r.nx - 1) / r.nx;                 // runs of about equal length
+    r.nx = (nel[0] + r.cells - 1) / r.cells;
     r.width = (r.cells * p + 1) | 1;
     return r;
 }

@@ -25,7 +25,7 @@ static int run_grids()
                     if (static_cast<int64_t>(a) * b * c * p * p * p > 60000000) continue;
                     for (size_t elem : {sizeof(float), sizeof(double)}) {
                         unsigned runs = 0;
-                        const MappedRuns r = mapped_runs(p, a, elem);
+                        const MappedRuns r = mapped_runs(p, n, elem);
                         if (!mapped_run_grid(r, n, runs)) return fail("no launch", n, p);
                         if (runs != static_cast<int64_t>(r.nx) * b * c || static_cast<int64_t>(runs) * 256 >> 32)
                             return fail("grid", n, p);
@@ -124,12 +124,32 @@ static int nontemporal_rows()
     return seen ? 0 : 1;
 }
 
+// runs cover the row of cells, fit their LDS, and are single cells before a grid has
+// fewer than two blocks per CU
+static int short_runs()
+{
+    for (int p = 3; p <= 6; ++p)
+        for (int a = 1; a <= 40; ++a)
+            for (int b : {1, 2, 3, 7, 16})
+                for (size_t elem : {sizeof(float), sizeof(double)}) {
+                    const int n[3] = {a, b, b};
+                    const MappedRuns r = mapped_runs(p, n, elem);
+                    if (!covers(r.nx, r.cells, a) || r.cells < 1 || r.cells > 16) return fail("cells", n, p);
+                    if (r.width < r.cells * p + 1 || r.width % 2 == 0) return fail("width", n, p);
+                    if (2 * (p + 1) * (p + 1) * r.width * elem > MAPPED_RUN_BYTES) return fail("LDS", n, p);
+                    // (runs of equal length: a row of 5 cells has 3 or 5 of them)
+                    if (r.cells > 2 && Q * r.nx * b * b < 512) return fail("blocks", n, p);
+                }
+    return 0;
+}
+
 int main(int argc, char **argv)
 {
     if (argc == 2 && !std::strcmp(argv[1], "run_grids")) return run_grids();
     if (argc == 2 && !std::strcmp(argv[1], "layouts")) return layouts();
     if (argc == 2 && !std::strcmp(argv[1], "lds_of_block")) return lds_of_block();
     if (argc == 2 && !std::strcmp(argv[1], "nontemporal_rows")) return nontemporal_rows();
+    if (argc == 2 && !std::strcmp(argv[1], "short_runs")) return short_runs();
     std::printf("unknown check\n");
     return 1;
 }

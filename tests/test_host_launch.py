@@ -23,7 +23,7 @@ def driver(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("check", ["run_grids", "layouts", "lds_of_block", "nontemporal_rows"])
+@pytest.mark.parametrize("check", ["run_grids", "layouts", "lds_of_block", "nontemporal_rows", "short_runs"])
 def test_launch(driver, check):
     out = subprocess.run([driver, check], capture_output=True, text=True)
     assert out.returncode == 0, out.stdout + out.stderr
