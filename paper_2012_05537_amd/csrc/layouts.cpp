@@ -70,7 +70,9 @@ YLayout y_layout(const Geometry &g)
     double best = 0.0;
     const int most = g.nodes <= 65536 ? 256 : YNT;         // lanes; small grids need the blocks
     const bool whole = g.N[0] <= most;
-    const int nc = y_cells(g.p), groups = (g.nel[1] + nc - 1) / nc;
+    // a tube of one cell has no second one to load (3200 x 1 cells, p = 1, FP64: 2.75 us,
+    // and 3.07 with eight cells per lane; 800 x 1, p = 4: 3.58 and 3.92)
+    const int nc = g.nel[1] == 1 ? 1 : y_cells(g.p), groups = (g.nel[1] + nc - 1) / nc;
     const int t0 = whole ? g.nel[0] : 63 / g.p, t1 = whole ? g.nel[0] : (most - 1) / g.p;
     for (int txc = t0; txc <= t1; ++txc) {
         const int cx = whole ? g.N[0] : txc * g.p + 1, ntx = (g.nel[0] + txc - 1) / txc;
@@ -79,7 +81,7 @@ YLayout y_layout(const Geometry &g)
             const double used = static_cast<double>(groups) * g.N[0] / (static_cast<double>(nt) * ntx * nty);
             if (used >= best) {
                 best = used;
-                b = YLayout{cx, txc, tyg, ntx, nty, nt, 1.0f / static_cast<float>(cx), 0};
+                b = YLayout{cx, txc, tyg, ntx, nty, nt, 1.0f / static_cast<float>(cx), nc, 0};
             }
         }
     }

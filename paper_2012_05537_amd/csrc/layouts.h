@@ -52,16 +52,17 @@ constexpr int z_columns(int nt)
 
 ZLayout z_layout(const Geometry &g, bool transpose, size_t elem);
 
-// Two dimensions (k_stream_y): tyg groups of y_cells(p) cells along y and cx
+// Two dimensions (k_stream_y): tyg groups of nc cells along y and cx
 // columns of each per block; txc cells along x per tile (the whole row if ntx = 1)
 constexpr int YNT = 512;              // most threads per block
 struct YLayout {
     int cx, txc, tyg, ntx, nty, nt;
     float rcx;
+    int nc;                           // source cells per lane: y_cells(p), or 1
     unsigned blocks;                  // per plane (0: too many)
 };
 
-// source cells per lane
+// source cells per lane where there is more than one along y
 constexpr int y_cells(int p) { return p >= 5 ? 1 : p >= 3 ? 2 : p == 2 ? 4 : 8; }
 
 YLayout y_layout(const Geometry &g);

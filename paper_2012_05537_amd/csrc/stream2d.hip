@@ -33,11 +33,11 @@ __device__ __forceinline__ int wrap2(int x, int n)
 // 4, 24 us in FP64 (6.5 TB/s) and 14 us in FP32; 1024^2 115 us; 510^2 at P = 6 25 us.
 // The march along y that this replaces (strips of 256 columns, chunks of 16
 // cells, each row interpolated along x out of LDS) took 26, 17, 127 and 33 us.
-template <typename S, int P>
+template <typename S, int P, int NC>
 __global__ void __launch_bounds__(YNT) k_stream_y(Geometry g, CellTables<S> tab, const S *__restrict__ in,
                                                   S *__restrict__ out, YLayout lay)
 {
-    constexpr int NC = y_cells(P), R = NC * P + 1;
+    constexpr int R = NC * P + 1;
     __shared__ S buf[NC * P][YNT];
     const int tid = threadIdx.x;
     const int tiles = lay.ntx * lay.nty;
@@ -130,7 +130,11 @@ template <typename S, int P>
 hipError_t launch_y(const Geometry &g, const CellTables<S> &t, const YLayout &lay, const S *in, S *out, hipStream_t st)
 {
     if (lay.blocks == 0) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((k_stream_y<S, P>), dim3(lay.blocks, 2 * Q2D), dim3(lay.nt), 0, st, g, t, in, out, lay);
+    if (lay.nc == 1)
+        hipLaunchKernelGGL((k_stream_y<S, P, 1>), dim3(lay.blocks, 2 * Q2D), dim3(lay.nt), 0, st, g, t, in, out, lay);
+    else
+        hipLaunchKernelGGL((k_stream_y<S, P, y_cells(P)>), dim3(lay.blocks, 2 * Q2D), dim3(lay.nt), 0, st, g, t, in, out,
+                           lay);
     return hipGetLastError();
 }
 

@@ -78,7 +78,8 @@ static int layouts()
                 Geometry g = geometry(n, p);
                 g.nodes = static_cast<int64_t>(g.N[0]) * g.N[1];
                 const YLayout l = y_layout(g);
-                const int groups = (b + y_cells(p) - 1) / y_cells(p);
+                if (l.nc != (b == 1 ? 1 : y_cells(p))) return fail("cells per lane (2-D)", n, p);
+                const int groups = (b + l.nc - 1) / l.nc;
                 if (!covers(l.ntx, l.txc, a) || !covers(l.nty, l.tyg, groups)) return fail("cells (2-D)", n, p);
                 if (l.nt > YNT || l.nt % 64 || l.cx * l.tyg > l.nt) return fail("threads (2-D)", n, p);
                 if (l.cx != (l.ntx == 1 ? g.N[0] : l.txc * p + 1)) return fail("columns (2-D)", n, p);
