@@ -326,14 +326,15 @@ static hipError_t collide_lat(const Geometry &g, const CollisionParams &cp, cons
         // 14.4 us, 63^3 37.9 -> 34.5, 129^3 390 -> 348, 243^3 2.78 -> 2.24 ms, but 39 x 33 x 27
         // the step 21.9 -> 22.7; FP64 129^3 700 -> 673 us, but 45^3 26.3 -> 28.1.
         constexpr int NB = 512 / sizeof(S), VL = 16 / sizeof(S);
-        // D3Q45 in FP64 keeps the register form between one block per CU and two rounds
-        // of three (26^3 nodes 9.4 us staged and 8.0, 30^3 10.0 and 8.5, 40^3 19.5 and 15.9,
-        // 46^3 27.4 and 24.8; 24^3 6.8 and 8.8, 48^3 28.4 and 28.6; steps alike).
+        // D3Q45 in FP64 keeps the register form between one block per CU and the size where
+        // two states fill the Infinity Cache (26^3 nodes 9.4 us staged and 8.0, 30^3 10.0 and
+        // 8.5, 40^3 19.5 and 15.9, 46^3 27.4 and 24.8, 50^3 33.6 and 30.4, 54^3 39.6 and 38.1; 24^3
+        // 6.8 and 8.8, 60^3 50.8 and 49.5, 62^3 56.6 and 56.9; steps alike).
         constexpr bool D3 = L::Q == 45, NO_NT = D3 && sizeof(S) == 8;
-        const bool few_rounds = NO_NT && g.nodes > 256 * NB && g.nodes <= 2 * 3 * 256 * NB;
+        const bool in_registers = NO_NT && g.nodes > 256 * NB && 2 * bytes <= INFINITY_CACHE_BYTES;
         const bool wide = g.nodes % VL == 0 && reinterpret_cast<uintptr_t>(in) % 16 == 0;
         const bool by_words = D3 && (sizeof(S) == 4 ? g.nodes > 65536 : bytes > INFINITY_CACHE_BYTES);
-        if ((wide || by_words) && !(NO_NT && nt) && !few_rounds) {
+        if ((wide || by_words) && !(NO_NT && nt) && !in_registers) {
             auto launch = [&](auto nth, auto wd) {
                 hipLaunchKernelGGL((k_collide_lds<S, L, decltype(nth)::value, decltype(wd)::value>),
                                    dim3(static_cast<unsigned>((g.nodes + NB - 1) / NB)), dim3(2 * NB), 0, st, g.nodes,

@@ -113,9 +113,9 @@ def test_fp64_reverse_step_forms_agree(n_el, p):
     assert float(dmu[1]) == pytest.approx(reps * float(dmu[0]), rel=1e-10)
 
 
-# FP64 collision: staged up to one block of 64 nodes per CU, in registers up to two
-# rounds of three blocks, staged beyond
-@pytest.mark.parametrize("n_el", [(32, 32, 16), (114, 48, 3), (64, 48, 32), (114, 62, 14)])
+# FP64 collision: staged up to one block of 64 nodes per CU, in registers while two
+# states fit the Infinity Cache (186,413 nodes), staged beyond
+@pytest.mark.parametrize("n_el", [(32, 32, 16), (114, 48, 3), (64, 56, 52), (74, 60, 42)])
 def test_fp64_collision_forms_agree(oracle, n_el):
     """Collision of a grid of copies of a small one, whose collision is checked against
     the oracle (1e-12, the repository's bar): equal to rounding (1e-13)."""
