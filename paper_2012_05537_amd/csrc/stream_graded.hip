@@ -497,6 +497,10 @@ bool graded_by_cell(const Geometry &g, bool transpose, int most, int my, size_t 
 {
     if (g.N[0] > 64 * GCW || most == 0 || g.p < (transpose ? 2 : 3)) return false;
     const GcLayout b = gc_layout(g);
+    // one block per plane: at order 6 its chain is longer than the march's (without launch
+    // overhead, 2 x 3 x 1 cells: 11.7 against 11.2 us in FP64, 11.5 and 10.1 in FP32; two
+    // blocks, 2 x 2 x 2: 10.5 against 15.4 and 10.1 against 13.8; order 5, 2 x 3 x 1, FP32 8.2 and 8.1)
+    if (!transpose && g.p == 6 && b.nty * g.nel[2] == 1) return false;
     return transpose || 2 * elem * b.tyc * ((my + 1) / 2 * 2) * b.cw * 64 <= 64 * 1024;
 }
 

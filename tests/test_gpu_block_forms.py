@@ -45,6 +45,28 @@ def test_streaming_by_block_size(oracle, precision, n_el, p):
     assert np.all(np.abs(lhs - rhs) <= tol * (np.abs(fg * y).sum(-1) + np.abs(x * st).sum(-1)))
 
 
+# order 6 with one block per plane (marched) and two
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("n_el", [(1, 1, 1), (2, 3, 1), (7, 4, 1), (7, 5, 1), (2, 3, 2)])
+def test_graded_streaming_of_few_cells(oracle, precision, n_el):
+    """Graded S of order 6 against the oracle (1e-12, FP32 1e-5)."""
+    from paper_2012_05537_amd.sllbm import SLLBM
+    rng = np.random.default_rng(sum(n_el))
+    widths = []
+    for n in n_el:
+        w = 1.0 + 0.4 * rng.uniform(-1.0, 1.0, n)
+        widths.append(w * (2 * np.pi / w.sum()))
+    ctx = SLLBM(n_el, 6, 0.2, 0.01, precision=precision)
+    ctx.set_mesh(*widths)
+    cfg = oracle.make_cfg(n_el, 6, 0.2, 0.01, widths=widths)
+    x = rng.normal(size=(2, Q, ctx.nodes)).astype(np.float32).astype(np.float64)
+    print("graded, few cells", precision, n_el, flush=True)
+    F, G = to_np(ctx.stream(to_dev(ctx, x[0], x[1])))
+    f, g = oracle.stream(cfg, x[0], x[1])
+    tol = 1e-5 if precision else 1e-12
+    assert rel_err(F, f) < tol and rel_err(G, g) < tol
+
+
 # states larger than the Infinity Cache, x rows of whole cache lines: non-temporal
 # stores, at every order in both precisions, blocks of 64 to 1024 threads
 LARGE = [((80, 70, 70), 1, 0), ((40, 36, 37), 2, 0), ((16, 32, 31), 3, 0), ((20, 20, 20), 4, 0), ((8, 13, 57), 4, 0),
