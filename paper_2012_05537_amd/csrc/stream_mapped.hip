@@ -48,7 +48,7 @@ __device__ __forceinline__ void lagrange_weights(const GlcBasis &gb, const doubl
     }
 }
 
-// G elements (4 or 5) of a cell and their weights: f into a0, a1 in turn, g into
+// G elements (8 or 9) of a cell and their weights: f into a0, a1 in turn, g into
 // b0, b1.  Element k sits in lane (E + k) % 16 of its 16-lane row and enters its
 // FMAs as a row broadcast (row_newbcast).  A register that a vector instruction
 // wrote may be read by such an FMA no less than two wait states later, and the
@@ -57,40 +57,61 @@ __device__ __forceinline__ void lagrange_weights(const GlcBasis &gb, const doubl
 // one sum have three others between them.
 #define SLLBM_ROW_FMA(OP, ACC, SRC, W, LANE) \
     OP " %" #ACC ", %" #SRC ", %" #W " row_newbcast:%" #LANE " row_mask:0xf bank_mask:0xf\n\t"
-#define SLLBM_ROW_FMAS(S, OP)                                                                                         \
-    template <int E, int G, int NR, int NW>                                                                           \
-    __device__ __forceinline__ void fma_rows(S &a0, S &a1, S &b0, S &b1, const S (&vf)[NR], const S (&vg)[NR],        \
-                                             const S (&w)[NW], int wi)                                                \
-    {                                                                                                                 \
-        static_assert(G == 4 || G == 5, "elements per block");                                                        \
-        if constexpr (G == 4)                                                                                         \
-            asm("s_nop 1\n\t"                                                                                         \
-                SLLBM_ROW_FMA(OP, 0, 4, 12, 16) SLLBM_ROW_FMA(OP, 2, 8, 12, 16)                                       \
-                SLLBM_ROW_FMA(OP, 1, 5, 13, 17) SLLBM_ROW_FMA(OP, 3, 9, 13, 17)                                       \
-                SLLBM_ROW_FMA(OP, 0, 6, 14, 18) SLLBM_ROW_FMA(OP, 2, 10, 14, 18)                                      \
-                SLLBM_ROW_FMA(OP, 1, 7, 15, 19) SLLBM_ROW_FMA(OP, 3, 11, 15, 19)                                      \
-                : "+&v"(a0), "+&v"(a1), "+&v"(b0), "+&v"(b1)                                                          \
-                : "v"(vf[E / 16]), "v"(vf[(E + 1) / 16]), "v"(vf[(E + 2) / 16]), "v"(vf[(E + 3) / 16]),               \
-                  "v"(vg[E / 16]), "v"(vg[(E + 1) / 16]), "v"(vg[(E + 2) / 16]), "v"(vg[(E + 3) / 16]),               \
-                  "v"(w[wi]), "v"(w[wi + 1]), "v"(w[wi + 2]), "v"(w[wi + 3]),                                         \
-                  "n"(E % 16), "n"((E + 1) % 16), "n"((E + 2) % 16), "n"((E + 3) % 16));                              \
-        else                                                                                                          \
-            asm("s_nop 1\n\t"                                                                                         \
-                SLLBM_ROW_FMA(OP, 0, 4, 14, 19) SLLBM_ROW_FMA(OP, 2, 9, 14, 19)                                       \
-                SLLBM_ROW_FMA(OP, 1, 5, 15, 20) SLLBM_ROW_FMA(OP, 3, 10, 15, 20)                                      \
-                SLLBM_ROW_FMA(OP, 0, 6, 16, 21) SLLBM_ROW_FMA(OP, 2, 11, 16, 21)                                      \
-                SLLBM_ROW_FMA(OP, 1, 7, 17, 22) SLLBM_ROW_FMA(OP, 3, 12, 17, 22)                                      \
-                SLLBM_ROW_FMA(OP, 0, 8, 18, 23) SLLBM_ROW_FMA(OP, 2, 13, 18, 23)                                      \
-                : "+&v"(a0), "+&v"(a1), "+&v"(b0), "+&v"(b1)                                                          \
-                : "v"(vf[E / 16]), "v"(vf[(E + 1) / 16]), "v"(vf[(E + 2) / 16]), "v"(vf[(E + 3) / 16]),               \
-                  "v"(vf[(E + 4) / 16]), "v"(vg[E / 16]), "v"(vg[(E + 1) / 16]), "v"(vg[(E + 2) / 16]),               \
-                  "v"(vg[(E + 3) / 16]), "v"(vg[(E + 4) / 16]), "v"(w[wi]), "v"(w[wi + 1]), "v"(w[wi + 2]),           \
-                  "v"(w[wi + 3]), "v"(w[wi + 4]), "n"(E % 16), "n"((E + 1) % 16), "n"((E + 2) % 16),                  \
-                  "n"((E + 3) % 16), "n"((E + 4) % 16));                                                              \
+#define SLLBM_AT(V, K) V[(E + K) / 16]
+#define SLLBM_ROW_FMAS(S, OP)                                                                                  \
+    template <int E, int G, int NR, int NW>                                                                    \
+    __device__ __forceinline__ void fma_rows(S &a0, S &a1, S &b0, S &b1, const S (&vf)[NR], const S (&vg)[NR], \
+                                             const S (&w)[NW], int wi)                                         \
+    {                                                                                                          \
+        static_assert(G == 8 || G == 9, "elements per block");                                                 \
+        if constexpr (G == 8)                                                                                  \
+            asm("s_nop 1\n\t"                                                                                  \
+                SLLBM_ROW_FMA(OP, 0, 4, 20, 28) SLLBM_ROW_FMA(OP, 2, 12, 20, 28)                               \
+                SLLBM_ROW_FMA(OP, 1, 5, 21, 29) SLLBM_ROW_FMA(OP, 3, 13, 21, 29)                               \
+                SLLBM_ROW_FMA(OP, 0, 6, 22, 30) SLLBM_ROW_FMA(OP, 2, 14, 22, 30)                               \
+                SLLBM_ROW_FMA(OP, 1, 7, 23, 31) SLLBM_ROW_FMA(OP, 3, 15, 23, 31)                               \
+                SLLBM_ROW_FMA(OP, 0, 8, 24, 32) SLLBM_ROW_FMA(OP, 2, 16, 24, 32)                               \
+                SLLBM_ROW_FMA(OP, 1, 9, 25, 33) SLLBM_ROW_FMA(OP, 3, 17, 25, 33)                               \
+                SLLBM_ROW_FMA(OP, 0, 10, 26, 34) SLLBM_ROW_FMA(OP, 2, 18, 26, 34)                              \
+                SLLBM_ROW_FMA(OP, 1, 11, 27, 35) SLLBM_ROW_FMA(OP, 3, 19, 27, 35)                              \
+                : "+&v"(a0), "+&v"(a1), "+&v"(b0), "+&v"(b1)                                                   \
+                : "v"(SLLBM_AT(vf, 0)), "v"(SLLBM_AT(vf, 1)), "v"(SLLBM_AT(vf, 2)), "v"(SLLBM_AT(vf, 3)),      \
+                  "v"(SLLBM_AT(vf, 4)), "v"(SLLBM_AT(vf, 5)), "v"(SLLBM_AT(vf, 6)), "v"(SLLBM_AT(vf, 7)),      \
+                  "v"(SLLBM_AT(vg, 0)), "v"(SLLBM_AT(vg, 1)), "v"(SLLBM_AT(vg, 2)), "v"(SLLBM_AT(vg, 3)),      \
+                  "v"(SLLBM_AT(vg, 4)), "v"(SLLBM_AT(vg, 5)), "v"(SLLBM_AT(vg, 6)), "v"(SLLBM_AT(vg, 7)),      \
+                  "v"(w[wi + 0]), "v"(w[wi + 1]), "v"(w[wi + 2]), "v"(w[wi + 3]),                              \
+                  "v"(w[wi + 4]), "v"(w[wi + 5]), "v"(w[wi + 6]), "v"(w[wi + 7]),                              \
+                  "n"((E + 0) % 16), "n"((E + 1) % 16), "n"((E + 2) % 16), "n"((E + 3) % 16),                  \
+                  "n"((E + 4) % 16), "n"((E + 5) % 16), "n"((E + 6) % 16), "n"((E + 7) % 16));                 \
+        else                                                                                                   \
+            asm("s_nop 1\n\t"                                                                                  \
+                SLLBM_ROW_FMA(OP, 0, 4, 22, 31) SLLBM_ROW_FMA(OP, 2, 13, 22, 31)                               \
+                SLLBM_ROW_FMA(OP, 1, 5, 23, 32) SLLBM_ROW_FMA(OP, 3, 14, 23, 32)                               \
+                SLLBM_ROW_FMA(OP, 0, 6, 24, 33) SLLBM_ROW_FMA(OP, 2, 15, 24, 33)                               \
+                SLLBM_ROW_FMA(OP, 1, 7, 25, 34) SLLBM_ROW_FMA(OP, 3, 16, 25, 34)                               \
+                SLLBM_ROW_FMA(OP, 0, 8, 26, 35) SLLBM_ROW_FMA(OP, 2, 17, 26, 35)                               \
+                SLLBM_ROW_FMA(OP, 1, 9, 27, 36) SLLBM_ROW_FMA(OP, 3, 18, 27, 36)                               \
+                SLLBM_ROW_FMA(OP, 0, 10, 28, 37) SLLBM_ROW_FMA(OP, 2, 19, 28, 37)                              \
+                SLLBM_ROW_FMA(OP, 1, 11, 29, 38) SLLBM_ROW_FMA(OP, 3, 20, 29, 38)                              \
+                SLLBM_ROW_FMA(OP, 0, 12, 30, 39) SLLBM_ROW_FMA(OP, 2, 21, 30, 39)                              \
+                : "+&v"(a0), "+&v"(a1), "+&v"(b0), "+&v"(b1)                                                   \
+                : "v"(SLLBM_AT(vf, 0)), "v"(SLLBM_AT(vf, 1)), "v"(SLLBM_AT(vf, 2)), "v"(SLLBM_AT(vf, 3)),      \
+                  "v"(SLLBM_AT(vf, 4)), "v"(SLLBM_AT(vf, 5)), "v"(SLLBM_AT(vf, 6)), "v"(SLLBM_AT(vf, 7)),      \
+                  "v"(SLLBM_AT(vf, 8)),                                                                        \
+                  "v"(SLLBM_AT(vg, 0)), "v"(SLLBM_AT(vg, 1)), "v"(SLLBM_AT(vg, 2)), "v"(SLLBM_AT(vg, 3)),      \
+                  "v"(SLLBM_AT(vg, 4)), "v"(SLLBM_AT(vg, 5)), "v"(SLLBM_AT(vg, 6)), "v"(SLLBM_AT(vg, 7)),      \
+                  "v"(SLLBM_AT(vg, 8)),                                                                        \
+                  "v"(w[wi + 0]), "v"(w[wi + 1]), "v"(w[wi + 2]), "v"(w[wi + 3]),                              \
+                  "v"(w[wi + 4]), "v"(w[wi + 5]), "v"(w[wi + 6]), "v"(w[wi + 7]),                              \
+                  "v"(w[wi + 8]),                                                                              \
+                  "n"((E + 0) % 16), "n"((E + 1) % 16), "n"((E + 2) % 16), "n"((E + 3) % 16),                  \
+                  "n"((E + 4) % 16), "n"((E + 5) % 16), "n"((E + 6) % 16), "n"((E + 7) % 16),                  \
+                  "n"((E + 8) % 16));                                                                          \
     }
 SLLBM_ROW_FMAS(double, "v_fmac_f64_dpp")
 SLLBM_ROW_FMAS(float, "v_fmac_f32_dpp")
 #undef SLLBM_ROW_FMAS
+#undef SLLBM_AT
 #undef SLLBM_ROW_FMA
 
 // sf, sg += sum over the cell's elements E, E + 1, ... of weight times value.
@@ -100,7 +121,7 @@ template <typename S, int P, int E, int NR>
 __device__ __forceinline__ void cell_sum(const S (&vf)[NR], const S (&vg)[NR], const S (&wxy)[(P + 1) * (P + 1)],
                                          const S (&wz)[P + 1], S (&z)[4], S &sf, S &sg)
 {
-    constexpr int K = P + 1, K2 = K * K, e = E % K2, G = (K2 - e) % 4 == 0 ? 4 : 5;
+    constexpr int K = P + 1, K2 = K * K, e = E % K2, G = (K2 - e) % 8 == 0 ? 8 : 9;
     fma_rows<E, G>(z[e % 2], z[1 - e % 2], z[2 + e % 2], z[3 - e % 2], vf, vg, wxy, e);
     if constexpr (e + G == K2) {
         sf = fma(wz[E / K2], z[0] + z[1], sf);
