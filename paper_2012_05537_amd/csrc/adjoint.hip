@@ -951,12 +951,17 @@ hipError_t Launch<S>::collide_vjp(const Geometry &g, const CollisionParams &cp, 
         }
     } else {
         blocks = static_cast<int>((2 * g.nodes + 255) / 256);
-        if (nt)
-            hipLaunchKernelGGL((k_collide_vjp<S, true>), dim3(static_cast<unsigned>(blocks)), dim3(256), 0, st,
-                               g.nodes, cp, state_n, lam, lam, dmu ? dmu_partials : nullptr);
-        else
-            hipLaunchKernelGGL((k_collide_vjp<S, false>), dim3(static_cast<unsigned>(blocks)), dim3(256), 0, st,
-                               g.nodes, cp, state_n, lam, lam, dmu ? dmu_partials : nullptr);
+        auto launch = [&](auto nth) {
+            hipLaunchKernelGGL((k_collide_vjp<S, decltype(nth)::value>), dim3(static_cast<unsigned>(blocks)), dim3(256), 0,
+                               st, g.nodes, cp, state_n, lam, lam, dmu ? dmu_partials : nullptr);
+        };
+        // (FP32: only small grids come here)
+        if constexpr (sizeof(S) == 4) {
+            launch(std::false_type());
+        } else {
+            if (nt) launch(std::true_type());
+            else launch(std::false_type());
+        }
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
