@@ -8,9 +8,16 @@
 
 namespace sllbm {
 
-// Byte offset of a node in an x-y plane: 32 bits suffice (the 90 planes of a
-// state whose x-y plane had 4 GB would not fit the card), so that an access is
-// a uniform row address plus one register per lane.
+// x modulo n, in 0 .. n - 1
+__device__ __forceinline__ int wrapi(int x, int n)
+{
+    const int r = x % n;
+    return r < 0 ? r + n : r;
+}
+
+// Byte offset of a node in an x-y plane: 32 bits suffice (two states, of 90 planes or
+// in two dimensions 38, whose x-y plane had 4 GB would not fit the card), so that an
+// access is a uniform row address plus one register per lane.
 template <typename S>
 __device__ __forceinline__ uint32_t plane_offset(int node)
 {

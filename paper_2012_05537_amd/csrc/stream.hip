@@ -23,16 +23,6 @@
 
 namespace sllbm {
 
-namespace {
-
-__device__ __forceinline__ int wrapi(int x, int n)
-{
-    int r = x % n;
-    return r < 0 ? r + n : r;
-}
-
-}  // namespace
-
 template <typename S, int P, int NT>
 constexpr int z_min_waves()
 {

@@ -19,16 +19,6 @@
 
 namespace sllbm {
 
-namespace {
-
-__device__ __forceinline__ int wrap2(int x, int n)
-{
-    int r = x % n;
-    return r < 0 ? r + n : r;
-}
-
-}  // namespace
-
 // Bound by HBM and, while two states fit it, the Infinity Cache: 512^2 nodes, P =
 // 4, 24 us in FP64 (6.5 TB/s) and 14 us in FP32; 1024^2 115 us; 510^2 at P = 6 25 us.
 // The march along y that this replaces (strips of 256 columns, chunks of 16
@@ -74,14 +64,14 @@ __global__ void __launch_bounds__(YNT) k_stream_y(Geometry g, CellTables<S> tab,
     if (whole) {
         xo = xl;
         row = xl % P;
-        cell = xl / P + wrap2(omx, g.nel[0]) + (row >= lsx ? 1 : 0);
+        cell = xl / P + wrapi(omx, g.nel[0]) + (row >= lsx ? 1 : 0);
         cell -= cell >= g.nel[0] ? g.nel[0] : 0;
         cell -= cell >= g.nel[0] ? g.nel[0] : 0;
     } else {
         cell = xl / P;
         const int j = lsx + xl % P;
         row = j % P;
-        xo = wrap2((cx0 - omx - 1) * P, Nx) + cell * P + j;          // below 2 N_x + P
+        xo = wrapi((cx0 - omx - 1) * P, Nx) + cell * P + j;          // below 2 N_x + P
         xo -= xo >= Nx ? Nx : 0;
         xo -= xo >= Nx ? Nx : 0;
     }
@@ -105,7 +95,7 @@ __global__ void __launch_bounds__(YNT) k_stream_y(Geometry g, CellTables<S> tab,
         }
     }
     __syncthreads();
-    int y = wrap2((ty * lay.tyg * NC - omy - 1) * P, Ny) + gl * NC * P + lsy;   // first output row
+    int y = wrapi((ty * lay.tyg * NC - omy - 1) * P, Ny) + gl * NC * P + lsy;   // first output row
     y -= y >= Ny ? Ny : 0;
     y -= y >= Ny ? Ny : 0;
 #pragma unroll

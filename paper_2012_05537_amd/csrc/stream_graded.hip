@@ -29,12 +29,6 @@ namespace sllbm {
 
 namespace {
 
-__device__ __forceinline__ int wrapg(int x, int n)
-{
-    int r = x % n;
-    return r < 0 ? r + n : r;
-}
-
 constexpr int GTX = 32, GTY = 8, GNT = GTX * GTY;
 constexpr int GRB = 2;                         // source z-rows interpolated per batch
 constexpr int64_t GRADED_TARGET_BLOCKS = 2048;
@@ -97,7 +91,7 @@ __global__ void __launch_bounds__(GNT) k_stream_graded(Geometry g, NodeTables<S>
     for (int k = 0; k < LK; ++k) {
         const int e = min(tid + k * GNT, nwin - 1);
         const int wy_ = e / wxv, wx_ = (e - wy_ * wxv) * V;
-        loff[k] = wrapg(ys0 + wy_, Ny) * Nx + wrapg(xs0 + wx_, Nx);
+        loff[k] = wrapi(ys0 + wy_, Ny) * Nx + wrapi(xs0 + wx_, Nx);
         soff[k] = wy_ * wxm + wx_;
     }
 
@@ -122,7 +116,7 @@ __global__ void __launch_bounds__(GNT) k_stream_graded(Geometry g, NodeTables<S>
     auto load_batch = [&](int r) {
 #pragma unroll
         for (int b = 0; b < RB; ++b) {
-            const S *base = src + static_cast<int64_t>(wrapg(r + b, Nz)) * NP;
+            const S *base = src + static_cast<int64_t>(wrapi(r + b, Nz)) * NP;
 #pragma unroll
             for (int k = 0; k < LK; ++k) raw[b][k] = *reinterpret_cast<const VT *>(base + loff[k]);
         }
@@ -236,11 +230,11 @@ __global__ void __launch_bounds__(64 * GCW) k_stream_graded_cells(Geometry g, Ce
     S wx[K];
 #pragma unroll
     for (int k = 0; k < K; ++k) wx[k] = tab.w[0][(static_cast<int64_t>(i) * Nx + xc) * K + k];
-    const int b0 = wrapg(tab.src[0][static_cast<int64_t>(i) * Nx + xc], Nx), bl = wrap1(b0 + P, Nx);
+    const int b0 = wrapi(tab.src[0][static_cast<int64_t>(i) * Nx + xc], Nx), bl = wrap1(b0 + P, Nx);
     const Uniform<S> wyt = (Uniform<S>)(tab.w[1] + static_cast<int64_t>(i) * Ny * K);
     const Uniform<S> wzt = (Uniform<S>)(tab.w[2] + static_cast<int64_t>(i) * Nz * K);
     const int cx = cw * 64;
-    int yo0 = wrapg(y0, Ny), zo = wrapg(z0, Nz);
+    int yo0 = wrapi(y0, Ny), zo = wrapi(z0, Nz);
     for (int l = 0; l < mz; ++l) {
         S *cell = lds + (static_cast<size_t>(l & 1) * tyc + cyl) * rows * cx;
         S t[K];
@@ -328,8 +322,8 @@ __global__ void __launch_bounds__(64 * GCW) k_stream_graded_cells_t(Geometry g, 
     int rowo[2][MO];
 #pragma unroll
     for (int j = 0; j < MO; ++j) {
-        rowo[0][j] = wrapg(r1 + min(j, max(m1 - 1, 0)), Ny) * Nx;
-        rowo[1][j] = wrapg(r0 + min(j, max(m0 - 1, 0)), Ny) * Nx;
+        rowo[0][j] = wrapi(r1 + min(j, max(m1 - 1, 0)), Ny) * Nx;
+        rowo[1][j] = wrapi(r0 + min(j, max(m0 - 1, 0)), Ny) * Nx;
     }
     Uniform<S> wyc = (Uniform<S>)(tab.tw[1] + (static_cast<int64_t>(i) * g.nel[1] + cy) * MO * K);
     // output column xc: node kx of cell xc / P; its taps along x (surplus ones repeat the last, with weight 0)
@@ -341,7 +335,7 @@ __global__ void __launch_bounds__(64 * GCW) k_stream_graded_cells_t(Geometry g, 
         const S *wxc = tab.tw[0] + (static_cast<int64_t>(i) * g.nel[0] + ex) * MO * K;
         const int s1 = fx[ex], n1 = fx[ex + 1] - s1;
         const int s0 = ex > 0 ? fx[ex - 1] : fx[g.nel[0] - 1] - Nx, n0 = s1 - s0;
-        const int a1 = wrapg(s1, Nx), a0 = wrapg(s0, Nx), team = cyl * cw * 64;
+        const int a1 = wrapi(s1, Nx), a0 = wrapi(s0, Nx), team = cyl * cw * 64;
 #pragma unroll
         for (int j = 0; j < MO; ++j) {
             to[0][j] = team + wrap1(a1 + min(j, max(n1 - 1, 0)), Nx);
@@ -354,7 +348,7 @@ __global__ void __launch_bounds__(64 * GCW) k_stream_graded_cells_t(Geometry g, 
 
     const int zc0 = chunk * zcells, zc1 = min(g.nel[2], zc0 + zcells);
     const int zr = zc0 > 0 ? fz[zc0 - 1] : fz[g.nel[2] - 1] - Nz;      // first row: the group before the block's cells
-    int z = wrapg(zr, Nz);
+    int z = wrapi(zr, Nz);
     S v[2][MO];
     auto load_row = [&] {
         const int64_t zo = z * NP;
