@@ -383,7 +383,8 @@ def measure_line(args, wl, wkey, prec_name, two_d, mesh):
         "nodes": r["nodes"], "order": wl["p"], "cfl": wl.get("cfl"), "dt": wl["dt"],
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS, "traffic": kernels[dom]["traffic"],
-                     "kernel": dom, "kernel_ms": kms, "algorithmic_bytes_per_launch": dom_bytes,
+                     "kernel": dom, "kernel_ms": kms,
+                     "longest_kernel": max(r["kernels"], key=lambda k: r["kernels"][k]["ms"]), "algorithmic_bytes_per_launch": dom_bytes,
                      "step_frac": r["bytes"] / step_s / 1e9 / HBM_PEAK_GBS,
                      "copy_GBps": copy_gbs, "frac_of_copy": achieved / copy_gbs},
         "kernels": kernels,

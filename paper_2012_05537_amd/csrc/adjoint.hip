@@ -4,10 +4,11 @@
 // the node-local collision (Eq. (5) with App. D) and S the semi-Lagrangian
 // streaming (Eq. (9)), which is linear.  Its vector-Jacobian product is
 //   lambda_n = J_C(X_n)^T S^T lambda_{n+1}.
-// S^T is the transposed streaming (stream.hip, stream_graded.hip); this file
+// S^T is the transposed streaming (stream.hip, stream_graded.hip,
+// stream_mapped.hip); this file
 // holds the collision VJP, the VJP of the equilibrium initialisation, and the
-// flow functional used for gradients with its derivative.  All reverse arithmetic is in double; states are stored in the
-// context's storage type.
+// flow functional used for gradients with its derivative.  All reverse arithmetic is
+// in double; states are stored in the context's storage type.
 //
 // Collision VJP (per node, f on the even lane of a pair, g on the odd lane).
 // With adjoints alpha_i of the post-collision values of the lane's population
@@ -396,7 +397,7 @@ __device__ __forceinline__ double block_sum256(double v, double *red)
 // One lane pair per node, alpha in registers; no grid-stride loop, out of
 // which the compiler would hoist the sweep's FP64 constants (230 SGPR
 // spills).  mu and lam may be the same buffer: each lane reads its 45 values
-// before writing them.  255 VGPRs, 2 waves per SIMD; in FP64 6.78 ms at 256^3
+// before writing them.  255 VGPRs and 4 more spilled, 2 waves per SIMD; in FP64 6.78 ms at 256^3
 // nodes (36.2 GB, 5.3 TB/s: HBM-bound), 114 us at 64^3 (175 us with 332
 // registers and one wave per SIMD).
 // NTH: non-temporal loads and stores (states larger than the Infinity Cache)
@@ -429,9 +430,9 @@ __global__ void __launch_bounds__(256, 2) k_collide_vjp(int64_t N, CollisionPara
 // mu and lam may be the same buffer (every copy has landed before the block's
 // first write).
 // Bound by HBM: it reads X and alpha and writes lambda once, 3.53 ms at 256^3
-// nodes in FP32 (18.1 GB, 5.1 TB/s; 166 VGPRs, 3 waves per SIMD), 451 us at
+// nodes in FP32 (18.1 GB, 5.1 TB/s; 166 VGPRs and 6 more spilled, 3 waves per SIMD), 451 us at
 // 128^3 and 63 us at 64^3.  While the sweep's sums sank past the branch on the
-// viscosity law it needed 256 VGPRs with spills (2 waves) and took 5.73 ms.
+// viscosity law it needed 256 VGPRs (2 waves) and took 5.73 ms.
 template <typename S, bool NTH, bool WIDE>
 __global__ void __launch_bounds__(1024 / sizeof(S), sizeof(S) == 4 ? 3 : 2) k_collide_vjp_lds(int64_t N, CollisionParams cp,
                                                             const S *__restrict__ X, const S *mu, S *lam,

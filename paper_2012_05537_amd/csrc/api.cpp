@@ -903,8 +903,8 @@ static hipError_t stream_into(sllbm_ctx *c, const void *in, void *out)
                                   static_cast<float *>(out), c->stream);
 }
 
-// S^T: the transposed z-march (equal cells) or the graded march over the
-// transposed per-node tables
+// S^T: by output cell (equal cells, graded cells), by march over the transposed
+// per-node tables (other graded grids), or by cell and node (distorted cells)
 static hipError_t stream_t_into(sllbm_ctx *c, const void *in, void *out)
 {
     if (c->mapped) {

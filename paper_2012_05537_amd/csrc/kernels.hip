@@ -17,8 +17,9 @@ namespace sllbm {
 
 // Collision of a whole state (Eq. (5) right-hand side with App. D), two
 // lanes per node (f on the even lane, g on the odd one), the values in
-// registers: D3Q45 in FP64 with non-temporal accesses, D2Q19 in FP32, and
-// smaller grids whose rows are not 16-byte aligned.  With non-temporal accesses
+// registers: D3Q45 in FP64 with non-temporal accesses and from one block per CU to
+// two states in the Infinity Cache, D2Q19 in FP32, and smaller grids whose rows are
+// not 16-byte aligned.  With non-temporal accesses
 // the moment sums are pinned before the viscosity branch (pin() in collision.h):
 // D3Q45 then needs 168 VGPRs, 3 waves per SIMD, instead of 224 and 2; in FP64
 // 4.61 -> 4.56 ms at 256^3 nodes (5.3 TB/s, HBM-bound) and 556 -> 532 us at 128^3.  On
@@ -57,7 +58,7 @@ __global__ void __launch_bounds__(256) k_collide(int64_t N, CollisionParams cp, 
 }
 
 // The collision with its values staged in LDS; used for D3Q45 in FP32
-// storage, and in FP64 without non-temporal accesses, and for D2Q19 in FP64.
+// storage, and in FP64 where k_collide is not, and for D2Q19 in FP64.
 // A block collides NB = 512 / sizeof(S) consecutive nodes (128 in FP32, 64 in
 // FP64; blocks in XCD order) with NB / 32 waves.  Their 2Q rows of NB values
 // (row r = pop * Q + i, 512 contiguous bytes of plane r) are copied from memory

@@ -68,7 +68,9 @@ YLayout y_layout(const Geometry &g)
     // the split with the fewest idle lanes
     YLayout b{};
     double best = 0.0;
-    const int most = g.nodes <= 65536 ? 256 : YNT;         // lanes; small grids need the blocks
+    // small grids need the blocks (512 x 64 nodes, p = 4, FP64, without launch overhead: 5.4
+    // us in tiles and 6.4 in whole rows, 400 x 128 7.7 and 8.0; 400 x 400 rows are whole)
+    const int most = g.nodes <= 65536 ? 256 : YNT;         // lanes
     const bool whole = g.N[0] <= most;
     // a tube of one cell has no second one to load (3200 x 1 cells, p = 1, FP64: 2.75 us,
     // and 3.07 with eight cells per lane; 800 x 1, p = 4: 3.58 and 3.92)

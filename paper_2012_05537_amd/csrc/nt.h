@@ -18,8 +18,8 @@ constexpr int64_t INFINITY_CACHE_BYTES = int64_t(256) << 20;   // MI355X
 // row_bytes: distance between the rows that blocks access (a population plane
 // in the node-local kernels, an x row in the streaming).  Unless that is whole
 // cache lines, neighbouring blocks share lines, and the hint drops a line before
-// its other part is read or written (129^3 nodes, FP32: the step 904 us with the
-// hint, 703 without; FP64 1587 and 1342).
+// its other part is read or written (129^3 nodes, FP64: the step 1598 us with the
+// hint, 1335 without; in FP32, collisions staged by words either way, 715 and 720).
 inline bool use_nontemporal(int64_t state_bytes, int64_t row_bytes)
 {
     return state_bytes > INFINITY_CACHE_BYTES && row_bytes % 128 == 0;

@@ -26,7 +26,7 @@ namespace sllbm {
 template <typename S, int P, int NT>
 constexpr int z_min_waves()
 {
-    if (NT > 512) return 4;                                // one block of 1024 threads
+    if (NT > 512) return P == 4 && sizeof(S) == 8 ? NT / 256 : 4;      // (LDS for one block)
     return sizeof(S) == 4 ? (P <= 4 ? 5 : P == 5 ? 4 : 3) : (P <= 3 ? 5 : P == 4 ? 4 : P == 5 ? 3 : 2);
 }
 
@@ -36,7 +36,8 @@ constexpr int z_min_waves()
 // the rate of a copy); 64^3 71 / 29 us, 24^3 (P = 3) 7.0 us, 100^3 nodes
 // at P = 5 294 us.  The march by 32 x 8 and 32 x 16 output tiles that this
 // replaces read a window of P + 1 more rows and columns per tile out of LDS
-// and took 5.2 / 2.9 ms, 89 / 47 us, 11.4 us and 668 us.
+// and took 5.2 / 2.9 ms, 89 / 47 us, 11.4 us and 668 us.  At order 6 in FP64 the uniform
+// weights exceed the scalar registers (76 spilled into lanes of vector registers).
 // NTH: non-temporal output stores (states larger than the Infinity Cache)
 template <typename S, int P, bool NTH, int NT>
 __global__ void __launch_bounds__(NT, (z_min_waves<S, P, NT>()))
@@ -285,7 +286,7 @@ constexpr int zt_depth()
 template <typename S, int P, int NT>
 constexpr int zt_min_waves()
 {
-    if (NT > 512) return 4;                                // one block of 1024 threads
+    if (NT > 512) return P == 4 && sizeof(S) == 8 ? NT / 256 : 4;      // (LDS for one block)
     return sizeof(S) == 4 ? (P <= 4 ? 5 : P == 5 ? 4 : 3) : (P <= 3 ? 5 : P == 4 ? 4 : P == 5 ? 3 : 2);
 }
 
@@ -294,7 +295,11 @@ constexpr int zt_min_waves()
 // 4.9 TB/s), 256^3 2.3 / 4.5 ms, 24^3 (P = 3) 8.0 us, 96^3 at P = 6 346 us; the
 // march by output tiles before it, with the windows in LDS, took 362 / 646 us,
 // 2.83 / 5.17 ms, 11.4 us and 632 us.  Skipping the second group's LDS reads on lanes
-// that are no node 0 (a branch) is 2 % slower to 2 % faster.
+// that are no node 0 (a branch) is 2 % slower to 2 % faster.  In FP64 the uniform weights
+// of orders 4, 5 and 6 spill 6, 52 and 202 scalar registers into lanes of vector
+// registers, in FP32 those of order 6 spill 26.  On a single cell (216 nodes, p = 6) the
+// chain of its one wave per plane takes 10.7 us in FP64 and 8.6 in FP32, against 8.8 and
+// 6.9 of the march; all its rows in flight at once do not shorten it.
 // NTH: non-temporal output stores (states larger than the Infinity Cache)
 template <typename S, int P, bool NTH, int NT>
 __global__ void __launch_bounds__(NT, (zt_min_waves<S, P, NT>()))
@@ -323,7 +328,7 @@ __global__ void __launch_bounds__(NT, (zt_min_waves<S, P, NT>()))
     S *dst = out + static_cast<int64_t>(pop * 45 + i) * N;
 
     // this lane's input column and output cell along y (surplus lanes repeat
-    // lane 0, as in the forward march); columns are counted in group order, so
+    // lane 0, as in the forward kernel); columns are counted in group order, so
     // that column e P + j of a row is input j of the group of cell e
     const int cx0 = tx * lay.txc, cy0 = ty * lay.tyc;
     int cyl = static_cast<int>((static_cast<float>(tid) + 0.5f) * lay.rcx), xl = tid - cyl * lay.cx;
@@ -458,7 +463,7 @@ __global__ void __launch_bounds__(NT, (zt_min_waves<S, P, NT>()))
             __builtin_amdgcn_sched_barrier(0);             // one output row's LDS reads at a time (registers)
         }
     };
-    // the first cell outside the loop, as in the forward march
+    // the first cell outside the loop, as in the forward kernel
     int c = zc0;
     if (c < zc1 - 1) {
         cell_step(std::false_type(), c);

@@ -4,7 +4,8 @@
 //
 // The outputs that read source cell c along an axis are P consecutive nodes,
 // (c - omin - 1)*P + lstar + j, j = 0 .. P-1, with weight row (lstar + j) mod P.
-// A lane takes one column (x) of NC source cells in a row along y: it loads their
+// A lane takes one column (x) of NC source cells in a row along y (one, where the
+// grid has no more): it loads their
 // NC*P + 1 nodes (all in flight at once), interpolates along y in registers with
 // the velocity's uniform weights and leaves NC*P values in LDS, from which the
 // block's lanes interpolate along x, one output column each.  While N_x <= 512 a
@@ -20,7 +21,8 @@
 namespace sllbm {
 
 // Bound by HBM and, while two states fit it, the Infinity Cache: 512^2 nodes, P =
-// 4, 24 us in FP64 (6.5 TB/s) and 14 us in FP32; 1024^2 115 us; 510^2 at P = 6 25 us.
+// 4, 24 us in FP64 (6.5 TB/s) and 14 us in FP32; 1024^2 115 us; 510^2 at P = 6 25 us;
+// the Sod tube of 800 x 4 nodes 3.0 us (3.3 with the march).
 // The march along y that this replaces (strips of 256 columns, chunks of 16
 // cells, each row interpolated along x out of LDS) took 26, 17, 127 and 33 us.
 template <typename S, int P, int NC>

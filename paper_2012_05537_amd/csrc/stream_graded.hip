@@ -484,8 +484,10 @@ int graded_cell_rows(int p, int most) { return most <= p + 1 ? p + 1 : most <= p
 // readers of a cell along x and y, and cells large enough for a block of one
 // (forward) or a few (transposed) along z.  Against the march, on the
 // cosine-graded mesh in FP64: forward P = 4, 64^3 nodes 77 against 139 us, 128^3 535
-// against 1003, P = 3, 24^3 12.5 against 21.6; but P = 2, FP32, 80 x 60 x 60 132 against
-// 104 and P = 1 374 against 160.  Transposed P = 4 96 against 267 and 684 against 1865 us, P = 2 57
+// against 1003, P = 3, 24^3 12.5 against 21.6; but P = 2, FP32, 80 x 60 x 60 135 against
+// 105 and 128^3 604 against 576 (in FP64 and on small FP32 grids P = 2 by cell is ahead:
+// 80 x 60 x 60 137 against 160, 128^3 618 against 768, 16^3 8.4 against 12.5, FP32 8.1
+// against 11.6; the march stays there as well) and P = 1 374 against 160.  Transposed P = 4 96 against 267 and 684 against 1865 us, P = 2 57
 // against 119; P = 1 176 against 175.
 bool graded_by_cell(const Geometry &g, bool transpose, int most, int my, size_t elem)
 {
