@@ -218,7 +218,7 @@ __global__ void __launch_bounds__(NT, (z_min_waves<S, P, NT>()))
 
 // NT: LDS columns of a block (z_columns), the fewest that hold its threads.
 // A block of one wave that kept 256 columns left a CU five waves at order 4 in FP64
-// (32 x 52 x 40 nodes: forward 24.9 us, transposed 34.2 us; 17.4 and 22.6 with its own
+// (32 x 52 x 40 nodes: forward 24.9 us, transposed 34.3 us; 16.8 and 21.1 with its own
 // LDS).  Strides known only at run time cost the transposed kernel registers (128^3
 // FP32 299 -> 348 us).
 template <int P, class Launch>
